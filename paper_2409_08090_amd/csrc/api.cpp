@@ -21,6 +21,7 @@
 #include "../../include/mils.h"
 #include "api_internal.h"
 #include "batch.h"
+#include "chip.h"
 #include "fft2.h"
 #include "index_math.h"
 #include "kernels.h"
@@ -38,6 +39,14 @@ struct PlanEntry {
   double* inv_phihat2 = nullptr; // two-pass plans: n doubles in last-pass order
   size_t bytes = 0;
 };
+
+// Tables of every sub-grid size and kernel of one tolerance.
+struct ChipSet {
+  ChipPlan plan[kChipKinds] = {};
+  char* buf = nullptr;
+  size_t bytes = 0;
+};
+constexpr int kChipStatus = 4;  // ints into the pinned status buffer
 
 // (nf, eps, precision, grids + 10 * batch, fixed grid size)
 using PlanKey = std::tuple<int64_t, double, int, int, int64_t, int>;
@@ -177,6 +186,13 @@ struct mils_context {
   bool batch_onchip = true;
   int64_t last_batch_onchip = 0;  // such series in the last batch built
   int* host_status = nullptr;  // pinned
+  // calls on sub-grids in LDS (chip.h): their tables by tolerance, the counter
+  // of their finished workgroups, and where the last one leaves the status
+  // (host_status + kChipStatus, as the device addresses it)
+  std::map<double, ChipSet> chips;
+  ChipDone* chip_done = nullptr;
+  int* chip_status = nullptr;
+  bool last_chip = false;  // the last call was one of these
   DevStats* last_stats = nullptr;
   int64_t last_illposed = 0;  // ill-posed frequencies of the last call whose status was read
   // plans built since the context was created, and the host time spent on them
@@ -403,6 +419,103 @@ int get_plan(mils_context* ctx, int64_t nf, double eps, int prec, int G, PlanEnt
   return MILS_OK;
 }
 
+// Tables of the sub-grids in LDS for tolerance eps: the host's part (the first
+// doubles of the tables), their size, and what finishes them at d.
+struct ChipTables {
+  std::vector<double> host;
+  size_t bytes = 0;
+  size_t o_hc[2], o_z[2], nz[2], o_tw[kChipBatchSizes], o_ph[kChipKinds];
+  ChipPlan plan[kChipKinds] = {};
+};
+
+void make_chip_tables(double eps, ChipTables* t) {
+  auto add = [&](const std::vector<double>& v) {
+    const size_t at = t->host.size();
+    t->host.insert(t->host.end(), v.begin(), v.end());
+    t->host.resize((t->host.size() + 31) & ~(size_t)31);
+    return at;
+  };
+  Plan kern[2] = {};
+  for (int wide = 0; wide < 2; ++wide) {
+    Plan& p = kern[wide];
+    chip_kernel(eps, wide != 0, &p.sigma, &p.w, &p.beta);
+    std::vector<double> z, gphi, hc;
+    phihat_nodes(p, &z, &gphi);
+    make_horner(p, &hc);
+    t->o_hc[wide] = add(hc);
+    t->nz[wide] = z.size();
+    z.insert(z.end(), gphi.begin(), gphi.end());
+    t->o_z[wide] = add(z);
+  }
+  std::vector<double> tw;
+  for (int i = 0; i < kChipBatchSizes; ++i) {
+    make_twiddle2(kChipBatchN[i], &tw);
+    t->o_tw[i] = add(tw);
+  }
+  size_t off = t->host.size();
+  for (int k = 0; k < kChipKinds; ++k) {
+    ChipPlan& c = t->plan[k];
+    const int wide = k / kChipBatchSizes;
+    c.N = kChipBatchN[k % kChipBatchSizes];
+    c.nfmax = (int)std::floor((double)c.N / kern[wide].sigma);
+    c.w = kern[wide].w;
+    c.hw = 0.5 * c.w;
+    t->o_ph[k] = off;
+    off += ((size_t)(c.nfmax / 2 + 1) + 31) & ~(size_t)31;
+  }
+  t->bytes = sizeof(double) * off;
+}
+
+// Uploads t to buf (t->bytes) and waits on stream s; plan[] then points there.
+hipError_t upload_chip_tables(const ChipTables& t, char* buf, ChipPlan* plan, hipStream_t s) {
+  double* d = reinterpret_cast<double*>(buf);
+  hipError_t he = hipMemcpyAsync(d, t.host.data(), sizeof(double) * t.host.size(),
+                                 hipMemcpyHostToDevice, s);
+  for (int k = 0; k < kChipKinds && he == hipSuccess; ++k) {
+    const int wide = k / kChipBatchSizes;
+    plan[k] = t.plan[k];
+    ChipPlan& c = plan[k];
+    c.hcoef = d + t.o_hc[wide];
+    c.tw = d + t.o_tw[k % kChipBatchSizes];
+    c.iph = d + t.o_ph[k];
+    he = launch_phihat(d + t.o_ph[k], c.nfmax / 2, (double)c.w, (double)c.N, d + t.o_z[wide],
+                       d + t.o_z[wide] + t.nz[wide], (int)t.nz[wide], s);
+  }
+  if (he == hipSuccess) he = hipStreamSynchronize(s);
+  if (he == hipSuccess) he = chip_prepare();
+  return he;
+}
+
+// The context's tables for tolerance eps (made on first use, all sizes
+// together: about 0.2 MB); NULL when they cannot be (no memory, the budget,
+// or make false): the caller then takes the staged path.
+const ChipSet* get_chip(mils_context* ctx, double eps, bool make) {
+  auto it = ctx->chips.find(eps);
+  if (it != ctx->chips.end()) return &it->second;
+  if (!make) return nullptr;
+  const auto t_build = std::chrono::steady_clock::now();
+  ChipTables t;
+  make_chip_tables(eps, &t);
+  ChipSet cs;
+  cs.bytes = t.bytes;
+  if (ctx->budget && ctx->plan_bytes + ctx->ws_bytes + cs.bytes > ctx->budget) return nullptr;
+  if (hipMalloc(reinterpret_cast<void**>(&cs.buf), cs.bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  // on the context's own stream: a caller's stream need not be ordered after
+  // the null stream
+  if (upload_chip_tables(t, cs.buf, cs.plan, ctx->aux) != hipSuccess) {
+    (void)hipGetLastError();
+    (void)hipFree(cs.buf);
+    return nullptr;
+  }
+  ctx->plan_bytes += cs.bytes;
+  mils_log(2, "on-chip tables eps=%g: w=%d, %.2f ms", eps, cs.plan[0].w,
+           1e3 * std::chrono::duration<double>(std::chrono::steady_clock::now() - t_build).count());
+  return &ctx->chips.emplace(eps, cs).first->second;
+}
+
 // Whether the single-series plan of (nf, eps, prec, G) exists with its device
 // tables (a call may then run without allocating).
 bool plan_ready(mils_context* ctx, int64_t nf, double eps, int prec, int G) {
@@ -586,6 +699,30 @@ CallArgs single_args(const double* t, const double* y, const double* dy, const d
   return a;
 }
 
+// Kind (see ChipSet) of a single-series call that runs in LDS, -1: staged.
+// One workgroup takes about 8 us and 0.011 us a point (measured at 100 to 8000
+// points) and the chip holds one per CU; the staged kernels of a short series
+// take about 60 us (launches) and 70 us per 1e6 frequencies.
+int chip_single_kind(mils_context* ctx, const Plan& plan, const CallArgs& a) {
+  if (plan.prec != 0 || a.deterministic) return -1;
+  double sigma, beta;
+  int w, best = -1;
+  chip_kernel(a.dmin, false, &sigma, &w, &beta);
+  double best_us = 60.0 + 70e-6 * (double)a.nf;
+  for (int i = 0; i < 2; ++i) {  // 256 and 1024 cells
+    const int N = kChipBatchN[i];
+    const int64_t D = chip_residues(a.nf, (int)std::floor((double)N / sigma));
+    const double rounds = std::ceil((double)(D + kLowMax) / ctx->num_cu);
+    const double us = rounds * ((N > 256 ? 10.0 : 8.0) + 0.011 * (double)a.nd);
+    if (us < best_us) {
+      best_us = us;
+      best = i;
+    }
+  }
+  // (a grid of one staged pass takes the widest kernel there too)
+  return best >= 0 && plan.npass == 1 ? best + kChipBatchSizes : best;
+}
+
 // Common body of the single-series calls.
 int run_single(mils_context* ctx, const double* t, const double* y, const double* dy,
                const double* h, int64_t nd, const mils_params* p, double* power, double* sums,
@@ -628,6 +765,19 @@ int run_single(mils_context* ctx, const double* t, const double* y, const double
   w.inv_phihat2 = pe->inv_phihat2;
 
   const CallArgs a = single_args(t, y, dy, h, nd, p, plan, power, sums);
+  const int kind = ctx->prof ? -1 : chip_single_kind(ctx, plan, a);
+  const ChipSet* cs = kind >= 0 ? get_chip(ctx, p->eps, !cap) : nullptr;
+  if (cs) {
+    const ChipPlan& cp = cs->plan[kind];
+    he = launch_chip_single(a, cp, (int)chip_residues(p->nf, cp.nfmax), w.stats, ctx->chip_done,
+                            ctx->chip_status, 1, 0, stream);
+    if (he != hipSuccess) return hip_fail(ctx, he, "kernel launch");
+    ctx->last_chip = true;
+    ctx->last_stream = stream;
+    ctx->have_pending = true;
+    return sync ? mils_context_status(ctx) : MILS_OK;
+  }
+  ctx->last_chip = false;
   StageHook hook{prof_hook, ctx};
   AuxStream aux{ctx->aux, ctx->ev_fork, ctx->ev_join, ctx->ev_mid};
   if (!ctx->prof && ctx->aux && ctx->sg.enabled && graphs_enabled()) {
@@ -704,6 +854,12 @@ int mils_context_create(int device, uint64_t hbm_budget_bytes, mils_context** ou
     if (he == hipSuccess) he = hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming);
     if (he == hipSuccess) he = hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming);
     if (he == hipSuccess) he = hipEventCreateWithFlags(&c->ev_mid, hipEventDisableTiming);
+    if (he == hipSuccess) he = hipMalloc(reinterpret_cast<void**>(&c->chip_done), kChipMaxSeries * sizeof(ChipDone));
+    if (he == hipSuccess) he = hipMemsetAsync(c->chip_done, 0, kChipMaxSeries * sizeof(ChipDone), c->aux);
+    if (he == hipSuccess) he = hipStreamSynchronize(c->aux);
+    if (he == hipSuccess)
+      he = hipHostGetDevicePointer(reinterpret_cast<void**>(&c->chip_status),
+                                   c->host_status + kChipStatus, 0);
     if (he != hipSuccess) {
       std::lock_guard<std::mutex> lk(g_err_mu);
       g_create_err = std::string("context init: ") + hipGetErrorString(he);
@@ -728,6 +884,8 @@ int mils_context_destroy(mils_context* ctx) {
     (void)hipDeviceSynchronize();
     for (auto& kv : ctx->plans)
       if (kv.second.tw) (void)hipFree(reinterpret_cast<char*>(kv.second.inv_phihat));
+    for (auto& kv : ctx->chips) (void)hipFree(kv.second.buf);
+    if (ctx->chip_done) (void)hipFree(ctx->chip_done);
     if (ctx->ws) (void)hipFree(ctx->ws);
     for (char* r : ctx->retired) (void)hipFree(r);
     free_batch_state(ctx->batch);
@@ -898,6 +1056,8 @@ struct ScratchTables {
   double eps = 0.0;
   int prec = 0;
   bool fft2 = false;
+  bool chip = false;  // tables of the sub-grids in LDS (for eps) instead
+  ChipPlan plan[kChipKinds] = {};
 };
 static std::mutex g_scratch_mu;
 static ScratchTables g_scratch_tables[kNoAllocDevices];
@@ -943,6 +1103,33 @@ static int mils_periodogram_noalloc_impl(mils_context* ctx, const double* t, con
   if (he != hipSuccess) return hip_fail(ctx, he, "hipSetDevice");
   char* base = static_cast<char*>(noalloc_scratch(ctx->device, &he));
   if (!base) return hip_fail(ctx, he, "scratch address");
+  const CallArgs a = single_args(t, y, dy, nullptr, nd, p, plan, power, nullptr);
+  const int kind = chip_single_kind(ctx, plan, a);
+  if (kind >= 0) {
+    // a short series on sub-grids in LDS, as in mils_periodogram: its tables
+    // and statistics in the scratch
+    ChipTables ct;
+    make_chip_tables(p->eps, &ct);
+    std::lock_guard<std::mutex> lk(g_scratch_mu);
+    ScratchTables& res = g_scratch_tables[ctx->device];
+    if (!(res.valid && res.chip && res.eps == p->eps)) {
+      res.valid = false;
+      he = upload_chip_tables(ct, base, res.plan, stream);
+      if (he != hipSuccess) return hip_fail(ctx, he, "scratch plan upload");
+      res.valid = true;
+      res.chip = true;
+      res.eps = p->eps;
+    }
+    const ChipPlan cp = res.plan[kind];
+    DevStats* st = reinterpret_cast<DevStats*>(base + up(ct.bytes));
+    he = launch_chip_single(a, cp, (int)chip_residues(p->nf, cp.nfmax), st, ctx->chip_done,
+                            ctx->chip_status, 1, 0, stream);
+    if (he != hipSuccess) return hip_fail(ctx, he, "kernel launch");
+    ctx->last_chip = true;
+    ctx->last_stream = stream;
+    ctx->have_pending = true;
+    return mils_context_status(ctx);
+  }
   double* inv_phihat = reinterpret_cast<double*>(base);
   char* twd = base + ph_b;
   double* nodes = reinterpret_cast<double*>(twd + tw_b);
@@ -952,7 +1139,7 @@ static int mils_periodogram_noalloc_impl(mils_context* ctx, const double* t, con
   {
     std::lock_guard<std::mutex> lk(g_scratch_mu);
     ScratchTables& res = g_scratch_tables[ctx->device];
-    const bool same = res.valid && res.nf == p->nf && res.eps == p->eps &&
+    const bool same = res.valid && !res.chip && res.nf == p->nf && res.eps == p->eps &&
                       res.prec == p->precision && res.fft2 == (bool)plan.fft2;
     if (!same) {
       res.valid = false;
@@ -983,6 +1170,7 @@ static int mils_periodogram_noalloc_impl(mils_context* ctx, const double* t, con
       if (he == hipSuccess) he = hipStreamSynchronize(stream);
       if (he != hipSuccess) return hip_fail(ctx, he, "scratch plan upload");
       res.valid = true;
+      res.chip = false;
       res.nf = p->nf;
       res.eps = p->eps;
       res.prec = p->precision;
@@ -994,11 +1182,11 @@ static int mils_periodogram_noalloc_impl(mils_context* ctx, const double* t, con
   w.tw = twd;
   w.inv_phihat = inv_phihat;
   w.inv_phihat2 = iphi2;
-  const CallArgs a = single_args(t, y, dy, nullptr, nd, p, plan, power, nullptr);
   AuxStream aux{ctx->aux, ctx->ev_fork, ctx->ev_join, ctx->ev_mid};
   he = launch_path(a, plan, w, stream, nullptr, ctx->aux ? &aux : nullptr);
   if (he != hipSuccess) return hip_fail(ctx, he, "kernel launch");
   ctx->last_stats = w.stats;
+  ctx->last_chip = false;
   ctx->last_stream = stream;
   ctx->have_pending = true;
   return mils_context_status(ctx);
@@ -1040,6 +1228,7 @@ static int run_direct(mils_context* ctx, const double* t, const double* y, const
   he = launch_direct(a, w, stream);
   if (he != hipSuccess) return hip_fail(ctx, he, "kernel launch");
   ctx->last_stats = w.stats;
+  ctx->last_chip = false;
   ctx->last_stream = stream;
   ctx->have_pending = true;
   return mils_context_status(ctx);
@@ -1133,7 +1322,23 @@ int mils_periodogram_shared_t(mils_context* ctx, const double* t, const double* 
   a.dmin = p->eps;
   a.periodogram = 1;
   const bool shared_w = (dy == nullptr || dy_stride == 0);
-  if (shared_w) {
+  // series as short as a single call on sub-grids in LDS: the same kernel,
+  // over the series side by side
+  const int kind = chip_single_kind(ctx, plan, a);
+  const ChipSet* cs = kind >= 0 ? get_chip(ctx, p->eps, true) : nullptr;
+  if (cs) {
+    const ChipPlan& cp = cs->plan[kind];
+    const int D = (int)chip_residues(p->nf, cp.nfmax);
+    for (int64_t i0 = 0; i0 < nseries && he == hipSuccess; i0 += kChipMaxSeries) {
+      CallArgs as = a;
+      as.y = y + i0 * nd;
+      as.dy = dy ? dy + i0 * dy_stride : nullptr;
+      as.power = power + i0 * p->nf;
+      he = launch_chip_single(as, cp, D, stats + i0, ctx->chip_done, ctx->chip_status,
+                              (int)std::min<int64_t>(kChipMaxSeries, nseries - i0), dy_stride,
+                              stream);
+    }
+  } else if (shared_w) {
     // the weight-only sums B and B2, once
     CallArgs aw = a;
     aw.unit_y = 1;
@@ -1182,7 +1387,7 @@ int mils_periodogram_shared_t(mils_context* ctx, const double* t, const double* 
   }
   if (he != hipSuccess) return hip_fail(ctx, he, "kernel launch");
   std::vector<DevStats> host(nst);
-  he = hipMemcpyAsync(host.data(), stats, sizeof(DevStats) * nst, hipMemcpyDeviceToHost, stream);
+  he = hipMemcpyAsync(host.data(), stats, sizeof(DevStats) * (size_t)nseries, hipMemcpyDeviceToHost, stream);
   if (he == hipSuccess) he = hipStreamSynchronize(stream);
   if (he != hipSuccess) return hip_fail(ctx, he, "status readback");
   ctx->have_pending = false;
@@ -1226,6 +1431,66 @@ int small_radices(int64_t n, signed char* rad) {
   return cnt;
 }
 
+// Workspace of a series on sub-grids in LDS (see layout_work).
+size_t layout_chip(int64_t nd, char* base, Work* w) {
+  auto up = [](size_t n) { return (n + 255) & ~(size_t)255; };
+  const size_t o_low = up(sizeof(DevStats)), o_rec = o_low + up(sizeof(double) * 6 * kLowMax);
+  if (w) {
+    *w = Work{};
+    w->stats = reinterpret_cast<DevStats*>(base);
+    w->lowfix = reinterpret_cast<double*>(base + o_low);
+    w->rec = reinterpret_cast<double*>(base + o_rec);
+  }
+  return o_rec + up(sizeof(double) * 2 * nd);
+}
+
+// The series of a batch that run on sub-grids in LDS: kind[c] (see ChipSet;
+// -1: not) and residues D[c].  A series takes the largest grid of the batch,
+// or the smallest that holds it whole.  The batch's grid is the one whose
+// estimated time is shortest: larger grids visit every point from fewer
+// workgroups, smaller ones spread few series over the chip.
+void choose_chip(const mils_context* ctx, const ChipSet& cs, const std::vector<int64_t>& idx,
+                 const int64_t* nd_off, const int64_t* nf_off, std::vector<int>* kind,
+                 std::vector<int>* D) {
+  const int64_t m = (int64_t)idx.size();
+  auto size_of = [&](int64_t nf, int top) {  // smallest grid up to top that holds nf whole
+    int i = 0;
+    while (i < top && nf > cs.plan[i].nfmax) ++i;
+    return i;
+  };
+  auto takes = [&](int64_t nd, int64_t nf) { return nd <= kChipBatchNd || nf <= kChipOneNf; };
+  int best = 0;
+  double best_cost = 1e300;
+  for (int top = 0; top < kChipBatchSizes; ++top) {
+    double total = 0.0, longest = 0.0;
+    for (int64_t c = 0; c < m; ++c) {
+      const int64_t nd = nd_off[idx[c] + 1] - nd_off[idx[c]];
+      const int64_t nf = nf_off[idx[c] + 1] - nf_off[idx[c]];
+      if (!takes(nd, nf)) continue;
+      const int i = size_of(nf, top);
+      // cycles of one residue (measured: 18 a point with the three grids at
+      // once, 33 one after another, and about 10 a cell)
+      const double one = (double)nd * (kChipBatchN[i] > 2048 ? 33.0 : 18.0) +
+                         10.0 * kChipBatchN[i] + 10000.0;
+      total += one * (double)chip_residues(nf, cs.plan[i].nfmax);
+      longest = std::max(longest, one);
+    }
+    const double cost = std::max(total / ctx->num_cu, longest);
+    if (cost < 0.97 * best_cost) {
+      best_cost = cost;
+      best = top;
+    }
+  }
+  for (int64_t c = 0; c < m; ++c) {
+    const int64_t nd = nd_off[idx[c] + 1] - nd_off[idx[c]];
+    const int64_t nf = nf_off[idx[c] + 1] - nf_off[idx[c]];
+    if (!takes(nd, nf)) continue;
+    const int k = size_of(nf, best) + (nf <= kChipWideNf ? kChipBatchSizes : 0);
+    (*kind)[c] = k;
+    (*D)[c] = (int)chip_residues(nf, cs.plan[k].nfmax);
+  }
+}
+
 // Body of mils_periodogram_batch; the serving loop calls it with
 // use_graph = false (its batches change with every call).
 // Builds the launches of a batch in B: the series idx[0..m) (indices into the
@@ -1237,13 +1502,25 @@ int build_batch(mils_context* ctx, BatchState& B, const std::vector<int64_t>& id
                 const std::vector<double>& sig, const std::vector<int>& tmax,
                 const int64_t* nd_off, const double* t, const double* y, const double* dy,
                 const int64_t* nf_off, const double* f0, const double* df,
-                const mils_params* common, double* power, int64_t nstatus, hipStream_t stream) {
+                const mils_params* common, double* power, int64_t nstatus, hipStream_t stream,
+                bool use_chip) {
   const int64_t m = (int64_t)idx.size();
   const int prec = common->precision;
   hipError_t he = hipSuccess;
+  // FP64 series on sub-grids in LDS (chip.h), each with its kind (grid size
+  // and kernel) and its number of residues; -1: a staged series (or, FP32
+  // forms, one whose grids fit LDS)
+  std::vector<int> chip_of(m, -1), chip_D(m, 0);
+  const ChipSet* chips = use_chip && prec == 0 ? get_chip(ctx, common->eps, true) : nullptr;
+  if (chips) choose_chip(ctx, *chips, idx, nd_off, nf_off, &chip_of, &chip_D);
   // grid size of each series, then grid-size classes (ratio <= 1.06) that share a plan
-  std::vector<int64_t> ngrid(m);
+  // A batch of one series makes its class's plan also when the series runs in
+  // LDS: the serving loop's warm-up runs one short series per class, and longer
+  // series of the class need the plan.
+  std::vector<int64_t> ngrid(m, 0);
+  const bool all_plans = m == 1;
   for (int64_t c = 0; c < m; ++c) {
+    if (chip_of[c] >= 0 && !all_plans) continue;
     const int64_t nf = nf_off[idx[c] + 1] - nf_off[idx[c]];
     auto k = std::make_tuple(nf, prec, common->eps, sig[c]);
     auto it = B.grid_of_nf.find(k);
@@ -1258,8 +1535,9 @@ int build_batch(mils_context* ctx, BatchState& B, const std::vector<int64_t>& id
     }
     ngrid[c] = it->second;
   }
-  std::vector<std::pair<int64_t, int>> ns(m);
-  for (int64_t c = 0; c < m; ++c) ns[c] = {ngrid[c], tmax[c]};
+  std::vector<std::pair<int64_t, int>> ns;
+  for (int64_t c = 0; c < m; ++c)
+    if (chip_of[c] < 0 || all_plans) ns.push_back({ngrid[c], tmax[c]});
   std::sort(ns.begin(), ns.end(), [](const std::pair<int64_t, int>& x, const std::pair<int64_t, int>& y) {
     return x.second != y.second ? x.second < y.second : x.first < y.first;
   });
@@ -1281,9 +1559,10 @@ int build_batch(mils_context* ctx, BatchState& B, const std::vector<int64_t>& id
   }
   const int ncls = (int)cls_n.size();
   std::vector<int64_t> cls_nf(ncls, 1);
-  std::vector<int> cls_of(m);
+  std::vector<int> cls_of(m, 0);
   std::vector<char> cls_tuned(ncls, 0);
   for (int64_t c = 0; c < m; ++c) {
+    if (chip_of[c] >= 0 && !all_plans) continue;
     cls_of[c] = cls_of_n[{ngrid[c], tmax[c]}];
     cls_nf[cls_of[c]] = std::max<int64_t>(cls_nf[cls_of[c]], nf_off[idx[c] + 1] - nf_off[idx[c]]);
     if (sig[c] > 1.0) cls_tuned[cls_of[c]] = 1;
@@ -1325,7 +1604,13 @@ int build_batch(mils_context* ctx, BatchState& B, const std::vector<int64_t>& id
     d.kzero = zero_index(d.f0, d.df, d.nf);
     d.plan = cls_of[c];
     d.index = (int)oc;
-    d.nsrad = ctx->batch_onchip ? small_radices(plans[cls_of[c]].n, d.srad) : 0;
+    if (chip_of[c] >= 0) {
+      d.small = 1;
+      d.nsrad = 0;
+      wsz[c] = layout_chip(d.nd, nullptr, nullptr);
+      continue;
+    }
+    d.nsrad = ctx->batch_onchip && prec == 1 ? small_radices(plans[cls_of[c]].n, d.srad) : 0;
     d.small = d.nsrad > 0;
     wsz[c] = (layout_work(plans[cls_of[c]], d.nd, 3, nullptr, nullptr, true) + 255) & ~(size_t)255;
   }
@@ -1351,18 +1636,29 @@ int build_batch(mils_context* ctx, BatchState& B, const std::vector<int64_t>& id
   // work items of every chunk
   struct ChunkItems {
     std::vector<BatchItem> spread, pass[kMaxPass - 1], last, small;
+    std::vector<BatchItem> chip_series, chip[kChipKinds];
     size_t small_lds = 0;
+    int staged = 0;  // series of the staged phases
+    int one = 0;     // series whose three grids fit one workgroup's LDS
   };
   std::vector<ChunkItems> ci(nchunks);
   for (int k = 0; k < nchunks; ++k) {
     for (int64_t c = chunk_begin[k]; c < chunk_begin[k + 1]; ++c) {
-      const Plan& q = plans[cls_of[c]];
       const int lc = (int)(c - chunk_begin[k]);
+      if (chip_of[c] >= 0) {
+        ci[k].chip_series.push_back({lc, 0, 0});
+        for (int r = 0; r < chip_D[c]; ++r) ci[k].chip[chip_of[c]].push_back({lc, r, chip_D[c]});
+        if (cur[c].nf <= kChipOneNf) ++ci[k].one;
+        continue;
+      }
+      const Plan& q = plans[cls_of[c]];
       if (cur[c].small) {
+        ++ci[k].one;
         ci[k].small.push_back({lc, 0, cls_of[c]});
         ci[k].small_lds = std::max(ci[k].small_lds, small_lds_bytes(q.n));
         continue;
       }
+      ++ci[k].staged;
       const int64_t ntl = (q.n + q.T - 1) / q.T;
       for (int64_t tl = 0; tl < ntl; ++tl) ci[k].spread.push_back({lc, (int)tl, cls_of[c]});
       for (int ip = 0; ip + 1 < q.npass; ++ip) {
@@ -1412,7 +1708,8 @@ int build_batch(mils_context* ctx, BatchState& B, const std::vector<int64_t>& id
   for (int k = 0; k < nchunks; ++k) {
     o_items[k] = off;
     off += list_bytes(ci[k].spread.size()) + list_bytes(ci[k].last.size()) +
-           list_bytes(ci[k].small.size());
+           list_bytes(ci[k].small.size()) + list_bytes(ci[k].chip_series.size());
+    for (const auto& v : ci[k].chip) off += list_bytes(v.size());
     for (int ip = 0; ip < kMaxPass - 1; ++ip) off += list_bytes(ci[k].pass[ip].size());
   }
   const size_t dev_bytes = off + 256;
@@ -1458,7 +1755,8 @@ int build_batch(mils_context* ctx, BatchState& B, const std::vector<int64_t>& id
   for (int k = 0; k < nchunks; ++k) {
     size_t woff = 0;
     for (int64_t c = chunk_begin[k]; c < chunk_begin[k + 1]; ++c) {
-      layout_work(plans[cls_of[c]], cur[c].nd, 3, B.ws + woff, &works[c], true);
+      if (chip_of[c] >= 0) layout_chip(cur[c].nd, B.ws + woff, &works[c]);
+      else layout_work(plans[cls_of[c]], cur[c].nd, 3, B.ws + woff, &works[c], true);
       woff += wsz[c];
     }
   }
@@ -1516,7 +1814,15 @@ int build_batch(mils_context* ctx, BatchState& B, const std::vector<int64_t>& id
     L.small_items = put(ci[k].small);
     L.nsmall = (int)ci[k].small.size();
     L.small_lds = ci[k].small_lds;
-    ctx->last_batch_onchip += L.nsmall;
+    L.nstaged = ci[k].staged;
+    L.chip_series = put(ci[k].chip_series);
+    L.nchip_series = (int)ci[k].chip_series.size();
+    for (int i = 0; i < kChipKinds; ++i) {
+      if (chips) L.chip[i] = chips->plan[i];
+      L.chip_items[i] = put(ci[k].chip[i]);
+      L.nchip_items[i] = (int)ci[k].chip[i].size();
+    }
+    ctx->last_batch_onchip += ci[k].one;
   }
   // the host vectors are released on return
   if (he == hipSuccess) he = hipStreamSynchronize(stream);
@@ -1588,7 +1894,7 @@ int autotune_batch(mils_context* ctx, int64_t ncurves, const int64_t* nd_off, co
       std::vector<double> sig(sample.size(), cv.first);
       std::vector<int> tm(sample.size(), cv.second);
       rc = build_batch(ctx, T, sample, sig, tm, nd_off, t, y, dy, nf_off, f0, df, common, power,
-                       ncurves, stream);
+                       ncurves, stream, false);
       if (rc == MILS_ERR_UNSUPPORTED) {  // this sigma does not plan for the band
         rc = MILS_OK;
         continue;
@@ -1688,7 +1994,7 @@ int mils_batch_run(mils_context* ctx, int64_t ncurves, const int64_t* nd_off, co
   if (!(B.valid && B.key == key)) {
     B.valid = false;
     int rc = build_batch(ctx, B, idx, sig, tmax, nd_off, t, y, dy, nf_off, f0, df, common, power,
-                         ncurves, stream);
+                         ncurves, stream, ctx->batch_onchip);
     if (rc != MILS_OK) return rc;
     B.key = key;
     B.valid = true;
@@ -1824,13 +2130,16 @@ int mils_context_status(mils_context* ctx) {
   if (!ctx->have_pending) return MILS_OK;
   static_assert(offsetof(DevStats, nill) == offsetof(DevStats, status) + sizeof(int),
                 "status and count are read together");
-  hipError_t he = hipMemcpyAsync(ctx->host_status, &ctx->last_stats->status, 2 * sizeof(int),
-                                 hipMemcpyDeviceToHost, ctx->last_stream);
+  hipError_t he = hipSuccess;
+  if (!ctx->last_chip)
+    he = hipMemcpyAsync(ctx->host_status, &ctx->last_stats->status, 2 * sizeof(int),
+                        hipMemcpyDeviceToHost, ctx->last_stream);
   if (he == hipSuccess) he = hipStreamSynchronize(ctx->last_stream);
   if (he != hipSuccess) return hip_fail(ctx, he, "status readback");
   ctx->have_pending = false;
-  int st = ctx->host_status[0];
-  ctx->last_illposed = st == 0 ? ctx->host_status[1] : 0;
+  const volatile int* word = ctx->host_status + (ctx->last_chip ? kChipStatus : 0);
+  int st = word[0];
+  ctx->last_illposed = st == 0 ? word[1] : 0;
   if (st == -1) return fail(ctx, MILS_ERR_INVALID_ARG, "non-finite input or dy <= 0");
   if (st == -2) return fail(ctx, MILS_ERR_DEGENERATE, "constant data: zero reference chi^2");
   return MILS_OK;

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "chip.h"
 #include "mils_internal.h"
 
 namespace mils {
@@ -33,7 +34,7 @@ struct BatchCurve {
   int64_t kzero;    // output index of the zero frequency, or -1
   int plan;         // grid-size class (index into the plan arrays)
   int index;        // position of the series in the caller's order
-  int small;        // 1: the whole pipeline in one workgroup's LDS (k_bsmall)
+  int small;        // 1: grids in LDS (chip.h, or k_bsmall for FP32 forms): no staged phase
   int nsrad;        // radix stages of the in-LDS transform of the n-cell grid
   signed char srad[kSmallMaxRad];
 };
@@ -82,6 +83,14 @@ struct BatchLaunch {
   int nlast;
   const BatchItem* small_items;      // series that run entirely in LDS
   int nsmall;
+  int nstaged;                       // series that run through the staged phases
+  // FP64 series on sub-grids in LDS (chip.h): the series, and the (series,
+  // residue) items of each kind (item: sub = residue, plan = D)
+  const BatchItem* chip_series;
+  int nchip_series;
+  ChipPlan chip[kChipKinds];
+  const BatchItem* chip_items[kChipKinds];
+  int nchip_items[kChipKinds];
   size_t small_lds;                  // dynamic LDS of that launch (largest grid)
   size_t pass_lds[kMaxPass - 1];     // dynamic LDS of each pass launch
   size_t last_lds;

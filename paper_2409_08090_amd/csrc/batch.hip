@@ -481,9 +481,19 @@ __global__ __launch_bounds__(NT) void k_bsmall(BatchArgs ba, const BatchItem* it
 template <typename Real>
 hipError_t launch_t(const BatchLaunch& bl, hipStream_t s) {
   const BatchArgs& ba = bl.args;
-  if (bl.nsmall > 0)
-    hipLaunchKernelGGL(k_bsmall<Real>, dim3(bl.nsmall), dim3(NT), bl.small_lds, s, ba,
-                       bl.small_items);
+  if (bl.nchip_series > 0) {
+    hipError_t e = launch_chip_prologue(ba, bl.chip_series, bl.nchip_series, s);
+    // the largest sub-grids first: their workgroups run longest
+    for (int i = kChipKinds - 1; i >= 0 && e == hipSuccess; --i)
+      if (bl.nchip_items[i] > 0)
+        e = launch_chip_items(ba, bl.chip[i], bl.chip_items[i], bl.nchip_items[i], s);
+    if (e != hipSuccess) return e;
+  }
+  if constexpr (sizeof(Real) == 4)
+    if (bl.nsmall > 0)
+      hipLaunchKernelGGL(k_bsmall<Real>, dim3(bl.nsmall), dim3(NT), bl.small_lds, s, ba,
+                         bl.small_items);
+  if (bl.nstaged == 0) return hipGetLastError();
   hipLaunchKernelGGL(k_bpro, dim3(ba.ncurves), dim3(NT), 0, s, ba);
   if (bl.nspread > 0)
     hipLaunchKernelGGL(k_bspread2<Real>, dim3(bl.nspread), dim3(NT), 0, s, ba, bl.spread_items);
@@ -515,11 +525,9 @@ hipError_t batch_prepare() {
   std::lock_guard<std::mutex> lk(mu);
   const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
   if (bit && (done & bit)) return hipSuccess;
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_bsmall<double>),
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_bsmall<float>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSmallLdsCap);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_bsmall<float>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSmallLdsCap);
+  if (e == hipSuccess) e = chip_prepare();
   if (e == hipSuccess) done |= bit;
   return e;
 }

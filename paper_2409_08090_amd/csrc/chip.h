@@ -1,0 +1,83 @@
+// chip.h -- periodograms whose grids never leave the chip (chip.hip).
+//
+// The frequencies of a series are split by residue: k = rho + D kappa, rho <
+// D.  The sums over kappa for one rho are the same transform again (first
+// frequency f0 + rho df, step D df, about nf / D frequencies), on a grid of
+// N ~ 1.28 nf / D cells.  With D chosen so that N is one of a few powers of
+// two, one workgroup takes one rho: it spreads all points of the series onto
+// its grids in LDS, transforms them there and writes its share of the power.
+// Nothing but the points and the power crosses HBM, no grid size needs a plan
+// of its own, and a series is spread over D workgroups.  Every point is
+// visited by D workgroups, so this is the cheaper way up to a limit on nd.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "mils_internal.h"
+
+namespace mils {
+
+// One sub-grid size: the kernel (shared by every size of a tolerance), the
+// factors 1 / phihat(m) and the two-level table of exp(2 pi i x / N).
+struct ChipPlan {
+  int N;                // grid cells (a power of two)
+  int nfmax;            // most frequencies of a sub-transform
+  int w;                // kernel width (even)
+  double hw;            // w / 2
+  const double* hcoef;  // kernel polynomials (see kHornerK), FP64
+  const double* iph;    // 1 / phihat(m), m = 0 .. nfmax / 2
+  const double* tw;     // tw2_count(N) complex
+};
+
+// Status of a single call in host memory (written by the call's last
+// workgroup) and the counter that finds that workgroup; zero between calls.
+struct ChipDone {
+  unsigned long long count;
+};
+
+// The whole periodogram (or, without a.periodogram, the raw sums) of one
+// series on grids of cp.N cells, one workgroup per residue of D.
+// host_status: device address of two pinned ints (status, ill-posed count).
+// nseries > 1: series i of the same times has its values at a.y + i nd, its
+// errors at a.dy + i dy_stride, its power at a.power + i nf, its statistics in
+// st[i] and its counter in done[i] (at most kChipMaxSeries; host_status is
+// series 0's).
+constexpr int kChipMaxSeries = 64;
+hipError_t launch_chip_single(const CallArgs& a, const ChipPlan& cp, int D, DevStats* st,
+                              ChipDone* done, int* host_status, int nseries, int64_t dy_stride,
+                              hipStream_t s);
+
+// Sub-grid sizes; single calls take one of the first two.
+constexpr int kChipBatchN[] = {256, 1024, 2048, 4096, 8192};
+constexpr int kChipBatchSizes = 5;
+// kinds of a batch's items: a grid size with the tolerance's kernel, or with
+// the widest one
+constexpr int kChipKinds = 2 * kChipBatchSizes;
+// most frequencies of a series that takes the widest kernel (its whole grid
+// fits one pass of the staged path, which does the same), and of a series
+// whose three grids would fit one workgroup's LDS whole
+constexpr int64_t kChipWideNf = 800, kChipOneNf = 2400;
+// Most points of a batched series.  Here a series costs about D (33 nd + 10 N)
+// cycles of one CU (N = 8192, D = nf / 6400), in the staged phases about
+// 700 nd and the launches of every phase: 419 series of 8192 to 10000 points
+// took 5.8 ms there and 4.1 ms here.
+constexpr int64_t kChipBatchNd = 16384;
+
+// Residues (workgroups) of a series on sub-grids of at most nfmax frequencies.
+inline int64_t chip_residues(int64_t nf, int nfmax) { return (nf + nfmax - 1) / nfmax; }
+
+// Batch: the statistics of the on-chip series and their point records
+// (prologue, one workgroup per series), then one workgroup per item (series,
+// residue) and grid size.
+struct BatchArgs;
+struct BatchItem;
+hipError_t launch_chip_prologue(const BatchArgs& ba, const BatchItem* series, int n,
+                                hipStream_t s);
+hipError_t launch_chip_items(const BatchArgs& ba, const ChipPlan& cp, const BatchItem* items,
+                             int n, hipStream_t s);
+
+// Allows the kernels their dynamic LDS (once per device, before any launch).
+hipError_t chip_prepare();
+
+}  // namespace mils

@@ -150,6 +150,7 @@ struct Work {
   double* lowpart;        // per-block partial direct sums near f = 0
   double* lowfix;         // direct sums A, B, B2 near f = 0: kLowParts rows of kLowMax x 6
   uint64_t* keys;         // det_keys(nd) sort keys of the reproducible binning
+  double* rec;            // on-chip series of a batch: nd pairs (w^ y~, w^)
 };
 
 // Keys of the reproducible binning: the next power of two >= nd (>= 2).

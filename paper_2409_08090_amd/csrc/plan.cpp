@@ -196,6 +196,18 @@ double planner_sigma(double eps, int prec, bool batch) { return choose_sigma(eps
 
 double kernel_beta(int w, double sigma) { return 0.97 * M_PI * w * (1.0 - 1.0 / (2.0 * sigma)); }
 
+void chip_kernel(double eps, bool wide, double* sigma, int* w, double* beta) {
+  // 1.28, the factor that the smooth grid sizes of ordinary plans come to;
+  // 2 when that would need a kernel wider than kMaxWidth cells
+  double s = 1.28;
+  if (std::log(width_margin(0) / eps) / (M_PI * std::sqrt(1.0 - 1.0 / s)) > kMaxWidth) s = 2.0;
+  int wi = wide ? kMaxWidth : kernel_width(eps, s, 0);
+  wi += wi & 1;
+  *sigma = s;
+  *w = wi;
+  *beta = kernel_beta(wi, s);
+}
+
 bool make_plan(const PlanRequest& r, Plan* out, std::string* err) {
   Plan p{};
   p.prec = r.prec;
@@ -485,6 +497,16 @@ void make_twiddles(Plan* p, std::vector<double>* tw) {
     }
   }
   p->tw_count = (int64_t)(tw->size() / 2);
+}
+
+void make_twiddle2(int L, std::vector<double>* tw) {
+  tw->clear();
+  for (int i = 0; i < tw2_count(L); ++i) {
+    const int x = i < kTwLo ? i : (i - kTwLo) * kTwLo;
+    const long double ang = 2.0L * 3.14159265358979323846264338327950288L * (long double)x / (long double)L;
+    tw->push_back((double)cosl(ang));
+    tw->push_back((double)sinl(ang));
+  }
 }
 
 void phihat_nodes(const Plan& p, std::vector<double>* z, std::vector<double>* gphi) {

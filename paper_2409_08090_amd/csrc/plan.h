@@ -37,6 +37,11 @@ int kernel_width(double eps, double sigma, int prec);
 // Shape parameter of the exponential-of-semicircle kernel.
 double kernel_beta(int w, double sigma);
 
+// Kernel of the sub-grids in LDS (chip.h): upsampling factor, width (even)
+// and shape for a tolerance.  wide: the widest kernel, for transforms of a
+// handful of frequencies.
+void chip_kernel(double eps, bool wide, double* sigma, int* w, double* beta);
+
 // Build the plan; returns false (with a message) when no supported
 // factorisation exists.
 bool make_plan(const PlanRequest& r, Plan* out, std::string* err);
@@ -44,6 +49,9 @@ bool make_plan(const PlanRequest& r, Plan* out, std::string* err);
 // Twiddle tables of the plan, as interleaved (re, im) pairs in FP64; the
 // caller narrows them to FP32 for FP32 plans.  Offsets are stored in the plan.
 void make_twiddles(Plan* p, std::vector<double>* tw);
+
+// Two-level table of exp(2 pi i x / L) (see kTwLo), interleaved pairs.
+void make_twiddle2(int L, std::vector<double>* tw);
 
 // Gauss-Legendre nodes z_r in (0, 1) and the products g_r * phi(z_r) used by
 // the phihat kernel (even rule of q points on [-1, 1], positive half).
