@@ -279,11 +279,13 @@ int64_t mils_context_illposed(const mils_context *ctx);
  * (same arguments, results and statuses) with every sum accumulated over the
  * points in FP64 for every frequency -- O(nd * nf) work, no transform, no
  * approximation beyond FP64 rounding (p->eps and p->precision are ignored).
- * Per point, the phase at the first of each thread's 12 consecutive
- * frequencies is reduced in double-double and the next ones follow by
- * multiplication with exp(2 pi i df (t - t_min)).  Synchronous.  About 5 s
- * at nd = 1e6, nf = 1.2e7 on one MI355X; a check of the transform path at
- * any size.
+ * The phase factors of a point at the frequencies f_q +- (r + 1/2) df are
+ * products of one for f_q and one for the offset, each reduced in
+ * double-double; their sums over the points run on the FP64 matrix cores.
+ * The workspace also holds the partial sums of a call of few frequencies (at
+ * most 100 MB, none where the context's budget leaves no room).
+ * Synchronous.  About 2.7 s at nd = 1e6, nf = 1.2e7 on one MI355X; a check of
+ * the transform path at any size.
  */
 int mils_direct_periodogram(mils_context *ctx, const double *t, const double *y,
                             const double *dy, int64_t nd, const mils_params *p, double *power,

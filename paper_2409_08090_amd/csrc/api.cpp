@@ -1204,8 +1204,23 @@ static int run_direct(mils_context* ctx, const double* t, const double* y, const
   hipError_t he = hipSetDevice(ctx->device);
   if (he != hipSuccess) return hip_fail(ctx, he, "hipSetDevice");
   const size_t sb = (sizeof(DevStats) + 255) & ~(size_t)255;
-  int rc = ensure_workspace(ctx, sb + sizeof(double) * 8 * kStatsBlocks);
+  const size_t base = sb + sizeof(double) * 8 * kStatsBlocks;
+  // slices of the points, so that there are two workgroups per CU (of at least
+  // 64 points); one, with no sums to keep, where the budget leaves no room
+  const int64_t ntile = (p->nf + kDirectTile - 1) / kDirectTile;
+  int nslice = (int)std::max<int64_t>(
+      1, std::min<int64_t>(2 * ctx->num_cu / ntile, (nd + 63) / 64));
+  size_t need = base + direct_part_bytes(p->nf, y != nullptr, nslice);
+  if (nslice > 1 && need > ctx->ws_bytes && ctx->budget && ctx->plan_bytes + need > ctx->budget)
+    nslice = 1;
+  int rc = ensure_workspace(ctx, base + direct_part_bytes(p->nf, y != nullptr, nslice));
+  if (rc == MILS_ERR_OOM && nslice > 1) {
+    nslice = 1;
+    rc = ensure_workspace(ctx, base);
+  }
   if (rc != MILS_OK) return rc;
+  he = direct_prepare();
+  if (he != hipSuccess) return hip_fail(ctx, he, "direct setup");
   Work w{};
   w.stats = reinterpret_cast<DevStats*>(ctx->ws);
   w.partials = reinterpret_cast<double*>(ctx->ws + sb);
@@ -1225,7 +1240,7 @@ static int run_direct(mils_context* ctx, const double* t, const double* y, const
   a.periodogram = y ? 1 : 0;
   a.power = power;
   a.sums = sums;
-  he = launch_direct(a, w, stream);
+  he = launch_direct(a, w, nslice, reinterpret_cast<double*>(ctx->ws + base), stream);
   if (he != hipSuccess) return hip_fail(ctx, he, "kernel launch");
   ctx->last_stats = w.stats;
   ctx->last_chip = false;

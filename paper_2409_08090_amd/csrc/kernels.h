@@ -65,10 +65,24 @@ struct SeriesGroup {
 hipError_t launch_series_group(const CallArgs& a, const Plan& p, const Work& w,
                                const SeriesGroup& sg, hipStream_t s);
 
-// Direct sums at every frequency, term by term, FP64 (statistics into
-// w.stats, which with w.partials is all of w it uses): the power (a.power) or,
-// with a.periodogram == 0, the raw sums of a.h (a.sums, interleaved re/im).
-hipError_t launch_direct(const CallArgs& a, const Work& w, hipStream_t s);
+// Statistics of the call into w.stats.
+void enqueue_stats(const CallArgs& a, const Work& w, hipStream_t s);
+
+// Direct sums at every frequency, term by term, FP64 (direct.hip; statistics
+// into w.stats, which with w.partials is all of w it uses): the power
+// (a.power) or, with a.periodogram == 0, the raw sums of a.h (a.sums,
+// interleaved re/im).  The points are split into nslice slices; more than one
+// leaves its sums in part (direct_part_bytes).
+constexpr int kDirectTile = 4096;  // frequencies of a workgroup
+inline size_t direct_part_bytes(int64_t nf, bool periodogram, int nslice) {
+  return nslice > 1 ? sizeof(double) * (periodogram ? 6 : 2) * (size_t)nslice *
+                          (size_t)((nf + kDirectTile - 1) / kDirectTile * kDirectTile)
+                    : 0;
+}
+hipError_t launch_direct(const CallArgs& a, const Work& w, int nslice, double* part,
+                         hipStream_t s);
+// Allows the kernels their LDS (before their first launch on a device).
+hipError_t direct_prepare();
 
 // 1 / phihat in the order of the two-pass FFT's last pass (see k_phihat2).
 hipError_t launch_phihat2(double* iphi2, const double* inv_phihat, int L0, int L1, int64_t n,
