@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmils.so")
 BUILD = os.path.join(HERE, "_build")
 
-SOURCES = ["kernels.hip", "batch.hip", "chip.hip", "direct.hip", "noalloc.hip", "plan.cpp", "api.cpp", "server.cpp"]
+SOURCES = ["kernels.hip", "batch.hip", "chip.hip", "direct.hip", "spread.hip", "noalloc.hip", "plan.cpp", "api.cpp", "server.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -25,9 +25,14 @@ FLAGS = [
 ]
 
 
+# spread kernels: no hoisting of FP64 literals into registers (spread.hip)
+NO_HOIST = ["-mllvm", "-disable-machine-licm"]
+FILE_FLAGS = {"spread.hip": NO_HOIST, "chip.hip": NO_HOIST}
+
+
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC, *FLAGS, *FILE_FLAGS.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         sys.stderr.write(r.stdout + r.stderr)

@@ -1690,9 +1690,11 @@ int build_batch(mils_context* ctx, BatchState& B, const std::vector<int64_t>& id
   }
   // dynamic LDS of each pass launch (largest class that takes part)
   size_t pass_lds[kMaxPass - 1] = {0, 0, 0}, last_lds = 0;
+  int wmax = 0;
   const size_t elem = prec == 1 ? 8 : 16;
   for (int k = 0; k < ncls; ++k) {
     const Plan& q = plans[k];
+    wmax = std::max(wmax, q.w);
     for (int ip = 0; ip + 1 < q.npass; ++ip) {
       const FftPass& ps = q.pass[ip];
       pass_lds[ip] = std::max(pass_lds[ip], elem * (size_t)(ps.L * ps.C + ps.L) + ps.L + 16);
@@ -1818,6 +1820,7 @@ int build_batch(mils_context* ctx, BatchState& B, const std::vector<int64_t>& id
     };
     L.spread_items = put(ci[k].spread);
     L.nspread = (int)ci[k].spread.size();
+    L.wmax = wmax;
     for (int ip = 0; ip < kMaxPass - 1; ++ip) {
       L.pass_items[ip] = put(ci[k].pass[ip]);
       L.npass_items[ip] = (int)ci[k].pass[ip].size();

@@ -77,6 +77,7 @@ struct BatchLaunch {
   int prec;
   const BatchItem* spread_items;     // every tile of every series (both geometries use them)
   int nspread;
+  int wmax;                          // widest kernel of the staged series' plans
   const BatchItem* pass_items[kMaxPass - 1];  // first/middle pass ip
   int npass_items[kMaxPass - 1];
   const BatchItem* last_items;

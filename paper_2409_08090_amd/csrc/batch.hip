@@ -256,14 +256,9 @@ __global__ __launch_bounds__(NT) void k_bpro(BatchArgs ba) {
 // plan are fetched once): geometry f into A and B, then geometry 2f into B2,
 // each only where the prologue's row flags say a kernel support reaches the
 // tile; a tile of empty rows returns after reading its flags.
-template <typename Real>
+template <typename Real, int SETS>
 __global__ __launch_bounds__(NT) void k_bspread2(BatchArgs ba, const BatchItem* items) {
   __shared__ double acc[2 * 2 * kTileMax];
-  __shared__ int rb[8], re[8], sv[2];
-  __shared__ union {
-    SpreadRecords<Real, 2, NT> two;
-    SpreadRecords<Real, 1, NT> one;
-  } rec;
   __shared__ Plan sp;
   const BatchItem it = items[blockIdx.x];
   const BatchCurve c = ba.curves[it.curve];
@@ -286,11 +281,11 @@ __global__ __launch_bounds__(NT) void k_bspread2(BatchArgs ba, const BatchItem* 
   __syncthreads();
   const CallArgs a = curve_args(ba, c);
   if (any_f)
-    spread_tile<Real, 1, 2, NT, true>(it.sub, sp.T, kTileMax, a, sp, w, st, 0, nullptr, acc, rb,
-                                      re, sv, rec.two);
+    spread_tile<Real, 1, 2, NT, SETS>(it.sub, sp.T, kTileMax, a, sp, w, st, w.grid[0], w.grid[1],
+                                      acc);
   if (any_2f)
-    spread_tile<Real, 2, 1, NT, true>(it.sub, sp.T, kTileMax, a, sp, w, st, 2, nullptr, acc, rb,
-                                      re, sv, rec.one);
+    spread_tile<Real, 2, 1, NT, SETS>(it.sub, sp.T, kTileMax, a, sp, w, st, w.grid[2], w.grid[2],
+                                      acc);
 }
 
 // A first/middle FFT pass ip.  FP64: one workgroup per (series, column
@@ -496,7 +491,8 @@ hipError_t launch_t(const BatchLaunch& bl, hipStream_t s) {
   if (bl.nstaged == 0) return hipGetLastError();
   hipLaunchKernelGGL(k_bpro, dim3(ba.ncurves), dim3(NT), 0, s, ba);
   if (bl.nspread > 0)
-    hipLaunchKernelGGL(k_bspread2<Real>, dim3(bl.nspread), dim3(NT), 0, s, ba, bl.spread_items);
+    hipLaunchKernelGGL((bl.wmax > 16 ? k_bspread2<Real, 2> : k_bspread2<Real, 1>),
+                       dim3(bl.nspread), dim3(NT), 0, s, ba, bl.spread_items);
   for (int ip = 0; ip < kMaxPass - 1; ++ip)
     if (bl.npass_items[ip] > 0)
       hipLaunchKernelGGL(k_bpass<Real>, dim3(bl.npass_items[ip]), dim3(NT), bl.pass_lds[ip], s,

@@ -102,34 +102,8 @@ __device__ __forceinline__ DevStats chip_stats(const CallArgs& a, Part* sh) {
 }
 
 // ---- spread -----------------------------------------------------------------
-// Lane I of every row of 16 lanes, broadcast to its row.
-template <int I>
-__device__ __forceinline__ double row_lane(double x) {
-  return __builtin_amdgcn_update_dpp(0.0, x, 0x150 + I, 0xf, 0xf, true);
-}
-template <int I>
-__device__ __forceinline__ int row_lane(int x) {
-  return __builtin_amdgcn_update_dpp(0, x, 0x150 + I, 0xf, 0xf, true);
-}
-
-// A lane's kernel polynomials: cell lane mod 16 of a support and, for kernels
-// wider than 16 cells (SETS = 2), cell 16 + lane mod 16.
-template <int SETS>
-struct LaneKernel {
-  double c[SETS][kHornerN64];
-};
-template <int SETS>
-__device__ __forceinline__ void load_kernel(LaneKernel<SETS>& lk, const double* tab) {
-  const int cell = threadIdx.x & 15;
-#pragma unroll
-  for (int s = 0; s < SETS; ++s)
-#pragma unroll
-    for (int j = 0; j < kHornerN64; ++j)
-      lk.c[s][j] = cell + 16 * s < kHornerK ? tab[j * kHornerK + cell + 16 * s] : 0.0;
-}
-
 template <int NG, int AP, int SETS, int I>
-__device__ __forceinline__ void add_points(double* acc, const LaneKernel<SETS>& lk, int w,
+__device__ __forceinline__ void add_points(double* acc, const LaneKernel<double, SETS>& lk, int w,
                                            int cnt, int lb, double u, const double* h) {
   if constexpr (I < 16) {
     // (four points a step; cnt is the same for the whole wave, and lanes
@@ -139,11 +113,7 @@ __device__ __forceinline__ void add_points(double* acc, const LaneKernel<SETS>& 
     double* cell = acc + row_lane<I>(lb) + (threadIdx.x & 15);
     double v[SETS];
 #pragma unroll
-    for (int s = 0; s < SETS; ++s) {
-      v[s] = lk.c[s][0];
-#pragma unroll
-      for (int j = 1; j < kHornerN64; ++j) v[s] = __builtin_fma(v[s], ui, lk.c[s][j]);
-    }
+    for (int s = 0; s < SETS; ++s) v[s] = kernel_value(lk, s, ui);
 #pragma unroll
     for (int c = 0; c < 2 * NG; ++c) {
       const double hi = row_lane<I>(h[c]);
@@ -164,7 +134,7 @@ __device__ __forceinline__ void add_points(double* acc, const LaneKernel<SETS>& 
 // the points' values come from their lanes by DPP broadcasts, with no LDS and
 // no barrier.
 template <int N, int NG, int AP, int SETS>
-__device__ __forceinline__ void chip_add(double* acc, const LaneKernel<SETS>& lk,
+__device__ __forceinline__ void chip_add(double* acc, const LaneKernel<double, SETS>& lk,
                                          const ChipPlan& cp, int cnt, double fh, double pl,
                                          const double* h) {
   const double uh = (double)N * fh, ul = (double)N * pl;  // exact: N is a power of two
@@ -206,7 +176,7 @@ __device__ __forceinline__ PointPhase point_phase(double t, double tau, double g
 // the raw strengths (which = 0).  fetch(j, t, ha, hb): point j's time and real
 // strengths.
 template <int N, int NT, bool ALL, int AP, int SETS, typename Fetch>
-__device__ __forceinline__ void chip_spread(double* acc, const LaneKernel<SETS>& lk,
+__device__ __forceinline__ void chip_spread(double* acc, const LaneKernel<double, SETS>& lk,
                                             const ChipPlan& cp, int nd, double tau, double gh,
                                             double gl, double fch, double fcl, int which,
                                             const Fetch& fetch) {
@@ -389,7 +359,7 @@ __device__ __forceinline__ int chip_residue(const CallArgs& a, const DevStats& s
   };
   int nan_count = 0;
   if constexpr (!PG || !S::seq) {
-    LaneKernel<SETS> lk;
+    LaneKernel<double, SETS> lk;
     load_kernel(lk, coef);
     clear();
     chip_spread<N, NT, PG, AP, SETS>(acc, lk, cp, nd, st.tau, gh, gl, fch, fcl, 0, fetch);
@@ -421,28 +391,24 @@ __device__ __forceinline__ int chip_residue(const CallArgs& a, const DevStats& s
     }
   } else {
     static_assert(TL == NT, "one line of N / E threads");
-    double2 va[E], vb[E], vc[E];
-    for (int g = 0; g < 3; ++g) {
-      // (opaque, so that the transform's LDS addresses are not kept in
-      // registers from one grid to the next)
+    // one grid after another (t is opaque in each, so that the transform's LDS
+    // addresses are not kept in registers from one grid to the next)
+    auto one_grid = [&](double2(&v)[E], int g) {
       int t = tid;
       asm volatile("" : "+v"(t));
-      clear();  // (its barrier also keeps the polynomials from being loaded once for all grids)
-      LaneKernel<SETS> lk;
+      clear();
+      LaneKernel<double, SETS> lk;
       load_kernel(lk, coef);
       chip_spread<N, NT, false, AP, SETS>(acc, lk, cp, nd, st.tau, gh, gl, fch, fcl, g, fetch);
       fold();
-      load(vc, 0, t);
+      load(v, 0, t);
       __syncthreads();
-      chip_line<N>(vc, t, line, twl, true);
-      if (g == 0) {
-#pragma unroll
-        for (int q = 0; q < E; ++q) va[q] = vc[q];
-      } else if (g == 1) {
-#pragma unroll
-        for (int q = 0; q < E; ++q) vb[q] = vc[q];
-      }
-    }
+      chip_line<N>(v, t, line, twl, true);
+    };
+    double2 va[E], vb[E], vc[E];
+    one_grid(va, 0);
+    one_grid(vb, 1);
+    one_grid(vc, 2);
 #pragma unroll
     for (int j = 0; j < E; ++j) {
       const int m = tid + TL * j;

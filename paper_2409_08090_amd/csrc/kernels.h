@@ -65,6 +65,11 @@ struct SeriesGroup {
 hipError_t launch_series_group(const CallArgs& a, const Plan& p, const Work& w,
                                const SeriesGroup& sg, hipStream_t s);
 
+// Spread of geometry geo (1: f, 2: 2f) into grids gbase .. gbase + ng - 1 of w
+// (spread.hip), over the active rows listed in w.
+void enqueue_spread(const CallArgs& a, const Plan& p, const Work& w, int geo, int ng, int gbase,
+                    hipStream_t s);
+
 // Statistics of the call into w.stats.
 void enqueue_stats(const CallArgs& a, const Work& w, hipStream_t s);
 

@@ -433,28 +433,6 @@ static void enqueue_row_class(const Plan& p, const Work& w, int nd, int geo0, in
   hipLaunchKernelGGL(k_row_compact, dim3((unsigned)ngeo), dim3(kRowThreads), 0, s, p, w, geo0);
 }
 
-// Spreading over the tiles of the active rows only (their list and count come
-// from k_row_compact): a fixed grid of workgroups takes tiles blk, blk + grid,
-// ...; every tile is written by exactly one workgroup, so the result does not
-// depend on scheduling.  T divides the row length S1 here.
-template <typename Real, int GEO, int NG, bool DET = false>
-__global__ __launch_bounds__(kThreads) void k_spread_rows(CallArgs a, Plan p, Work w, int gbase,
-                                                          const int* act_rows, int slot) {
-  __shared__ double acc[NG * 2 * kTileMax];
-  __shared__ int rb[8], re[8], sv[2];
-  __shared__ SpreadRecords<Real, NG, kThreads> rec;
-  const DevStats* stp = w.stats;
-  if (stp->status != 0) return;
-  const int tpr = (int)(p.S1 / p.T);
-  const int ntile = w.nact[slot] * tpr;
-  for (int t = blockIdx.x; t < ntile; t += gridDim.x) {
-    const int q = t / tpr;
-    const int tile = act_rows[q] * tpr + (t - q * tpr);
-    spread_tile<Real, GEO, NG, kThreads, true, DET>(tile, p.T, kTileMax, a, p, w, *stp, gbase,
-                                                    nullptr, acc, rb, re, sv, rec);
-  }
-}
-
 // ============================================================================
 // FFT passes.
 // ============================================================================
@@ -1207,22 +1185,13 @@ static hipError_t launch_path_t(const CallArgs& a, const Plan& p, const Work& w,
     if (e != hipSuccess) return e;
   }
 
-  const int64_t ntiles = (p.S1 / p.T) * p.nrows;
-  const unsigned sgrid = (unsigned)(ntiles < kSpreadGrid ? ntiles : kSpreadGrid);
   // The f geometry (row classes, spread and then the first FFT pass of its
   // two grids) is the longer branch: it is launched (and captured) first.
   mark(kStageSpreadF, 1, s);
   if (!rows_first)
     enqueue_row_class(p, w, nd, 0, 1, s);
-  if (a.periodogram && a.deterministic)
-    hipLaunchKernelGGL((k_spread_rows<Real, 1, 2, true>), dim3(sgrid), dim3(kThreads), 0, s, a, p,
-                       w, 0, w.act_rows_f, 0);
-  else if (a.periodogram)
-    hipLaunchKernelGGL((k_spread_rows<Real, 1, 2>), dim3(sgrid), dim3(kThreads), 0, s, a, p, w, 0,
-                       w.act_rows_f, 0);
-  else
-    hipLaunchKernelGGL((k_spread_rows<Real, 1, 1>), dim3(sgrid), dim3(kThreads), 0, s, a, p, w, 0,
-                       w.act_rows_f, 0);
+  if (a.periodogram) enqueue_spread(a, p, w, 1, 2, 0, s);
+  else enqueue_spread(a, p, w, 1, 1, 0, s);
   mark(kStageSpreadF, 0, s);
   if (a.periodogram && !p.fft2) {
     mark(kStageLow, 1, s2);
@@ -1233,12 +1202,7 @@ static hipError_t launch_path_t(const CallArgs& a, const Plan& p, const Work& w,
     mark(kStageSpread2F, 1, s2);
     if (!rows_first)
       enqueue_row_class(p, w, nd, 1, 1, s2);
-    if (a.deterministic)
-      hipLaunchKernelGGL((k_spread_rows<Real, 2, 1, true>), dim3(sgrid), dim3(kThreads), 0, s2, a,
-                         p, w, 2, w.act_rows_2f, 1);
-    else
-      hipLaunchKernelGGL((k_spread_rows<Real, 2, 1>), dim3(sgrid), dim3(kThreads), 0, s2, a, p, w,
-                         2, w.act_rows_2f, 1);
+    enqueue_spread(a, p, w, 2, 1, 2, s2);
     mark(kStageSpread2F, 0, s2);
   }
   if (p.fft2) {
@@ -1367,14 +1331,10 @@ static hipError_t launch_weight_sums_t(const CallArgs& aw, const Plan& p, const 
   using T2 = typename cplx<Real>::T;
   enqueue_stats(aw, w, s);
   enqueue_bins(aw, p, w, s);
-  const int64_t ntiles = (p.S1 / p.T) * p.nrows;
-  const unsigned sgrid = (unsigned)(ntiles < kSpreadGrid ? ntiles : kSpreadGrid);
   const int nd = (int)aw.nd;
   enqueue_row_class(p, w, nd, 0, 2, s);
-  hipLaunchKernelGGL((k_spread_rows<Real, 1, 1>), dim3(sgrid), dim3(kThreads), 0, s, aw, p, w, 1,
-                     w.act_rows_f, 0);
-  hipLaunchKernelGGL((k_spread_rows<Real, 2, 1>), dim3(sgrid), dim3(kThreads), 0, s, aw, p, w, 2,
-                     w.act_rows_2f, 1);
+  enqueue_spread(aw, p, w, 1, 1, 1, s);
+  enqueue_spread(aw, p, w, 2, 1, 2, s);
   T2* in[2];
   enqueue_passes<Real>(p, w, 1, 2, 2, s, in);
   CallArgs as = aw;
@@ -1396,8 +1356,6 @@ template <typename Real>
 static hipError_t launch_series_group_t(const CallArgs& a, const Plan& p, const Work& w,
                                         const SeriesGroup& sg, hipStream_t s) {
   using T2 = typename cplx<Real>::T;
-  const int64_t ntiles = (p.S1 / p.T) * p.nrows;
-  const unsigned sgrid = (unsigned)(ntiles < kSpreadGrid ? ntiles : kSpreadGrid);
   CallArgs al = a;
   al.nser = sg.m;
   for (int g = 0; g < sg.m; ++g) {
@@ -1412,8 +1370,7 @@ static hipError_t launch_series_group_t(const CallArgs& a, const Plan& p, const 
     enqueue_stats(ag, wg, s);
     if (sg.need_sort) enqueue_bins(ag, p, wg, s);
     enqueue_lowfreq(ag, wg, s);
-    hipLaunchKernelGGL((k_spread_rows<Real, 1, 1>), dim3(sgrid), dim3(kThreads), 0, s, ag, p, wg,
-                       g, w.act_rows_f, 0);
+    enqueue_spread(ag, p, wg, 1, 1, g, s);
     al.spow[g] = sg.power[g];
     al.sst[g] = sg.stats[g];
     al.slow[g] = sg.lowfix[g];

@@ -52,8 +52,10 @@ __device__ __forceinline__ void add_cell_range(int* rb, int* re, int& cnt, int64
     ++cnt;
     return;
   }
-  int64_t x0 = c0 % n;
+  // (c0 is within one period of [0, n): no division)
+  int64_t x0 = c0;
   if (x0 < 0) x0 += n;
+  else if (x0 >= n) x0 -= n;
   const int64_t x1 = x0 + (c1 - c0);
   const int64_t e1 = x1 <= n ? x1 : n;
   rb[cnt] = bs[x0 >> p.Tb_shift];
@@ -105,218 +107,353 @@ __device__ __forceinline__ bool row_active(int64_t r, int h, const Plan& p, cons
   return tot > 0;
 }
 
-// Per-point records of one chunk of NT points of a spreading tile (LDS): the
-// first covered cell relative to the tile (kSpreadNone: the point misses the
-// tile), the kernel argument u and the NG complex strengths (component c of
-// grid g at h[(2g + c) NT + i]).
-constexpr int kSpreadNone = -(1 << 30);
+// Lane I of every row of 16 lanes, broadcast to its row (one DPP move).
+template <int I, typename V>
+__device__ __forceinline__ V row_lane(V x) {
+  return __builtin_amdgcn_update_dpp((V)0, x, 0x150 + I, 0xf, 0xf, true);
+}
+
+// A lane's kernel polynomials: cell lane mod 16 of a support and, for kernels
+// wider than 16 cells (SETS = 2), cell 16 + lane mod 16 (zero past the
+// kernel's width).
+template <typename Real, int SETS>
+struct LaneKernel {
+  static constexpr int N = sizeof(Real) == 8 ? kHornerN64 : kHornerN32;
+  Real c[SETS][N];
+};
+template <typename Real, int SETS>
+__device__ __forceinline__ void load_kernel(LaneKernel<Real, SETS>& lk, const Real* tab) {
+  const int cell = threadIdx.x & 15;
+#pragma unroll
+  for (int s = 0; s < SETS; ++s)
+#pragma unroll
+    for (int j = 0; j < LaneKernel<Real, SETS>::N; ++j)
+      lk.c[s][j] = cell + 16 * s < kHornerK ? tab[j * kHornerK + cell + 16 * s] : (Real)0;
+}
+template <typename Real, int SETS>
+__device__ __forceinline__ Real kernel_value(const LaneKernel<Real, SETS>& lk, int s, Real u) {
+  Real v = lk.c[s][0];
+#pragma unroll
+  for (int j = 1; j < LaneKernel<Real, SETS>::N; ++j) v = v * u + lk.c[s][j];
+  return v;
+}
+
+// Statistics of the call through the constant address space (they do not
+// change during the kernels that use this): scalar loads.
+__device__ __forceinline__ DevStats load_stats(const DevStats* src) {
+  static_assert(sizeof(DevStats) % 4 == 0, "whole words");
+  DevStats st;
+  const ConstPtr<int> q = (ConstPtr<int>)(const int*)src;
+  int* d = reinterpret_cast<int*>(&st);
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(DevStats) / 4); ++i) d[i] = q[i];
+  return st;
+}
+
+// Where the spread reads the points: the caller's arrays or, after a sort, the
+// sorted copies.
+struct PointSource {
+  const double* t;
+  const double* y;   // y, or the raw strengths
+  const double* dy;  // NULL: unit weights
+};
+__device__ __forceinline__ PointSource point_source(const CallArgs& a, const Work& w,
+                                                    const DevStats& st) {
+  PointSource s;
+  if (st.need_sort) {
+    s.t = w.ts;
+    s.y = a.periodogram ? w.ys : w.hs;
+    s.dy = a.periodogram ? w.dys : nullptr;
+  } else {
+    s.t = a.t;
+    s.y = a.periodogram ? a.y : a.h;
+    s.dy = a.periodogram ? a.dy : nullptr;
+  }
+  return s;
+}
+
+// First cell of a point's support relative to cell a0 (mod n, in (-n, n - w])
+// and its kernel argument u.
+template <typename Real, int GEO>
+__device__ __forceinline__ void point_cell(double t, const DevStats& st, const CallArgs& a,
+                                           const Plan& p, int64_t a0, int& lb, Real& u) {
+  int cell;
+  double frac;
+  const int n = (int)p.n;
+  grid_coord32(t, st.tau, GEO * a.df, (double)p.n, n, cell, frac);
+  const int o0 = (int)ceil(frac - p.hw);
+  lb = cell + o0 - (int)a0;  // in (-2n, n)
+  if (lb < 0) lb += n;
+  if (lb < 0) lb += n;
+  if (lb > n - p.w) lb -= n;
+  // u = 2t - 1, t = o0 + hw - frac in [0, 1)
+  u = (Real)(2.0 * ((double)o0 + p.hw - frac) - 1.0);
+}
+
+// The complex strengths of a point: component c of grid g at h[2 g + c].
+template <typename Real, int GEO, int NG>
+__device__ __forceinline__ void point_strengths(double t, double y, double dv,
+                                                const DevStats& st, const CallArgs& a,
+                                                double invW, Real* h) {
+  double pc, ps;
+  prephase(t, st.tau, a.fch, a.fcl, pc, ps);
+  if (a.periodogram) {
+    const double wj = 1.0 / (dv * dv);
+    const double wh = wj * invW;
+    if (GEO == 1) {
+      const double yt = a.unit_y ? 1.0 : y - st.ysub;
+      h[0] = (Real)(wh * yt * pc);
+      h[1] = (Real)(wh * yt * ps);
+      if (NG > 1) {
+        h[2 * NG - 2] = (Real)(wh * pc);
+        h[2 * NG - 1] = (Real)(wh * ps);
+      }
+    } else {
+      // exp(2 i theta) from exp(i theta)
+      h[0] = (Real)(wh * (pc * pc - ps * ps));
+      h[1] = (Real)(wh * (2.0 * pc * ps));
+    }
+  } else {
+    h[0] = (Real)(y * pc);
+    h[1] = (Real)(y * ps);
+  }
+}
+
+// Value and error of point j as far as geometry GEO needs them (0 and 1 else).
+template <int GEO>
+__device__ __forceinline__ void point_values(const PointSource& src, const CallArgs& a, int j,
+                                             double& y, double& dv) {
+  y = GEO == 1 && !a.unit_y ? src.y[j] : 0.0;
+  dv = src.dy ? src.dy[j] : 1.0;
+}
+
+// The point ranges of the cyclic cell interval [c0, c1), c0 within one period
+// of [0, n): b0..e0 and, past the period's end, b1..e1.  Every lane of the
+// workgroup computes them alike, so the loads are scalar ones.
+struct CellRanges {
+  int b0, e0, b1, e1;
+};
+__device__ __forceinline__ CellRanges cell_ranges(int c0, int c1, const Plan& p, const int* bin_start,
+                                                  int nd) {
+  const ConstPtr<int> bs = (ConstPtr<int>)bin_start;
+  const int n = (int)p.n;
+  CellRanges r = {0, nd, 0, 0};
+  if (c1 - c0 >= n) return r;
+  int x0 = c0 < 0 ? c0 + n : c0 >= n ? c0 - n : c0;
+  const int x1 = x0 + (c1 - c0);
+  const int e1 = x1 <= n ? x1 : n;
+  r.b0 = bs[x0 >> p.Tb_shift];
+  r.e0 = bs[((e1 - 1) >> p.Tb_shift) + 1];
+  if (x1 > n) {
+    r.b1 = bs[0];
+    r.e1 = bs[((x1 - n - 1) >> p.Tb_shift) + 1];
+  }
+  return r;
+}
+
+constexpr int kSpreadNone = -(1 << 30);  // first cell of a point that misses the tile
+
+// Four points of the wave at a time (lanes I .. of the four rows of 16), every
+// lane its cell of the support: see spread_tile.
+template <typename Real, int NG, int SETS, int I>
+__device__ __forceinline__ void add_wave_points(double* acc, int tcap, int T, int n, int w,
+                                                const LaneKernel<Real, SETS>& lk, int cnt, int lb,
+                                                Real u, const Real* h) {
+  if constexpr (I < 16) {
+    // (cnt is the same for the whole wave; lanes without a point miss the tile)
+    if (I % 4 == 0 && I >= cnt) return;
+    const Real ui = row_lane<I>(u);
+    const int first = row_lane<I>(lb) + (int)(threadIdx.x & 15);
+    Real hi[2 * NG];
+#pragma unroll
+    for (int c = 0; c < 2 * NG; ++c) hi[c] = row_lane<I>(h[c]);
+#pragma unroll
+    for (int s = 0; s < SETS; ++s) {
+      const Real v = kernel_value(lk, s, ui);
+      int x = first + 16 * s;
+      if (x < 0) x += n;
+      else if (x >= n) x -= n;
+      if ((unsigned)x < (unsigned)T && (s == 0 || (int)(threadIdx.x & 15) + 16 < w)) {
+#pragma unroll
+        for (int c = 0; c < 2 * NG; ++c) atomicAdd(&acc[c * tcap + x], (double)(v * hi[c]));
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    add_wave_points<Real, NG, SETS, I + 1>(acc, tcap, T, n, w, lk, cnt, lb, u, h);
+  }
+}
+
+// Spread one tile of geometry GEO into NG grids: cells [tile*T, tile*T + T)
+// of the flat grid, where T either divides the row length S1 of the
+// [nrows][S1] view or is a whole number of rows; the caller knows that the
+// tile lies in an active row.  out0, out1: the grids (passed apart: an index
+// into w.grid known only at run time puts the kernel's whole argument into
+// scratch memory).  acc: LDS accumulator of NG*2*tcap doubles
+// (T <= tcap; doubles for FP32 grids too: on gfx950 the LDS atomic add of
+// doubles runs at full rate while that of floats waits ~50x longer per
+// instruction).  Called by every thread of the workgroup (it contains
+// barriers).
+//
+// Each wave takes 64 points of the tile's ranges at a time, one per lane, and
+// adds them four at a time: 16 lanes take one point's cells, each with its
+// own polynomial in registers and the point's values by DPP broadcast from
+// its lane, so that a row's adds are one run of cells and the waves need
+// neither records in LDS nor barriers between the clearing and the store.
+// Bound by the latency of a tile's loads and by FP64 arithmetic (both
+// geometries of the 1e6-point curve: 47 us of it).  Against records in LDS, a
+// barrier per 256 points and arguments in scratch: both spreads of that curve,
+// side by side, 115 -> 73 us (FP32 100 -> 55), 1e5 points 27 -> 17 us.
+template <typename Real, int GEO, int NG, int NT, int SETS>
+__device__ __forceinline__ void spread_tile(int tile, int Tt, int tcap, const CallArgs& a,
+                                            const Plan& p, const Work& w, const DevStats& st,
+                                            void* out0, void* out1, double* acc) {
+  using T2 = typename cplx<Real>::T;
+  const int tid = threadIdx.x;
+  const int n = (int)p.n, nd = (int)a.nd;
+  const int a0 = tile * Tt;
+  const int T = n - a0 < Tt ? n - a0 : Tt;
+  const int h = (int)ceil(p.hw) + 1;
+  CellRanges ra, rb = {0, 0, 0, 0};
+  if constexpr (GEO == 1) {
+    ra = cell_ranges(a0 - h, a0 + T + h, p, w.bin_start, nd);
+  } else {
+    // u_2f = 2 u_f mod n: the cyclic interval [c0, c1) has the two pre-images
+    // [c0/2, c1/2) and [(c0+n)/2, (c1+n)/2) in u_f (one cell of slack each side)
+    const int c0 = a0 - h, c1 = a0 + T + h;
+    if (c1 - c0 + 8 >= n) {
+      ra = {0, nd, 0, 0};
+    } else {
+      ra = cell_ranges((int)floordiv2(c0) - 1, (int)ceildiv2(c1) + 1, p, w.bin_start, nd);
+      rb = cell_ranges((int)floordiv2((int64_t)c0 + n) - 1, (int)ceildiv2((int64_t)c1 + n) + 1, p,
+                       w.bin_start, nd);
+    }
+  }
+  for (int x = tid; x < T; x += NT) {
+#pragma unroll
+    for (int c = 0; c < 2 * NG; ++c) acc[c * tcap + x] = 0.0;
+  }
+  LaneKernel<Real, SETS> lk;
+  load_kernel(lk, (const Real*)p.hcoef);
+  __syncthreads();
+  const PointSource src = point_source(a, w, st);
+  const double invW = 1.0 / st.W;
+  // a kernel support can meet the tile at most once unless the tile spans
+  // nearly the whole periodic grid
+  const bool wrap_free = T <= n - p.w;
+  const int lane = tid & 63;
+#pragma unroll 1
+  for (int r = 0; r < 2 * GEO; ++r) {
+    const int jbeg = r == 0 ? ra.b0 : r == 1 ? ra.b1 : r == 2 ? rb.b0 : rb.b1;
+    const int jend = r == 0 ? ra.e0 : r == 1 ? ra.e1 : r == 2 ? rb.e0 : rb.e1;
+    for (int j0 = jbeg + (tid - lane); j0 < jend; j0 += NT) {
+      const int j = j0 + lane;
+      int lb = kSpreadNone;
+      Real u = 0, hs[2 * NG] = {};
+      if (j < jend) {
+        // (all three loads at once: few points of the ranges miss the tile)
+        const double t = src.t[j];
+        double y, dv;
+        point_values<GEO>(src, a, j, y, dv);
+        point_cell<Real, GEO>(t, st, a, p, a0, lb, u);
+        if (wrap_free && (lb >= T || lb + p.w <= 0)) lb = kSpreadNone;
+        point_strengths<Real, GEO, NG>(t, y, dv, st, a, invW, hs);
+      }
+      add_wave_points<Real, NG, SETS, 0>(acc, tcap, T, n, p.w, lk, jend - j0, lb, u, hs);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    T2* out = reinterpret_cast<T2*>(g == 0 ? out0 : out1) + a0;
+    for (int x = tid; x < T; x += NT) {
+      T2 v;
+      v.x = (Real)acc[(2 * g) * tcap + x];
+      v.y = (Real)acc[(2 * g + 1) * tcap + x];
+      out[x] = v;
+    }
+  }
+  __syncthreads();  // acc is reused by the next tile
+}
+
+// The same in a fixed order (bitwise-reproducible sums): a chunk of NT points
+// at a time leaves its records in LDS, and each thread adds them one after
+// another to the cells x = tid, tid + NT, ... that it owns.
 template <typename Real, int NG, int NT>
 struct SpreadRecords {
   int lb[NT];
   Real u[NT];
   Real h[2 * NG * NT];
 };
-
-// Spread one tile of geometry GEO into NG grids: cells [tile*T, tile*T + T)
-// of the flat grid, where T either divides the row length S1 of the
-// [nrows][S1] view or is a whole number of rows.  Unless KNOWN (the caller
-// already knows that the tile lies in an active row and has written the row
-// flags), the flag of every row that starts inside the tile is written and a
-// tile of inactive rows returns at once.  acc: LDS accumulator of NG*2*tcap
-// doubles (T <= tcap; doubles for FP32 grids too: on gfx950 the LDS atomic
-// add of doubles runs at full rate while that of floats waits ~50x longer
-// per instruction); rb, re: 8 LDS ints each; sv: 2 LDS ints.  Called by
-// every thread of the workgroup (it contains barriers).
-template <typename Real, int GEO, int NG, int NT, bool KNOWN = false, bool DET = false>
-__device__ void spread_tile(int tile, int Tt, int tcap, const CallArgs& a, const Plan& p,
-                            const Work& w, const DevStats& st, int gbase, unsigned char* rowflag,
-                            double* acc, int* rb, int* re, int* sv,
-                            SpreadRecords<Real, NG, NT>& rec) {
+template <typename Real, int GEO, int NG, int NT>
+__device__ void spread_tile_det(int tile, int Tt, int tcap, const CallArgs& a, const Plan& p,
+                                const Work& w, const DevStats& st, void* out0, void* out1,
+                                double* acc, int* rb, int* re, int* sv,
+                                SpreadRecords<Real, NG, NT>& rec) {
   using T2 = typename cplx<Real>::T;
   const int tid = threadIdx.x;
   const int64_t a0 = (int64_t)tile * Tt;
   const int T = (int)((p.n - a0) < Tt ? (p.n - a0) : Tt);
-  const int h = (int)ceil(p.hw) + 1;
   const int nd = (int)a.nd;
-  const int* bs = w.bin_start;
-  if (KNOWN) {
-    if (tid == 0) {
-      sv[1] = 1;
-      sv[0] = gather_ranges<GEO>(rb, re, a0 - h, a0 + T + h, p, bs, nd);
-    }
-  } else if (tid == 0) {
-    const int64_t r0 = a0 / p.S1, r1 = (a0 + T - 1) / p.S1;
-    int any = 0;
-    for (int64_t r = r0; r <= r1; ++r) {
-      int cnt = gather_ranges<GEO>(rb, re, r * p.S1 - h, (r + 1) * p.S1 + h, p, bs, nd);
-      int tot = 0;
-      for (int i = 0; i < cnt; ++i) tot += re[i] - rb[i];
-      const int active = tot > 0;
-      if (r * p.S1 >= a0) rowflag[r] = (unsigned char)active;
-      any |= active;
-    }
-    sv[1] = any;
-    sv[0] = any ? gather_ranges<GEO>(rb, re, a0 - h, a0 + T + h, p, bs, nd) : 0;
-  }
-  __syncthreads();
-  const int active = sv[1];
-  const int nr = sv[0];
-  if (!active) {
-    __syncthreads();  // sv/rb/re are reused by the next tile
-    return;
+  if (tid == 0) {
+    const int h = (int)ceil(p.hw) + 1;
+    sv[0] = gather_ranges<GEO>(rb, re, a0 - h, a0 + T + h, p, w.bin_start, nd);
   }
   for (int x = tid; x < T; x += NT) {
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      acc[(2 * g) * tcap + x] = 0;
-      acc[(2 * g + 1) * tcap + x] = 0;
-    }
+    for (int c = 0; c < 2 * NG; ++c) acc[c * tcap + x] = 0.0;
   }
   __syncthreads();
-
-  const bool sorted = !st.need_sort;
-  const double tau = st.tau;
+  const int nr = sv[0];
+  const PointSource src = point_source(a, w, st);
   const double invW = 1.0 / st.W;
-  const double ysub = st.ysub;
-  const double gstep = GEO * a.df;
   const int n = (int)p.n;
-  const double nreal = (double)p.n;
-  const int wd = p.w;
-  const double hw = p.hw;
-  // a kernel support can meet the tile at most once unless the tile spans
-  // nearly the whole periodic grid
-  const bool wrap_free = T <= n - wd;
-  const double* tt = sorted ? a.t : w.ts;
-  const double* yy = a.periodogram ? (sorted ? a.y : w.ys) : (sorted ? a.h : w.hs);
-  const double* dd = sorted ? a.dy : w.dys;
-  const bool have_dy = a.periodogram && (sorted ? a.dy != nullptr : true);
-  // Lane layout of the accumulation: KL consecutive lanes take one point,
-  // lane kk adding the kernel value at the point's cell lb + kk; each lane
-  // holds the polynomial of its offset kk in registers.  The Q = 64/KL points
-  // a wave takes at once lie a quarter chunk apart in the (sorted) point
-  // order, so their runs of cells do not meet.
-  constexpr int NC = sizeof(Real) == 8 ? kHornerN64 : kHornerN32;
-  const int KL = wd <= 16 ? 16 : 32;
-  const int kk = tid & (KL - 1);
-  const int grp = tid / KL;          // group of KL lanes
-  const int Q = 64 / KL;             // groups per wave
-  const int wave = tid >> 6;
-  const int q = grp - wave * Q;      // group within the wave
-  const int nwave = NT / 64;
+  const bool wrap_free = T <= n - p.w;
+  constexpr int NC = LaneKernel<Real, 1>::N;
   const ConstPtr<Real> hc = (ConstPtr<Real>)(p.hcoef);
-  Real cf[NC];
-#pragma unroll
-  for (int j = 0; j < NC; ++j) cf[j] = kk < kHornerK ? hc[j * kHornerK + kk] : (Real)0;
   for (int r = 0; r < nr; ++r) {
     const int jend = re[r];
     for (int base = rb[r]; base < jend; base += NT) {
-      // (1) one point per thread: its record
-      {
-        const int j = base + tid;
-        int lbv = kSpreadNone;
-        if (j < jend) {
-          const double t = tt[j];
-          int cell;
-          double frac;
-          grid_coord32(t, tau, gstep, nreal, n, cell, frac);
-          const int o0 = (int)ceil(frac - hw);
-          int lb = cell + o0 - (int)a0;  // in (-2n, n)
-          if (lb < 0) lb += n;
-          if (lb < 0) lb += n;
-          if (lb > n - wd) lb -= n;
-          if (!(wrap_free && (lb >= T || lb + wd <= 0))) {
-            lbv = lb;
-            double pc, ps;
-            prephase(t, tau, a.fch, a.fcl, pc, ps);
-            Real hre[NG], him[NG];
-            if (a.periodogram) {
-              double wj = 1.0;
-              if (have_dy) {
-                const double dv = dd[j];
-                wj = 1.0 / (dv * dv);
-              }
-              const double wh = wj * invW;
-              if (GEO == 1) {
-                const double yt = a.unit_y ? 1.0 : yy[j] - ysub;
-                hre[0] = (Real)(wh * yt * pc);
-                him[0] = (Real)(wh * yt * ps);
-                if (NG > 1) {
-                  hre[NG - 1] = (Real)(wh * pc);
-                  him[NG - 1] = (Real)(wh * ps);
-                }
-              } else {
-                // exp(2 i theta) from exp(i theta)
-                hre[0] = (Real)(wh * (pc * pc - ps * ps));
-                him[0] = (Real)(wh * (2.0 * pc * ps));
-              }
-            } else {
-              const double hv = yy[j];
-              hre[0] = (Real)(hv * pc);
-              him[0] = (Real)(hv * ps);
-            }
-            // kernel argument: u = 2t - 1, t = o0 + hw - frac in [0, 1)
-            rec.u[tid] = (Real)(2.0 * ((double)o0 + hw - frac) - 1.0);
+      const int j = base + tid;
+      int lb = kSpreadNone;
+      if (j < jend) {
+        const double t = src.t[j];
+        Real u, h[2 * NG];
+        point_cell<Real, GEO>(t, st, a, p, a0, lb, u);
+        if (wrap_free && (lb >= T || lb + p.w <= 0)) lb = kSpreadNone;
+        else {
+          double y, dv;
+          point_values<GEO>(src, a, j, y, dv);
+          point_strengths<Real, GEO, NG>(t, y, dv, st, a, invW, h);
+          rec.u[tid] = u;
 #pragma unroll
-            for (int g = 0; g < NG; ++g) {
-              rec.h[(2 * g) * NT + tid] = hre[g];
-              rec.h[(2 * g + 1) * NT + tid] = him[g];
-            }
-          }
+          for (int c = 0; c < 2 * NG; ++c) rec.h[c * NT + tid] = h[c];
         }
-        rec.lb[tid] = lbv;
       }
+      rec.lb[tid] = lb;
       __syncthreads();
-      // (2) the chunk's points, KL lanes each
       const int cnt = jend - base < NT ? jend - base : NT;
-      if constexpr (DET) {
-        // fixed order: each thread owns cells x = tid, tid + NT, ... of the
-        // tile and adds the chunk's points to them one after another (no
-        // atomics; the point order is the binning's, itself fixed)
-        for (int i = 0; i < cnt; ++i) {
-          const int lb = rec.lb[i];
-          if (lb == kSpreadNone) continue;
-          const Real u = rec.u[i];
-          for (int x = tid; x < T; x += NT) {
-            int off = x - lb;  // cell offset within the point's support, mod n
-            if (off < 0) off += n;
-            else if (off >= n) off -= n;
-            if (off >= wd) continue;
-            Real v = hc[off];
-            for (int jc = 1; jc < NC; ++jc) v = v * u + hc[jc * kHornerK + off];
-#pragma unroll
-            for (int g = 0; g < NG; ++g) {
-              acc[(2 * g) * tcap + x] += (double)(v * rec.h[(2 * g) * NT + i]);
-              acc[(2 * g + 1) * tcap + x] += (double)(v * rec.h[(2 * g + 1) * NT + i]);
-            }
-          }
-        }
-      } else
-      for (int it = 0; it * Q * nwave < NT; ++it) {
-        const int i = q * (NT / Q) + wave + nwave * it;  // point slot
-        if (i >= cnt) continue;
-        const int lb = rec.lb[i];
-        if (lb == kSpreadNone || kk >= wd) continue;
-        int loc = lb + kk;
-        if (loc < 0) loc += n;
-        else if (loc >= n) loc -= n;
-        if (loc >= T) continue;
+      for (int i = 0; i < cnt; ++i) {
+        const int lbi = rec.lb[i];
+        if (lbi == kSpreadNone) continue;
         const Real u = rec.u[i];
-        Real v = cf[0];
+        for (int x = tid; x < T; x += NT) {
+          int off = x - lbi;  // cell offset within the point's support, mod n
+          if (off < 0) off += n;
+          else if (off >= n) off -= n;
+          if (off >= p.w) continue;
+          Real v = hc[off];
+          for (int jc = 1; jc < NC; ++jc) v = v * u + hc[jc * kHornerK + off];
 #pragma unroll
-        for (int jc = 1; jc < NC; ++jc) v = v * u + cf[jc];
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-          atomicAdd(&acc[(2 * g) * tcap + loc], (double)(v * rec.h[(2 * g) * NT + i]));
-          atomicAdd(&acc[(2 * g + 1) * tcap + loc], (double)(v * rec.h[(2 * g + 1) * NT + i]));
+          for (int c = 0; c < 2 * NG; ++c)
+            acc[c * tcap + x] += (double)(v * rec.h[c * NT + i]);
         }
       }
       __syncthreads();
     }
   }
-  __syncthreads();
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
-    T2* out = reinterpret_cast<T2*>(w.grid[gbase + g]);
+    T2* out = reinterpret_cast<T2*>(g == 0 ? out0 : out1);
     for (int x = tid; x < T; x += NT) {
       T2 v;
       v.x = (Real)acc[(2 * g) * tcap + x];
@@ -326,7 +463,6 @@ __device__ void spread_tile(int tile, int Tt, int tcap, const CallArgs& a, const
   }
   __syncthreads();
 }
-
 
 template <typename Real>
 struct PassBufs {
