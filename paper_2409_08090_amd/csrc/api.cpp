@@ -46,7 +46,9 @@ struct ChipSet {
   char* buf = nullptr;
   size_t bytes = 0;
 };
-constexpr int kChipStatus = 4;  // ints into the pinned status buffer
+// ints into the pinned status buffer: words that a call on sub-grids and one
+// of the staged path leave there
+constexpr int kChipStatus = 4, kPathStatus = 8;
 
 // (nf, eps, precision, grids + 10 * batch, fixed grid size)
 using PlanKey = std::tuple<int64_t, double, int, int, int64_t, int>;
@@ -192,7 +194,10 @@ struct mils_context {
   std::map<double, ChipSet> chips;
   ChipDone* chip_done = nullptr;
   int* chip_status = nullptr;
-  bool last_chip = false;  // the last call was one of these
+  // where the last call left its status: DevStats on the device, kChipStatus
+  // (status and ill-posed count), or kPathStatus (status and whether there are
+  // ill-posed outputs, counted in DevStats)
+  int last_words = 0;
   DevStats* last_stats = nullptr;
   int64_t last_illposed = 0;  // ill-posed frequencies of the last call whose status was read
   // plans built since the context was created, and the host time spent on them
@@ -764,7 +769,8 @@ int run_single(mils_context* ctx, const double* t, const double* y, const double
   w.inv_phihat = pe->inv_phihat;
   w.inv_phihat2 = pe->inv_phihat2;
 
-  const CallArgs a = single_args(t, y, dy, h, nd, p, plan, power, sums);
+  CallArgs a = single_args(t, y, dy, h, nd, p, plan, power, sums);
+  a.host_words = ctx->chip_status + (kPathStatus - kChipStatus);
   const int kind = ctx->prof ? -1 : chip_single_kind(ctx, plan, a);
   const ChipSet* cs = kind >= 0 ? get_chip(ctx, p->eps, !cap) : nullptr;
   if (cs) {
@@ -772,12 +778,12 @@ int run_single(mils_context* ctx, const double* t, const double* y, const double
     he = launch_chip_single(a, cp, (int)chip_residues(p->nf, cp.nfmax), w.stats, ctx->chip_done,
                             ctx->chip_status, 1, 0, stream);
     if (he != hipSuccess) return hip_fail(ctx, he, "kernel launch");
-    ctx->last_chip = true;
+    ctx->last_words = kChipStatus;
     ctx->last_stream = stream;
     ctx->have_pending = true;
     return sync ? mils_context_status(ctx) : MILS_OK;
   }
-  ctx->last_chip = false;
+  ctx->last_words = kPathStatus;
   StageHook hook{prof_hook, ctx};
   AuxStream aux{ctx->aux, ctx->ev_fork, ctx->ev_join, ctx->ev_mid};
   if (!ctx->prof && ctx->aux && ctx->sg.enabled && graphs_enabled()) {
@@ -1103,7 +1109,8 @@ static int mils_periodogram_noalloc_impl(mils_context* ctx, const double* t, con
   if (he != hipSuccess) return hip_fail(ctx, he, "hipSetDevice");
   char* base = static_cast<char*>(noalloc_scratch(ctx->device, &he));
   if (!base) return hip_fail(ctx, he, "scratch address");
-  const CallArgs a = single_args(t, y, dy, nullptr, nd, p, plan, power, nullptr);
+  CallArgs a = single_args(t, y, dy, nullptr, nd, p, plan, power, nullptr);
+  a.host_words = ctx->chip_status + (kPathStatus - kChipStatus);
   const int kind = chip_single_kind(ctx, plan, a);
   if (kind >= 0) {
     // a short series on sub-grids in LDS, as in mils_periodogram: its tables
@@ -1125,7 +1132,7 @@ static int mils_periodogram_noalloc_impl(mils_context* ctx, const double* t, con
     he = launch_chip_single(a, cp, (int)chip_residues(p->nf, cp.nfmax), st, ctx->chip_done,
                             ctx->chip_status, 1, 0, stream);
     if (he != hipSuccess) return hip_fail(ctx, he, "kernel launch");
-    ctx->last_chip = true;
+    ctx->last_words = kChipStatus;
     ctx->last_stream = stream;
     ctx->have_pending = true;
     return mils_context_status(ctx);
@@ -1186,7 +1193,7 @@ static int mils_periodogram_noalloc_impl(mils_context* ctx, const double* t, con
   he = launch_path(a, plan, w, stream, nullptr, ctx->aux ? &aux : nullptr);
   if (he != hipSuccess) return hip_fail(ctx, he, "kernel launch");
   ctx->last_stats = w.stats;
-  ctx->last_chip = false;
+  ctx->last_words = 0;
   ctx->last_stream = stream;
   ctx->have_pending = true;
   return mils_context_status(ctx);
@@ -1243,7 +1250,7 @@ static int run_direct(mils_context* ctx, const double* t, const double* y, const
   he = launch_direct(a, w, nslice, reinterpret_cast<double*>(ctx->ws + base), stream);
   if (he != hipSuccess) return hip_fail(ctx, he, "kernel launch");
   ctx->last_stats = w.stats;
-  ctx->last_chip = false;
+  ctx->last_words = 0;
   ctx->last_stream = stream;
   ctx->have_pending = true;
   return mils_context_status(ctx);
@@ -2148,14 +2155,23 @@ int mils_context_status(mils_context* ctx) {
   if (!ctx->have_pending) return MILS_OK;
   static_assert(offsetof(DevStats, nill) == offsetof(DevStats, status) + sizeof(int),
                 "status and count are read together");
+  // the kernels leave the words in pinned memory; only a call with ill-posed
+  // outputs (and the direct sums) copies its count back
+  auto copy = [&]() {
+    return hipMemcpyAsync(ctx->host_status, &ctx->last_stats->status, 2 * sizeof(int),
+                          hipMemcpyDeviceToHost, ctx->last_stream);
+  };
+  const volatile int* word = ctx->host_status + ctx->last_words;
   hipError_t he = hipSuccess;
-  if (!ctx->last_chip)
-    he = hipMemcpyAsync(ctx->host_status, &ctx->last_stats->status, 2 * sizeof(int),
-                        hipMemcpyDeviceToHost, ctx->last_stream);
+  if (ctx->last_words == 0) he = copy();
   if (he == hipSuccess) he = hipStreamSynchronize(ctx->last_stream);
+  if (he == hipSuccess && ctx->last_words == kPathStatus && word[0] == 0 && word[1] != 0) {
+    he = copy();
+    if (he == hipSuccess) he = hipStreamSynchronize(ctx->last_stream);
+    word = ctx->host_status;
+  }
   if (he != hipSuccess) return hip_fail(ctx, he, "status readback");
   ctx->have_pending = false;
-  const volatile int* word = ctx->host_status + (ctx->last_chip ? kChipStatus : 0);
   int st = word[0];
   ctx->last_illposed = st == 0 ? word[1] : 0;
   if (st == -1) return fail(ctx, MILS_ERR_INVALID_ARG, "non-finite input or dy <= 0");

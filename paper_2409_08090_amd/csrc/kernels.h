@@ -65,10 +65,22 @@ struct SeriesGroup {
 hipError_t launch_series_group(const CallArgs& a, const Plan& p, const Work& w,
                                const SeriesGroup& sg, hipStream_t s);
 
+// prologue.hip: the block partials of the statistics; then the statistics, the
+// bins and the histogram of points that need the sort; then the row flags of
+// ngeo geometries (0: none) and, with scatter, those points in bin order.
+void enqueue_pro_stats(const CallArgs& a, const Plan& p, const Work& w, hipStream_t s);
+void enqueue_bins(const CallArgs& a, const Plan& p, const Work& w, hipStream_t s);
+void enqueue_rows(const CallArgs& a, const Plan& p, const Work& w, int ngeo, bool scatter,
+                  hipStream_t s);
+
 // Spread of geometry geo (1: f, 2: 2f) into grids gbase .. gbase + ng - 1 of w
-// (spread.hip), over the active rows listed in w.
+// (spread.hip), over the tiles of rows whose flag is set.
 void enqueue_spread(const CallArgs& a, const Plan& p, const Work& w, int geo, int ng, int gbase,
                     hipStream_t s);
+// In one launch: lowrows rows of direct sums near f = 0 (0: none), geometry f
+// into grids 0 and 1, and geometry 2f into grid 2.
+void enqueue_spread_pg(const CallArgs& a, const Plan& p, const Work& w, int lowrows, bool f,
+                       bool f2, hipStream_t s);
 
 // Statistics of the call into w.stats.
 void enqueue_stats(const CallArgs& a, const Work& w, hipStream_t s);

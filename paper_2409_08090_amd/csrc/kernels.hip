@@ -2,9 +2,8 @@
 //
 // Path of one periodogram (nifty-ls paper, Sec. 1):
 //   k_stats      weights, weighted mean / variance, time range, input checks
-//   k_bins_*     point binning by fine-grid cell (sorted fast path, or a
-//                counting sort)
-//   k_spread     exponential-of-semicircle spreading onto the upsampled grid
+//   prologue.hip the same together with the point binning by fine-grid cell
+//   spread.hip   exponential-of-semicircle spreading onto the upsampled grid
 //                (geometry f: data and weight strengths; geometry 2f: weights)
 //   k_fft_pass   one pass of the multi-pass Stockham FFT through HBM
 //   k_fft_last   last FFT pass fused with deconvolution (the diagonal
@@ -143,157 +142,11 @@ __global__ __launch_bounds__(kThreads) void k_stats_final(CallArgs a, Work w, in
     st->nill = 0;
     st->nlow = 0;
     st->k_lo = 0;
-  }
-}
-
-// ============================================================================
-// Binning.  bin_start[b] = index of the first point (in the order the spread
-// reads them) whose cell lies in bin b or later; bin_start[nbins] = nd.
-// ============================================================================
-// Sorted fast path: when the bins of consecutive points are non-decreasing,
-// bin_start[b] is the first point whose bin is >= b.  The bins up to the
-// first point's all start at point 0 and those after the last point's at nd:
-// the whole grid writes them (they can be most of the grid: the frequency
-// step makes the grid's period several times the time span).  Every other
-// point j starts the bins (bin(j-1), bin(j)], so it computes its own and its
-// predecessor's bin and writes those entries: each bin is written by exactly
-// one point, and a run longer than 8 bins (a gap in the data) by the whole
-// wave.  A descent sets need_sort instead, and the counting sort below
-// rebuilds everything.
-__global__ __launch_bounds__(kThreads) void k_bins_sorted(CallArgs a, Plan p, Work w) {
-  const DevStats* st = w.stats;
-  if (st->status != 0) return;
-  if (a.wstats && !st->need_sort) return;  // the weights-only call's bins hold
-  const int nd = (int)a.nd;
-  const int nb = (int)p.nbins;
-  const int64_t gtid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  // The histogram of the counting sort is cleared by every block, before any
-  // early exit: need_sort may be raised by another block of this launch.
-  for (int64_t i = gtid; i <= nb; i += stride) w.bin_count[i] = 0;
-  if (st->need_sort) return;
-  const double tau = st->tau;
-  const int b_first = point_bin(a.t[0], tau, a.df, p);
-  const int b_last = point_bin(a.t[nd - 1], tau, a.df, p);
-  for (int64_t b = gtid; b <= nb; b += stride) {
-    if (b <= b_first) w.bin_start[b] = 0;
-    else if (b > b_last) w.bin_start[b] = nd;
-  }
-  const int lane = threadIdx.x & 63;
-  // wave-uniform loop over points 1 .. nd-1: every lane takes part in the
-  // ballot and the shuffles
-  for (int64_t j0 = 1 + (int64_t)blockIdx.x * kThreads + (threadIdx.x - lane); j0 < nd;
-       j0 += stride) {
-    const int64_t j = j0 + lane;
-    int lo = 0, hi = -1;  // the bins [lo, hi] that start at point j
-    if (j < nd) {
-      const int bp = point_bin(a.t[j - 1], tau, a.df, p);
-      const int bc = point_bin(a.t[j], tau, a.df, p);
-      if (bc < bp) atomicOr(&w.stats->need_sort, 1);
-      else {
-        lo = bp + 1;
-        hi = bc;
-      }
+    if (a.host_words) {
+      a.host_words[0] = status;
+      a.host_words[1] = 0;
     }
-    const bool run = hi - lo >= 8;
-    if (!run)
-      for (int b = lo; b <= hi; ++b) w.bin_start[b] = (int)j;
-    unsigned long long runs = __ballot(run);
-    while (runs) {
-      const int src = __ffsll(runs) - 1;
-      runs &= runs - 1;
-      const int l = __shfl(lo, src, 64), h = __shfl(hi, src, 64);
-      const int v = (int)(j0 + src);
-      for (int b = l + lane; b <= h; b += 64) w.bin_start[b] = v;
-    }
-  }
-}
-
-__global__ __launch_bounds__(kThreads) void k_sort_hist(CallArgs a, Plan p, Work w) {
-  const DevStats* st = w.stats;
-  if (st->status != 0 || !st->need_sort) return;
-  const double tau = st->tau;
-  for (int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x; j < a.nd;
-       j += (int64_t)gridDim.x * kThreads)
-    atomicAdd(&w.bin_count[point_bin(a.t[j], tau, a.df, p)], 1);
-}
-
-// Exclusive scan of bin_count[0..nbins] into bin_start, in three launches:
-// per-chunk scans, a one-block scan of the chunk totals, then the offsets.
-__global__ __launch_bounds__(kThreads) void k_scan1(Plan p, Work w) {
-  const DevStats* st = w.stats;
-  if (st->status != 0 || !st->need_sort) return;
-  __shared__ int s[kThreads];
-  const int64_t base = (int64_t)blockIdx.x * kScanChunk;
-  const int64_t cnt = p.nbins + 1;
-  int v[8];
-  int sum = 0;
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    int64_t i = base + threadIdx.x * 8 + q;
-    v[q] = i < cnt ? w.bin_count[i] : 0;
-    sum += v[q];
-  }
-  s[threadIdx.x] = sum;
-  __syncthreads();
-  for (int off = 1; off < kThreads; off <<= 1) {
-    int x = threadIdx.x >= off ? s[threadIdx.x - off] : 0;
-    __syncthreads();
-    s[threadIdx.x] += x;
-    __syncthreads();
-  }
-  int run = s[threadIdx.x] - sum;  // exclusive prefix of this thread
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    int64_t i = base + threadIdx.x * 8 + q;
-    if (i < cnt) w.bin_start[i] = run;
-    run += v[q];
-  }
-  if (threadIdx.x == kThreads - 1) w.scan_part[blockIdx.x] = s[kThreads - 1];
-}
-
-// Offsets of the per-chunk scans: block b adds the totals of chunks 0..b-1
-// (a few hundred values) to its chunk.
-__global__ __launch_bounds__(kThreads) void k_scan3(Plan p, Work w) {
-  const DevStats* st = w.stats;
-  if (st->status != 0 || !st->need_sort) return;
-  __shared__ int red[kThreads];
-  int part = 0;
-  for (unsigned b = threadIdx.x; b < blockIdx.x; b += kThreads) part += w.scan_part[b];
-  red[threadIdx.x] = part;
-  __syncthreads();
-  for (int sft = kThreads / 2; sft > 0; sft >>= 1) {
-    if ((int)threadIdx.x < sft) red[threadIdx.x] += red[threadIdx.x + sft];
-    __syncthreads();
-  }
-  const int add = red[0];
-  const int64_t cnt = p.nbins + 1;
-  for (int q = 0; q < 8; ++q) {
-    int64_t i = (int64_t)blockIdx.x * kScanChunk + q * kThreads + threadIdx.x;
-    if (i < cnt) {
-      int v = w.bin_start[i] + add;
-      w.bin_start[i] = v;
-      if (i < p.nbins) w.bin_cursor[i] = v;
-    }
-  }
-}
-
-__global__ __launch_bounds__(kThreads) void k_sort_scatter(CallArgs a, Plan p, Work w) {
-  const DevStats* st = w.stats;
-  if (st->status != 0 || !st->need_sort) return;
-  const double tau = st->tau;
-  for (int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x; j < a.nd;
-       j += (int64_t)gridDim.x * kThreads) {
-    double t = a.t[j];
-    int pos = atomicAdd(&w.bin_cursor[point_bin(t, tau, a.df, p)], 1);
-    if (pos < 0 || pos >= a.nd) continue;  // cannot happen with a consistent histogram
-    w.ts[pos] = t;
-    if (a.periodogram) {
-      w.ys[pos] = a.y ? a.y[j] : 0.0;
-      w.dys[pos] = a.dy ? a.dy[j] : 1.0;
-    } else {
-      w.hs[pos] = a.h[j];
-    }
+    if (status == 0 && a.periodogram) low_band(*st, a.f0, a.df, a.nf, st->k_lo, st->nlow);
   }
 }
 
@@ -362,78 +215,6 @@ __global__ __launch_bounds__(kThreads) void k_det_gather(CallArgs a, Plan p, Wor
 }
 
 // ============================================================================
-// Spreading.  A tile is T consecutive cells of one row of the [nrows][S1]
-// view of the grid; its workgroup gathers every point whose kernel support
-// (w cells around u) meets the tile, accumulates the kernel-weighted
-// strengths in LDS and writes the tile once: no global atomics, no halo
-// exchange, and the result does not depend on how tiles are scheduled.
-// Rows that no kernel support reaches are not written (nor visited); their
-// flag tells the first FFT pass to treat them as zero.
-// ============================================================================
-// Row classification for the spread: the flag of every row of a geometry
-// (1 if a kernel support reaches it) and the list of active rows in order.
-// The compaction is one workgroup of kRowThreads threads; thread i takes the
-// rows [i*rpt, (i+1)*rpt) (rpt = ceil(nrows / kRowThreads)), so their order
-// survives one scan of the per-thread counts.
-constexpr int kRowThreads = 1024;
-static_assert(kRowsMax <= kRowThreads * 32, "row flags of a thread fit one word");
-// Row classes, in two launches for geometries geo0 .. geo0 + gridDim.y - 1
-// (0: f, 1: 2f).  k_row_flags: one thread per row of the [nrows][S1] view
-// sets its flag (whether any kernel support of the geometry reaches it);
-// k_row_compact: one workgroup per geometry lists the active rows in order
-// and stores their count in nact[geometry].
-__global__ __launch_bounds__(256) void k_row_flags(Plan p, Work w, int nd, int geo0) {
-  const DevStats* st = w.stats;
-  if (st->status != 0) return;
-  const int geo = geo0 + (int)blockIdx.y;
-  const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (r >= p.nrows) return;
-  const int h = (int)ceil(p.hw) + 1;
-  const bool active = geo == 0 ? row_active<1>(r, h, p, w.bin_start, nd)
-                               : row_active<2>(r, h, p, w.bin_start, nd);
-  (geo == 0 ? w.rowflag_f : w.rowflag_2f)[r] = (unsigned char)active;
-}
-
-__global__ __launch_bounds__(kRowThreads) void k_row_compact(Plan p, Work w, int geo0) {
-  __shared__ int scan[kRowThreads];
-  const DevStats* st = w.stats;
-  if (st->status != 0) return;
-  const int geo = geo0 + (int)blockIdx.x;
-  const unsigned char* rowflag = geo == 0 ? w.rowflag_f : w.rowflag_2f;
-  int* act_rows = geo == 0 ? w.act_rows_f : w.act_rows_2f;
-  const int tid = threadIdx.x;
-  const int nrows = (int)p.nrows;
-  const int rpt = (nrows + kRowThreads - 1) / kRowThreads;
-  const int r0 = tid * rpt;
-  unsigned flags = 0;  // bit i: row r0 + i is active (rpt <= 32)
-  int cnt = 0;
-  for (int i = 0; i < rpt && r0 + i < nrows; ++i) {
-    const int active = rowflag[r0 + i] != 0;
-    flags |= (unsigned)active << i;
-    cnt += active;
-  }
-  scan[tid] = cnt;
-  __syncthreads();
-  for (int off = 1; off < kRowThreads; off <<= 1) {
-    const int x = tid >= off ? scan[tid - off] : 0;
-    __syncthreads();
-    scan[tid] += x;
-    __syncthreads();
-  }
-  int pos = scan[tid] - cnt;
-  for (int i = 0; i < rpt && r0 + i < nrows; ++i)
-    if ((flags >> i) & 1u) act_rows[pos++] = r0 + i;
-  if (tid == kRowThreads - 1) w.nact[geo] = scan[tid];
-}
-
-static void enqueue_row_class(const Plan& p, const Work& w, int nd, int geo0, int ngeo,
-                              hipStream_t s) {
-  const unsigned nb = (unsigned)((p.nrows + 255) / 256);
-  hipLaunchKernelGGL(k_row_flags, dim3(nb, (unsigned)ngeo), dim3(256), 0, s, p, w, nd, geo0);
-  hipLaunchKernelGGL(k_row_compact, dim3((unsigned)ngeo), dim3(kRowThreads), 0, s, p, w, geo0);
-}
-
-// ============================================================================
 // FFT passes.
 // ============================================================================
 template <typename Real, int EMAX, int NT, bool TW2>
@@ -451,14 +232,14 @@ template <typename Real, int G, int EMAX, int NT, bool TW2>
 __global__ __launch_bounds__(NT) void k_fft_last(PassBufs<Real> b, FftPass ps, Plan pl,
                                                  CallArgs a, const typename cplx<Real>::T* tw,
                                                  const double* inv_phihat, const DevStats* stp,
-                                                 const double* lowfix) {
+                                                 const double* lowfix, int lowrows) {
   extern __shared__ __align__(16) unsigned char smem[];
   if (stp->status != 0) return;
   const int64_t nblk = (ps.P + ps.C - 1) / ps.C;
   const int64_t blk = xcd_remap(blockIdx.x, nblk);
   const DevStats st = *stp;
   fft_last_block<Real, G, EMAX, NT, TW2>(blk, b, ps, pl.n, pl.nf, pl.K, a, tw, inv_phihat, st,
-                                         smem, G == 3 ? lowfix : nullptr, kLowParts,
+                                         smem, G == 3 ? lowfix : nullptr, lowrows,
                                          const_cast<int*>(&stp->nill));
 }
 
@@ -669,7 +450,8 @@ __global__ __launch_bounds__(G * L1 / 16, G == 3 ? 3 : 2) void k_fft2_last(Fft2B
                                                             const typename cplx<Real>::T* tw,
                                                             const double* iphi2,
                                                             const DevStats* stp,
-                                                            const double* lowfix, void* outv) {
+                                                            const double* lowfix, int lowrows,
+                                                            void* outv) {
   using T2 = typename cplx<Real>::T;
   using Lds = typename std::conditional<HALVES, Real, T2>::type;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -743,13 +525,13 @@ __global__ __launch_bounds__(G * L1 / 16, G == 3 ? 3 : 2) void k_fft2_last(Fft2B
         const bool low = q >= 0 && q < st.nlow;
         if (low) {
           for (int c6 = 0; c6 < 6; ++c6) s6[c6] = lowfix[6 * q + c6];
-          for (int pp = 1; pp < kLowParts; ++pp)
+          for (int pp = 1; pp < lowrows; ++pp)
             for (int c6 = 0; c6 < 6; ++c6) s6[c6] += lowfix[pp * 6 * kLowMax + 6 * q + c6];
         }
         double p = ls_power(s6[0], s6[1], s6[2], s6[3], s6[4], s6[5], st, a.norm, a.fit_mean,
                             low ? 0.0 : a.dmin);
         if (kout == a.kzero) p = 0.0;
-        else if (p != p) atomicAdd(nill, 1);
+        else if (p != p) count_nan(a, nill, 1);
         pw[m1] = p;
       }
       if (r + 1 < NR) __syncthreads();
@@ -780,7 +562,8 @@ __global__ __launch_bounds__(L1 / 16, sizeof(Real) == 8 ? 1 : 2) void k_fft2_las
                                                              const typename cplx<Real>::T* tw,
                                                              const double* iphi2,
                                                              const DevStats* stp,
-                                                             const double* lowfix, double* pwout) {
+                                                             const double* lowfix, int lowrows,
+                                                             double* pwout) {
   using T2 = typename cplx<Real>::T;
   using Lds = typename std::conditional<HALVES, Real, T2>::type;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -823,7 +606,7 @@ __global__ __launch_bounds__(L1 / 16, sizeof(Real) == 8 ? 1 : 2) void k_fft2_las
     const bool low = q >= 0 && q < st.nlow;
     if (low) {
       for (int c6 = 0; c6 < 6; ++c6) s6[c6] = lowfix[6 * q + c6];
-      for (int pp = 1; pp < kLowParts; ++pp)
+      for (int pp = 1; pp < lowrows; ++pp)
         for (int c6 = 0; c6 < 6; ++c6) s6[c6] += lowfix[pp * 6 * kLowMax + 6 * q + c6];
     }
     double p = ls_power(s6[0], s6[1], s6[2], s6[3], s6[4], s6[5], st, a.norm, a.fit_mean,
@@ -832,7 +615,7 @@ __global__ __launch_bounds__(L1 / 16, sizeof(Real) == 8 ? 1 : 2) void k_fft2_las
     else if (p != p) ++nan_count;
     pw[m1] = p;
   }
-  if (nan_count) atomicAdd(const_cast<int*>(&stp->nill), nan_count);
+  if (nan_count) count_nan(a, const_cast<int*>(&stp->nill), nan_count);
 }
 
 // Results of the last pass, [L0][L1] by (m0, m1), into frequency order:
@@ -921,19 +704,6 @@ void enqueue_stats(const CallArgs& a, const Work& w, hipStream_t s) {
   hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(kThreads), 0, s, a, w, kStatsBlocks);
 }
 
-// Binning: the sorted fast path, then the counting sort, whose kernels exit
-// at once unless the fast path found a descent.
-static void enqueue_bins(const CallArgs& a, const Plan& p, const Work& w, hipStream_t s) {
-  const int64_t nbt = (a.nd > p.nbins + 1 ? a.nd : p.nbins + 1);
-  hipLaunchKernelGGL(k_bins_sorted, dim3(grid_for(nbt, 1 << 20)), dim3(kThreads), 0, s, a, p, w);
-  const unsigned sort_blocks = grid_for(a.nd > p.nbins ? a.nd : p.nbins, 512);
-  hipLaunchKernelGGL(k_sort_hist, dim3(sort_blocks), dim3(kThreads), 0, s, a, p, w);
-  const int64_t nchunks = (p.nbins + 1 + kScanChunk - 1) / kScanChunk;
-  hipLaunchKernelGGL(k_scan1, dim3((unsigned)nchunks), dim3(kThreads), 0, s, p, w);
-  hipLaunchKernelGGL(k_scan3, dim3((unsigned)nchunks), dim3(kThreads), 0, s, p, w);
-  hipLaunchKernelGGL(k_sort_scatter, dim3(sort_blocks), dim3(kThreads), 0, s, a, p, w);
-}
-
 // Reproducible binning (see k_det_keys).
 static void enqueue_det_bins(const CallArgs& a, const Plan& p, const Work& w, hipStream_t s) {
   const int64_t nk = det_keys(a.nd);
@@ -946,7 +716,7 @@ static void enqueue_det_bins(const CallArgs& a, const Plan& p, const Work& w, hi
   hipLaunchKernelGGL(k_det_gather, dim3(grid_for(nbt, 1 << 16)), dim3(kThreads), 0, s, a, p, w);
 }
 
-// Direct sums near f = 0 into w.lowfix.
+// Direct sums near f = 0 into kLowParts rows of w.lowfix.
 static void enqueue_lowfreq(const CallArgs& a, const Work& w, hipStream_t s) {
   const unsigned lb = grid_for(a.nd, kLowBlocks);
   hipLaunchKernelGGL(k_lowfreq, dim3(lb), dim3(kThreads), 0, s, a, w);
@@ -981,7 +751,7 @@ static void enqueue_pass(const FftPass& ps, const PassBufs<Real>& b, int ng, con
 // series sharing its weights), or the complex sums (G = 1).
 template <typename Real>
 static void enqueue_last(const CallArgs& a, const Plan& p, const PassBufs<Real>& b, int G,
-                         const Work& w, hipStream_t s) {
+                         const Work& w, int lowrows, hipStream_t s) {
   using T2 = typename cplx<Real>::T;
   constexpr bool f64 = sizeof(Real) == 8;
   constexpr int ELAST = f64 ? kElast64 : kElast32;
@@ -1017,18 +787,18 @@ static void enqueue_last(const CallArgs& a, const Plan& p, const PassBufs<Real>&
                        : k_fft_last<Real, 1, EBIG, kThreadsBig, true>;
     big_lds(reinterpret_cast<const void*>(kern), lds);
     hipLaunchKernelGGL(kern, grid, dim3(kThreadsBig), lds, s, b, ps, p, a, tw, ip, w.stats,
-                       w.lowfix);
+                       w.lowfix, lowrows);
   } else if (G == 3) {
     hipLaunchKernelGGL((k_fft_last<Real, 3, ELAST, NTL, false>), grid, dim3(NTL), lds, s, b, ps,
-                       p, a, tw, ip, w.stats, w.lowfix);
+                       p, a, tw, ip, w.stats, w.lowfix, lowrows);
   } else if (ps.C * ps.L <= ELAST / 3) {
     // one grid of a plan made for three (the weight-only sums): the
     // third-size instance holds a third of the registers
     hipLaunchKernelGGL((k_fft_last<Real, 1, ELAST / 3, NTL, false>), grid, dim3(NTL), lds, s, b,
-                       ps, p, a, tw, ip, w.stats, w.lowfix);
+                       ps, p, a, tw, ip, w.stats, w.lowfix, lowrows);
   } else {
     hipLaunchKernelGGL((k_fft_last<Real, 1, ELAST, NTL, false>), grid, dim3(NTL), lds, s, b, ps,
-                       p, a, tw, ip, w.stats, w.lowfix);
+                       p, a, tw, ip, w.stats, w.lowfix, lowrows);
   }
 }
 
@@ -1092,7 +862,7 @@ static void enqueue_fft2_first(const Plan& p, const Fft2Bufs<Real>& b, int ng, c
 
 template <typename Real, int L1, int G>
 static void enqueue_fft2_last_l(const CallArgs& a, const Plan& p, const Fft2Bufs<Real>& b,
-                                const Work& w, hipStream_t st) {
+                                const Work& w, int lowrows, hipStream_t st) {
   using T2 = typename cplx<Real>::T;
   constexpr bool H = sizeof(Real) == 8;
   const int L0 = p.pass[0].L;
@@ -1107,12 +877,13 @@ static void enqueue_fft2_last_l(const CallArgs& a, const Plan& p, const Fft2Bufs
     const size_t lds3 = f2_last_seq_lds<Real>(L1, H);                                          \
     big_lds(reinterpret_cast<const void*>(kern), lds3);                                        \
     hipLaunchKernelGGL(kern, dim3((unsigned)L0), dim3(L1 / 16), lds3, st, b, ps, p, a, tw,      \
-                       w.inv_phihat2, w.stats, lowfix, reinterpret_cast<double*>(w.f2out));    \
+                       w.inv_phihat2, w.stats, lowfix, lowrows,                                \
+                       reinterpret_cast<double*>(w.f2out));                                    \
   } else {                                                                                     \
     auto kern = k_fft2_last<Real, L1, G, CC, H>;                                               \
     big_lds(reinterpret_cast<const void*>(kern), lds);                                         \
     hipLaunchKernelGGL(kern, dim3((unsigned)L0), dim3(G * L1 / 16), lds, st, b, ps, p, a, tw,   \
-                       w.inv_phihat2, w.stats, lowfix, w.f2out);                               \
+                       w.inv_phihat2, w.stats, lowfix, lowrows, w.f2out);                      \
   }
   if (C == 8) MILS_F2_LAST(8)
   else if (C == 4) MILS_F2_LAST(4)
@@ -1137,125 +908,121 @@ static void enqueue_fft2_out(const CallArgs& a, const Plan& p, int G, const Work
 
 template <typename Real>
 static void enqueue_fft2_last(const CallArgs& a, const Plan& p, const Fft2Bufs<Real>& b, int G,
-                              const Work& w, hipStream_t st) {
+                              const Work& w, int lowrows, hipStream_t st) {
   const int L1 = p.pass[1].L;
   if (G == 3) {
-    if (L1 == 2048) enqueue_fft2_last_l<Real, 2048, 3>(a, p, b, w, st);
-    else enqueue_fft2_last_l<Real, 4096, 3>(a, p, b, w, st);
+    if (L1 == 2048) enqueue_fft2_last_l<Real, 2048, 3>(a, p, b, w, lowrows, st);
+    else enqueue_fft2_last_l<Real, 4096, 3>(a, p, b, w, lowrows, st);
   } else {
-    if (L1 == 2048) enqueue_fft2_last_l<Real, 2048, 1>(a, p, b, w, st);
-    else if (L1 == 4096) enqueue_fft2_last_l<Real, 4096, 1>(a, p, b, w, st);
-    else enqueue_fft2_last_l<Real, 8192, 1>(a, p, b, w, st);
+    if (L1 == 2048) enqueue_fft2_last_l<Real, 2048, 1>(a, p, b, w, lowrows, st);
+    else if (L1 == 4096) enqueue_fft2_last_l<Real, 4096, 1>(a, p, b, w, lowrows, st);
+    else enqueue_fft2_last_l<Real, 8192, 1>(a, p, b, w, lowrows, st);
   }
 }
 
+// One series: binning, both spreads, the FFT passes over all grids, the last
+// pass.  A periodogram of at most kLowFusedNd points sums the frequencies near
+// f = 0 in workgroups of the spread's launch, so that everything runs on one
+// stream; with more points those sums run on the auxiliary stream beside the
+// FFT passes (they then cost more than a launch).  With a stage hook the parts
+// of the fused launches run apart, so that each stage is timed.
 template <typename Real>
 static hipError_t launch_path_t(const CallArgs& a, const Plan& p, const Work& w, hipStream_t s,
                                 const StageHook* hook, const AuxStream* aux) {
   using T2 = typename cplx<Real>::T;
-  const int G = a.periodogram ? 3 : 1;
-  // The periodogram forks after binning: the 2f geometry (row flags, spread,
-  // first FFT pass of its grid) and the direct sums near f = 0 run on the
-  // auxiliary stream, beside the f geometry, and join before the second pass.
-  const bool fork = a.periodogram && aux != nullptr;
-  hipStream_t s2 = fork ? aux->s : s;
+  const bool pg = a.periodogram != 0;
+  const int G = pg ? 3 : 1;
   auto mark = [&](int stage, int begin, hipStream_t st) {
     if (hook) hook->fn(hook->ud, stage, begin, st);
   };
   mark(kStageStats, 1, s);
-  enqueue_stats(a, w, s);
+  if (a.deterministic) enqueue_stats(a, w, s);
+  else enqueue_pro_stats(a, p, w, s);
   mark(kStageStats, 0, s);
   mark(kStageBin, 1, s);
   if (a.deterministic) enqueue_det_bins(a, p, w, s);
   else enqueue_bins(a, p, w, s);
+  if (!p.fft2) enqueue_rows(a, p, w, pg ? 2 : 1, !a.deterministic, s);
   mark(kStageBin, 0, s);
-  const int nd = (int)a.nd;
-  // two-pass plans classify the rows of both geometries before the fork:
-  // beside the other branch's persistent spread, a one-workgroup launch
-  // waits long for a free CU
-  const bool rows_first = p.fft2 && a.periodogram;
-  if (rows_first) {
+  if (p.fft2) {
     mark(kStageRows, 1, s);
-    enqueue_row_class(p, w, nd, 0, 2, s);
+    enqueue_rows(a, p, w, pg ? 2 : 1, !a.deterministic, s);
     mark(kStageRows, 0, s);
   }
-  if (fork) {
-    hipError_t e = hipEventRecord(aux->fork, s);
-    if (e == hipSuccess) e = hipStreamWaitEvent(s2, aux->fork, 0);
-    if (e != hipSuccess) return e;
-  }
 
-  // The f geometry (row classes, spread and then the first FFT pass of its
-  // two grids) is the longer branch: it is launched (and captured) first.
-  mark(kStageSpreadF, 1, s);
-  if (!rows_first)
-    enqueue_row_class(p, w, nd, 0, 1, s);
-  if (a.periodogram) enqueue_spread(a, p, w, 1, 2, 0, s);
-  else enqueue_spread(a, p, w, 1, 1, 0, s);
-  mark(kStageSpreadF, 0, s);
-  if (a.periodogram && !p.fft2) {
-    mark(kStageLow, 1, s2);
-    enqueue_lowfreq(a, w, s2);
-    mark(kStageLow, 0, s2);
+  const bool low_fused = a.nd <= kLowFusedNd;
+  const bool fork = pg && !low_fused && aux != nullptr;
+  hipStream_t s2 = fork ? aux->s : s;
+  int lowrows = kLowParts;
+  if (!pg) {
+    mark(kStageSpreadF, 1, s);
+    enqueue_spread(a, p, w, 1, 1, 0, s);
+    mark(kStageSpreadF, 0, s);
+  } else {
+    if (low_fused) lowrows = low_fused_rows(a.nd);
+    if (hook || a.deterministic) {
+      mark(kStageSpreadF, 1, s);
+      if (a.deterministic) enqueue_spread(a, p, w, 1, 2, 0, s);
+      else enqueue_spread_pg(a, p, w, 0, true, false, s);
+      mark(kStageSpreadF, 0, s);
+      mark(kStageSpread2F, 1, s);
+      if (a.deterministic) enqueue_spread(a, p, w, 2, 1, 2, s);
+      else enqueue_spread_pg(a, p, w, 0, false, true, s);
+      mark(kStageSpread2F, 0, s);
+      if (low_fused) {
+        mark(kStageLow, 1, s);
+        enqueue_spread_pg(a, p, w, lowrows, false, false, s);
+        mark(kStageLow, 0, s);
+      }
+    } else {
+      enqueue_spread_pg(a, p, w, low_fused ? lowrows : 0, true, true, s);
+    }
+    if (!low_fused) {
+      if (fork) {
+        hipError_t e = hipEventRecord(aux->fork, s);
+        if (e == hipSuccess) e = hipStreamWaitEvent(s2, aux->fork, 0);
+        if (e != hipSuccess) return e;
+      }
+      mark(kStageLow, 1, s2);
+      enqueue_lowfreq(a, w, s2);
+      mark(kStageLow, 0, s2);
+    }
   }
-  if (a.periodogram) {
-    mark(kStageSpread2F, 1, s2);
-    if (!rows_first)
-      enqueue_row_class(p, w, nd, 1, 1, s2);
-    enqueue_spread(a, p, w, 2, 1, 2, s2);
-    mark(kStageSpread2F, 0, s2);
-  }
+  auto join = [&]() -> hipError_t {
+    if (!fork) return hipSuccess;
+    hipError_t e = hipEventRecord(aux->join, s2);
+    if (e == hipSuccess) e = hipStreamWaitEvent(s, aux->join, 0);
+    return e;
+  };
   if (p.fft2) {
-    // two-pass register-tile FFT: the first pass of each geometry's grids on
-    // its branch, then (joined) the last pass and the transpose
+    // two-pass register-tile FFT
     Fft2Bufs<Real> b;
     for (int g = 0; g < 3; ++g) {
       b.grid[g] = reinterpret_cast<T2*>(w.grid[g < G ? g : 0]);
       b.mid[g] = reinterpret_cast<T2*>(w.grid2[g < G ? g : 0]);
       b.rowflag[g] = g == 2 ? w.rowflag_2f : w.rowflag_f;
     }
-    if (fork) {
-      // both spreads first (the first pass fills every CU and would starve
-      // the other branch's small kernels), then the first pass of all three
-      // grids in one launch beside the direct sums near f = 0
-      hipError_t e = hipEventRecord(aux->mid, s2);
-      if (e == hipSuccess) e = hipStreamWaitEvent(s, aux->mid, 0);
-      if (e != hipSuccess) return e;
-      mark(kStagePass0, 1, s);
-      enqueue_fft2_first<Real>(p, b, 3, w, s);
-      mark(kStagePass0, 0, s);
-      mark(kStageLow, 1, s2);
-      enqueue_lowfreq(a, w, s2);
-      mark(kStageLow, 0, s2);
-      e = hipEventRecord(aux->join, s2);
-      if (e == hipSuccess) e = hipStreamWaitEvent(s, aux->join, 0);
-      if (e != hipSuccess) return e;
-    } else {
-      if (a.periodogram) {
-        mark(kStageLow, 1, s);
-        enqueue_lowfreq(a, w, s);
-        mark(kStageLow, 0, s);
-      }
-      mark(kStagePass0, 1, s);
-      enqueue_fft2_first<Real>(p, b, G, w, s);
-      mark(kStagePass0, 0, s);
-    }
+    mark(kStagePass0, 1, s);
+    enqueue_fft2_first<Real>(p, b, G, w, s);
+    mark(kStagePass0, 0, s);
+    hipError_t e = join();
+    if (e != hipSuccess) return e;
     mark(kStageLast, 1, s);
-    enqueue_fft2_last<Real>(a, p, b, G, w, s);
+    enqueue_fft2_last<Real>(a, p, b, G, w, lowrows, s);
     mark(kStageLast, 0, s);
     mark(kStageOut, 1, s);
     enqueue_fft2_out(a, p, G, w, s);
     mark(kStageOut, 0, s);
     return hipGetLastError();
   }
-  // passes 0 .. npass-2; launch over grids [g0, g0 + ng) of the current set
+  // passes 0 .. npass-2 over grids [g0, g0 + ng) of the current set
   T2* cur[3];
   T2* alt[3];
   for (int g = 0; g < 3; ++g) {
     cur[g] = reinterpret_cast<T2*>(w.grid[g]);
     alt[g] = reinterpret_cast<T2*>(w.grid2[g]);
   }
-  auto pass = [&](int ip, int g0, int ng, hipStream_t st) {
+  auto pass = [&](int ip, int g0, int ng) {
     PassBufs<Real> b;
     for (int i = 0; i < 3; ++i) {
       const int g = g0 + i < 3 ? g0 + i : 2;
@@ -1263,30 +1030,23 @@ static hipError_t launch_path_t(const CallArgs& a, const Plan& p, const Work& w,
       b.out[i] = (ip == 0) ? cur[g] : alt[g];
       b.rowflag[i] = (ip == 0) ? (g == 2 ? w.rowflag_2f : w.rowflag_f) : nullptr;
     }
-    enqueue_pass<Real>(p.pass[ip], b, ng, w, st);
+    enqueue_pass<Real>(p.pass[ip], b, ng, w, s);
   };
   if (p.npass >= 2) {
-    if (fork) {
+    // (timed as two launches, one per geometry)
+    const int first = hook && pg ? 2 : G;
+    mark(kStagePass0, 1, s);
+    pass(0, 0, first);
+    mark(kStagePass0, 0, s);
+    if (first < G) {
       mark(kStagePass0, 1, s);
-      pass(0, 0, 2, s);   // f grids
-      mark(kStagePass0, 0, s);
-      mark(kStagePass0, 1, s2);
-      pass(0, 2, 1, s2);  // 2f grid
-      mark(kStagePass0, 0, s2);
-    } else {
-      mark(kStagePass0, 1, s);
-      pass(0, 0, G, s);
+      pass(0, first, G - first);
       mark(kStagePass0, 0, s);
     }
   }
-  if (fork) {
-    hipError_t e = hipEventRecord(aux->join, s2);
-    if (e == hipSuccess) e = hipStreamWaitEvent(s, aux->join, 0);
-    if (e != hipSuccess) return e;
-  }
   for (int ip = 1; ip + 1 < p.npass; ++ip) {
     mark(kStagePass0 + ip, 1, s);
-    pass(ip, 0, G, s);
+    pass(ip, 0, G);
     mark(kStagePass0 + ip, 0, s);
     for (int g = 0; g < 3; ++g) {
       T2* tmp = cur[g];
@@ -1294,6 +1054,8 @@ static hipError_t launch_path_t(const CallArgs& a, const Plan& p, const Work& w,
       alt[g] = tmp;
     }
   }
+  hipError_t e = join();
+  if (e != hipSuccess) return e;
   {
     PassBufs<Real> b;
     for (int g = 0; g < 3; ++g) {
@@ -1302,7 +1064,7 @@ static hipError_t launch_path_t(const CallArgs& a, const Plan& p, const Work& w,
       b.rowflag[g] = nullptr;
     }
     mark(kStageLast, 1, s);
-    enqueue_last<Real>(a, p, b, G, w, s);
+    enqueue_last<Real>(a, p, b, G, w, lowrows, s);
     mark(kStageLast, 0, s);
   }
   return hipGetLastError();
@@ -1329,10 +1091,9 @@ template <typename Real>
 static hipError_t launch_weight_sums_t(const CallArgs& aw, const Plan& p, const Work& w,
                                        double* bsum_b, double* bsum_b2, hipStream_t s) {
   using T2 = typename cplx<Real>::T;
-  enqueue_stats(aw, w, s);
+  enqueue_pro_stats(aw, p, w, s);
   enqueue_bins(aw, p, w, s);
-  const int nd = (int)aw.nd;
-  enqueue_row_class(p, w, nd, 0, 2, s);
+  enqueue_rows(aw, p, w, 2, true, s);
   enqueue_spread(aw, p, w, 1, 1, 1, s);
   enqueue_spread(aw, p, w, 2, 1, 2, s);
   T2* in[2];
@@ -1347,7 +1108,7 @@ static hipError_t launch_weight_sums_t(const CallArgs& aw, const Plan& p, const 
       b.rowflag[g] = nullptr;
     }
     as.sums = i == 0 ? bsum_b : bsum_b2;
-    enqueue_last<Real>(as, p, b, 1, w, s);
+    enqueue_last<Real>(as, p, b, 1, w, kLowParts, s);
   }
   return hipGetLastError();
 }
@@ -1367,8 +1128,13 @@ static hipError_t launch_series_group_t(const CallArgs& a, const Plan& p, const 
     Work wg = w;
     wg.stats = sg.stats[g];
     wg.lowfix = sg.lowfix[g];
-    enqueue_stats(ag, wg, s);
-    if (sg.need_sort) enqueue_bins(ag, p, wg, s);
+    if (sg.need_sort) {
+      enqueue_pro_stats(ag, p, wg, s);
+      enqueue_bins(ag, p, wg, s);
+      enqueue_rows(ag, p, wg, 0, true, s);
+    } else {
+      enqueue_stats(ag, wg, s);
+    }
     enqueue_lowfreq(ag, wg, s);
     enqueue_spread(ag, p, wg, 1, 1, g, s);
     al.spow[g] = sg.power[g];
@@ -1383,7 +1149,7 @@ static hipError_t launch_series_group_t(const CallArgs& a, const Plan& p, const 
     b.out[g] = nullptr;
     b.rowflag[g] = nullptr;
   }
-  enqueue_last<Real>(al, p, b, sg.m, w, s);
+  enqueue_last<Real>(al, p, b, sg.m, w, kLowParts, s);
   return hipGetLastError();
 }
 

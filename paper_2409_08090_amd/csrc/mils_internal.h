@@ -102,6 +102,8 @@ struct CallArgs {
   double dmin;
   int periodogram;    // 1: three grids + power; 0: one grid + complex sums
   int deterministic;  // fixed summation orders (bitwise-reproducible results)
+  int* host_words;    // pinned host memory (NULL: not used): status, and whether
+                      // any output is ill-posed (its count is DevStats::nill)
   double* power;      // periodogram output
   double* sums;       // trig sums output (interleaved re/im)
   // Series sharing their weights (same t and dy): a weights-only call has
@@ -130,7 +132,7 @@ struct Work {
   double* partials;       // per-block partial reductions
   int* bin_start;         // nbins + 1
   int* bin_count;         // nbins + 1 (counting sort)
-  int* bin_cursor;        // nbins
+  int* bin_cursor;        // nbins (batch series)
   int* scan_part;         // scan block sums
   double* ts;             // sorted copies (counting sort path)
   double* ys;
@@ -138,9 +140,7 @@ struct Work {
   double* hs;
   unsigned char* rowflag_f;   // nrows
   unsigned char* rowflag_2f;  // nrows
-  int* act_rows_f;            // nrows: active rows of geometry f, in order
-  int* act_rows_2f;           // nrows: same for geometry 2f
-  int* nact;                  // 2: number of active rows (f, 2f)
+  int* done;                  // finished blocks of the histogram (k_pro_bins)
   void* grid[3];          // G grids of n complex
   void* grid2[3];         // second buffers for passes >= 2
   const void* tw;         // twiddles (plan-owned)
@@ -148,7 +148,8 @@ struct Work {
   const double* inv_phihat2; // two-pass plans: 1 / phihat in last-pass order, n entries (plan-owned)
   void* f2out;               // two-pass plans: last-pass results, n doubles (power) or double2 (sums)
   double* lowpart;        // per-block partial direct sums near f = 0
-  double* lowfix;         // direct sums A, B, B2 near f = 0: kLowParts rows of kLowMax x 6
+  double* lowfix;         // direct sums A, B, B2 near f = 0: rows of kLowMax x 6 that the
+                          // last pass adds (kLowParts, or up to kLowRows of a fused call)
   uint64_t* keys;         // det_keys(nd) sort keys of the reproducible binning
   double* rec;            // on-chip series of a batch: nd pairs (w^ y~, w^)
 };
@@ -194,6 +195,15 @@ constexpr int kLowMax = 16;
 constexpr int kLowGroup = 8;
 constexpr int kLowBlocks = 512;
 constexpr int kLowParts = 8;  // rows of lowfix (partial sums; the last pass adds them)
+// Calls of at most kLowFusedNd points form them in workgroups of the spread's
+// launch, one row per 2048 points up to kLowRows (a quarter of the frequencies
+// each: 48 registers of sums instead of 192, at twice the phase work).
+constexpr int64_t kLowFusedNd = 200000;
+constexpr int kLowRows = 32;
+inline int low_fused_rows(int64_t nd) {
+  const int64_t r = (nd + 2047) / 2048;
+  return (int)(r < kLowRows ? r : kLowRows);
+}
 
 // LDS pitch of the last FFT pass: its rows are interleaved element by element
 // with no padding.

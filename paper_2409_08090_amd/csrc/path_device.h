@@ -596,6 +596,12 @@ __device__ __forceinline__ double ls_power(double Ar, double Ai, double Br, doub
   }
 }
 
+// Counts ill-posed outputs (power NaN) and tells the host that there are some.
+__device__ __forceinline__ void count_nan(const CallArgs& a, int* nill, int n) {
+  atomicAdd(nill, n);
+  if (a.host_words) a.host_words[1] = 1;
+}
+
 // Last pass: D rows of length L per workgroup for the G grids, transformed in
 // LDS; output k of row p is the mode m = p + P k.  Deconvolution, crop to the
 // nf requested modes and (G = 3) the power are fused into the store.
@@ -733,7 +739,7 @@ __device__ void fft_last_block(int64_t blk, const PassBufs<Real>& b, const FftPa
       double pw = ls_power(s6[0], s6[1], s6[2], s6[3], s6[4], s6[5], st, a.norm, a.fit_mean,
                            low ? 0.0 : a.dmin);
       if (kout == a.kzero) pw = 0.0;
-      else if (nill && pw != pw) atomicAdd(nill, 1);
+      else if (nill && pw != pw) count_nan(a, nill, 1);
       a.power[kout] = pw;
     } else {
       const T2 A = buf[k * R + d];

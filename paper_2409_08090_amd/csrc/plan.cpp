@@ -559,7 +559,7 @@ size_t layout_work(const Plan& p, int64_t nd, int G, char* base, Work* w, bool p
   if (!per_series) x.partials = reinterpret_cast<double*>(take(sizeof(double) * 8 * kStatsBlocks));
   x.bin_start = reinterpret_cast<int*>(take(sizeof(int) * (p.nbins + 1)));
   x.bin_count = reinterpret_cast<int*>(take(sizeof(int) * (p.nbins + 1)));
-  x.bin_cursor = reinterpret_cast<int*>(take(sizeof(int) * (p.nbins + 1)));
+  if (per_series) x.bin_cursor = reinterpret_cast<int*>(take(sizeof(int) * (p.nbins + 1)));
   const int64_t nchunks = (p.nbins + 1 + 2047) / 2048;
   x.scan_part = reinterpret_cast<int*>(take(sizeof(int) * (nchunks + 1)));
   x.ts = reinterpret_cast<double*>(take(sizeof(double) * nd));
@@ -571,13 +571,12 @@ size_t layout_work(const Plan& p, int64_t nd, int G, char* base, Work* w, bool p
   }
   if (!per_series) x.lowpart = reinterpret_cast<double*>(take(sizeof(double) * 6 * kLowMax * kLowBlocks));
   if (!per_series) x.keys = reinterpret_cast<uint64_t*>(take(sizeof(uint64_t) * det_keys(nd)));
-  x.lowfix = reinterpret_cast<double*>(take(sizeof(double) * 6 * kLowMax * (per_series ? 1 : kLowParts)));
-  x.rowflag_f = reinterpret_cast<unsigned char*>(take(p.nrows));
-  x.rowflag_2f = reinterpret_cast<unsigned char*>(take(p.nrows));
+  x.lowfix = reinterpret_cast<double*>(take(sizeof(double) * 6 * kLowMax * (per_series ? 1 : kLowRows)));
+  // (whole words: the spread reads four flags at a time)
+  x.rowflag_f = reinterpret_cast<unsigned char*>(take((p.nrows + 3) & ~(int64_t)3));
+  x.rowflag_2f = reinterpret_cast<unsigned char*>(take((p.nrows + 3) & ~(int64_t)3));
   if (!per_series) {
-    x.act_rows_f = reinterpret_cast<int*>(take(sizeof(int) * p.nrows));
-    x.act_rows_2f = reinterpret_cast<int*>(take(sizeof(int) * p.nrows));
-    x.nact = reinterpret_cast<int*>(take(sizeof(int) * 2));
+    x.done = reinterpret_cast<int*>(take(sizeof(int)));
   }
   const size_t cbytes = p.prec == 1 ? 8 : 16;
   for (int g = 0; g < G; ++g) x.grid[g] = take(cbytes * p.n);

@@ -14,45 +14,118 @@
 
 namespace mils {
 
-// Spreading over the tiles of the active rows only (their list and count come
-// from k_row_compact): a fixed grid of workgroups takes tiles blk, blk + grid,
-// ...; every tile is written by exactly one workgroup, so the result does not
-// depend on scheduling.  T divides the row length S1 here.
+// Whether any kernel support reaches row r (through scalar loads).
+__device__ __forceinline__ bool row_set(const unsigned char* flags, int r) {
+  const unsigned word = ((ConstPtr<unsigned>)(const unsigned*)flags)[r >> 2];
+  return (word >> (8 * (r & 3))) & 255u;
+}
+
+// Spreading over the tiles of the rows whose flag is set: a fixed grid of
+// workgroups takes tiles b, b + nb, ...; every tile is written by exactly one
+// workgroup, so the result does not depend on scheduling.  T divides the row
+// length S1 here.
+template <typename Real, int GEO, int NG, int SETS>
+__device__ __forceinline__ void spread_tiles(int b, int nb, int T, int tcap, const CallArgs& a,
+                                             const Plan& p, const Work& w, const DevStats& st,
+                                             void* out0, void* out1, double* acc) {
+  const unsigned char* flags = GEO == 1 ? w.rowflag_f : w.rowflag_2f;
+  const int tpr = (int)p.S1 / T;
+  const int ntile = (int)p.nrows * tpr;
+  for (int t = b; t < ntile; t += nb)
+    if (row_set(flags, t / tpr))
+      spread_tile<Real, GEO, NG, kThreads, SETS>(t, T, tcap, a, p, w, st, out0, out1, acc);
+}
+
 template <typename Real, int GEO, int NG, int SETS>
 __global__ __launch_bounds__(kThreads) void k_spread_rows(CallArgs a, Plan p, Work w, void* out0,
-                                                          void* out1, const int* act_rows,
-                                                          int slot) {
+                                                          void* out1) {
   __shared__ double acc[NG * 2 * kTileMax];
   const DevStats st = load_stats(w.stats);
   if (st.status != 0) return;
-  const int tpr = (int)(p.S1 / p.T);
-  const int ntile = *(ConstPtr<int>)(w.nact + slot) * tpr;
-  for (int t = blockIdx.x; t < ntile; t += gridDim.x) {
-    const int q = t / tpr;
-    const int tile = ((ConstPtr<int>)act_rows)[q] * tpr + (t - q * tpr);
-    spread_tile<Real, GEO, NG, kThreads, SETS>(tile, p.T, kTileMax, a, p, w, st, out0, out1,
-                                               acc);
+  spread_tiles<Real, GEO, NG, SETS>(blockIdx.x, gridDim.x, p.T, kTileMax, a, p, w, st, out0, out1,
+                                    acc);
+}
+
+// Direct sums A, B, B2 at four of the frequencies near f = 0 (group g: k_lo +
+// 4 g ..) over slice r of nr of the points, into row r of lowfix.  Fixed order:
+// the 24 sums are shared out over the lanes of each wave by exchanging halves,
+// then added over the waves.
+__device__ __forceinline__ void low_slice(const CallArgs& a, const DevStats& st, int g, int r,
+                                          int nr, double* lowfix, double* red) {
+  constexpr int NV = 24;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int ng = st.nlow - 4 * g < 4 ? st.nlow - 4 * g : 4;
+  if (ng <= 0) return;
+  double v[NV];
+  low_accumulate<4>(a, st, st.k_lo + 4 * g, ng, (int64_t)r * kThreads + tid,
+                    (int64_t)nr * kThreads, v);
+  int base = 0;
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    const int off = 32 >> s, half = NV >> (s + 1);
+    const bool up = lane & off;
+    if (up) base += half;
+#pragma unroll
+    for (int i = 0; i < half; ++i) {
+      const double keep = up ? v[i + half] : v[i];
+      const double give = up ? v[i] : v[i + half];
+      v[i] = keep + __shfl_xor(give, off, 64);
+    }
   }
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1) v[i] += __shfl_xor(v[i], off, 64);
+  if ((lane & 7) == 0)
+#pragma unroll
+    for (int i = 0; i < 3; ++i) red[(tid >> 6) * NV + base + i] = v[i];
+  __syncthreads();
+  if (tid < NV) {
+    double sum = 0.0;
+    for (int i = 0; i < kThreads / 64; ++i) sum += red[i * NV + tid];
+    lowfix[r * 6 * kLowMax + NV * g + tid] = sum;
+  }
+}
+
+// A periodogram's spreads and direct sums in one launch: the first 4 lowrows
+// workgroups take the direct sums (they run longest), the next nf the tiles of
+// geometry f, the others those of geometry 2f, whose one grid lets a tile be
+// twice as long (T2).
+template <typename Real, int SETS>
+__global__ __launch_bounds__(kThreads) void k_spread_pg(CallArgs a, Plan p, Work w, int lowrows,
+                                                        int nf, int T2) {
+  __shared__ double acc[4 * kTileMax];
+  const DevStats st = load_stats(w.stats);
+  if (st.status != 0) return;
+  int b = (int)blockIdx.x;
+  if (b < 4 * lowrows) {
+    low_slice(a, st, b & 3, b >> 2, lowrows, w.lowfix, acc);
+    return;
+  }
+  b -= 4 * lowrows;
+  if (b < nf)
+    spread_tiles<Real, 1, 2, SETS>(b, nf, p.T, kTileMax, a, p, w, st, w.grid[0], w.grid[1], acc);
+  else
+    spread_tiles<Real, 2, 1, SETS>(b - nf, (int)gridDim.x - 4 * lowrows - nf, T2, 2 * kTileMax, a,
+                                   p, w, st, w.grid[2], w.grid[2], acc);
 }
 
 // The same with fixed summation orders.
 template <typename Real, int GEO, int NG>
 __global__ __launch_bounds__(kThreads) void k_spread_det(CallArgs a, Plan p, Work w, void* out0,
-                                                         void* out1, const int* act_rows,
-                                                         int slot) {
+                                                         void* out1) {
   __shared__ double acc[NG * 2 * kTileMax];
   __shared__ int rb[8], re[8], sv[1];
   __shared__ SpreadRecords<Real, NG, kThreads> rec;
   const DevStats st = *w.stats;
   if (st.status != 0) return;
+  const unsigned char* flags = GEO == 1 ? w.rowflag_f : w.rowflag_2f;
   const int tpr = (int)(p.S1 / p.T);
-  const int ntile = w.nact[slot] * tpr;
-  for (int t = blockIdx.x; t < ntile; t += gridDim.x) {
-    const int q = t / tpr;
-    const int tile = act_rows[q] * tpr + (t - q * tpr);
-    spread_tile_det<Real, GEO, NG, kThreads>(tile, p.T, kTileMax, a, p, w, st, out0, out1, acc,
-                                             rb, re, sv, rec);
-  }
+  const int ntile = (int)p.nrows * tpr;
+  for (int t = blockIdx.x; t < ntile; t += gridDim.x)
+    if (row_set(flags, t / tpr))
+      spread_tile_det<Real, GEO, NG, kThreads>(t, p.T, kTileMax, a, p, w, st, out0, out1, acc, rb,
+                                               re, sv, rec);
 }
 
 namespace {
@@ -63,16 +136,33 @@ void enqueue(const CallArgs& a, const Plan& p, const Work& w, int gbase, hipStre
   const dim3 grid((unsigned)(ntiles < kSpreadGrid ? ntiles : kSpreadGrid));
   void* out0 = w.grid[gbase];
   void* out1 = w.grid[gbase + NG - 1];
-  const int* rows = GEO == 1 ? w.act_rows_f : w.act_rows_2f;
   if (a.deterministic)
     hipLaunchKernelGGL((k_spread_det<Real, GEO, NG>), grid, dim3(kThreads), 0, s, a, p, w, out0,
-                       out1, rows, GEO - 1);
+                       out1);
   else if (p.w <= 16)
     hipLaunchKernelGGL((k_spread_rows<Real, GEO, NG, 1>), grid, dim3(kThreads), 0, s, a, p, w,
-                       out0, out1, rows, GEO - 1);
+                       out0, out1);
   else
     hipLaunchKernelGGL((k_spread_rows<Real, GEO, NG, 2>), grid, dim3(kThreads), 0, s, a, p, w,
-                       out0, out1, rows, GEO - 1);
+                       out0, out1);
+}
+
+template <typename Real>
+void enqueue_pg(const CallArgs& a, const Plan& p, const Work& w, int lowrows, bool f, bool f2,
+                hipStream_t s) {
+  const int T2 = p.S1 % (2 * p.T) == 0 ? 2 * p.T : p.T;
+  auto blocks = [&](int T) {
+    const int64_t n = (p.S1 / T) * p.nrows;
+    return (int)(n < kSpreadGrid ? n : kSpreadGrid);
+  };
+  const int nf = f ? blocks(p.T) : 0, n2 = f2 ? blocks(T2) : 0;
+  const dim3 grid((unsigned)(4 * lowrows + nf + n2));
+  if (p.w <= 16)
+    hipLaunchKernelGGL((k_spread_pg<Real, 1>), grid, dim3(kThreads), 0, s, a, p, w, lowrows, nf,
+                       T2);
+  else
+    hipLaunchKernelGGL((k_spread_pg<Real, 2>), grid, dim3(kThreads), 0, s, a, p, w, lowrows, nf,
+                       T2);
 }
 
 template <typename Real>
@@ -89,6 +179,12 @@ void enqueue_spread(const CallArgs& a, const Plan& p, const Work& w, int geo, in
                     hipStream_t s) {
   if (p.prec == 1) enqueue_real<float>(a, p, w, geo, ng, gbase, s);
   else enqueue_real<double>(a, p, w, geo, ng, gbase, s);
+}
+
+void enqueue_spread_pg(const CallArgs& a, const Plan& p, const Work& w, int lowrows, bool f,
+                       bool f2, hipStream_t s) {
+  if (p.prec == 1) enqueue_pg<float>(a, p, w, lowrows, f, f2, s);
+  else enqueue_pg<double>(a, p, w, lowrows, f, f2, s);
 }
 
 }  // namespace mils
