@@ -34,6 +34,8 @@ namespace {
 
 struct PlanEntry {
   Plan plan;
+  Plan split;                    // the same grid as a split transform (split.split > 0)
+  void* split_tw = nullptr;      // its twiddles
   void* tw = nullptr;            // twiddles (FP64 or FP32 pairs)
   double* inv_phihat = nullptr;  // K + 1 doubles
   double* inv_phihat2 = nullptr; // two-pass plans: n doubles in last-pass order
@@ -338,8 +340,9 @@ bool fft2_enabled() {
 
 int get_plan(mils_context* ctx, int64_t nf, double eps, int prec, int G, PlanEntry** out,
              bool upload, bool batch = false, int64_t n_fixed = 0, int tile_max = 0,
-             bool fft2 = false) {
-  PlanKey key{nf, eps, prec, G + (batch ? 10 : 0) + (fft2 ? 20 : 0), n_fixed, tile_max};
+             bool fft2 = false, bool split = true) {
+  PlanKey key{nf, eps, prec, G + (batch ? 10 : 0) + (fft2 ? 20 : 0) + (split ? 0 : 40), n_fixed,
+              tile_max};
   auto it = ctx->plans.find(key);
   if (it != ctx->plans.end() && (!upload || it->second.tw)) {
     *out = &it->second;
@@ -353,9 +356,12 @@ int get_plan(mils_context* ctx, int64_t nf, double eps, int prec, int G, PlanEnt
   r.n_fixed = n_fixed;
   r.tile_max = tile_max;
   r.fft2 = fft2;
+  r.split = split;
   if (!make_plan(r, &e.plan, &err)) return fail(ctx, MILS_ERR_UNSUPPORTED, err);
-  std::vector<double> tw;
+  std::vector<double> tw, stw;
   make_twiddles(&e.plan, &tw);
+  e.split.split = 0;
+  if (split_plan(e.plan, &e.split)) make_twiddles(&e.split, &stw);
   if (upload) {
     const size_t twbytes = prec == 1 ? tw.size() * sizeof(float) : tw.size() * sizeof(double);
     const size_t phbytes = sizeof(double) * (e.plan.K + 1);
@@ -366,11 +372,12 @@ int get_plan(mils_context* ctx, int64_t nf, double eps, int prec, int G, PlanEnt
     make_horner(e.plan, &hc);
     const size_t hbytes = hc.size() * (prec == 1 ? sizeof(float) : sizeof(double));
     const size_t p2bytes = e.plan.fft2 ? sizeof(double) * e.plan.n : 0;
-    e.bytes = twbytes + phbytes + nbytes + hbytes + p2bytes;
+    const size_t sbytes = stw.size() * sizeof(double);
+    e.bytes = twbytes + phbytes + nbytes + hbytes + p2bytes + sbytes;
     if (ctx->budget && ctx->plan_bytes + ctx->ws_bytes + e.bytes > ctx->budget)
       return fail(ctx, MILS_ERR_OOM, "plan tables exceed the HBM budget");
     char* buf = nullptr;
-    hipError_t he = hipMalloc(&buf, twbytes + phbytes + nbytes + hbytes + p2bytes + 1280);
+    hipError_t he = hipMalloc(&buf, twbytes + phbytes + nbytes + hbytes + p2bytes + sbytes + 1536);
     if (he != hipSuccess) return fail(ctx, MILS_ERR_OOM, "hipMalloc of plan tables failed");
     e.inv_phihat = reinterpret_cast<double*>(buf);
     e.tw = buf + ((phbytes + 255) & ~(size_t)255);
@@ -396,6 +403,12 @@ int get_plan(mils_context* ctx, int64_t nf, double eps, int prec, int G, PlanEnt
     }
     if (he != hipSuccess) return hip_fail(ctx, he, "plan upload");
     e.plan.hcoef = hdev;
+    if (sbytes) {
+      e.split.hcoef = hdev;
+      e.split_tw = hdev + ((hbytes + 255) & ~(size_t)255) + ((p2bytes + 255) & ~(size_t)255);
+      he = hipMemcpy(e.split_tw, stw.data(), sbytes, hipMemcpyHostToDevice);
+      if (he != hipSuccess) return hip_fail(ctx, he, "plan upload");
+    }
     if (e.plan.fft2)
       e.inv_phihat2 = reinterpret_cast<double*>(hdev + ((hbytes + 255) & ~(size_t)255));
     he = launch_phihat(e.inv_phihat, e.plan.K, (double)e.plan.w, (double)e.plan.n, nodes,
@@ -523,10 +536,24 @@ const ChipSet* get_chip(mils_context* ctx, double eps, bool make) {
 
 // Whether the single-series plan of (nf, eps, prec, G) exists with its device
 // tables (a call may then run without allocating).
-bool plan_ready(mils_context* ctx, int64_t nf, double eps, int prec, int G) {
-  PlanKey key{nf, eps, prec, G + (ctx->fft2 ? 20 : 0), 0, 0};
+bool plan_ready(mils_context* ctx, int64_t nf, double eps, int prec, int G, bool split) {
+  PlanKey key{nf, eps, prec, G + (ctx->fft2 ? 20 : 0) + (split ? 0 : 40), 0, 0};
   auto it = ctx->plans.find(key);
   return it != ctx->plans.end() && it->second.tw;
+}
+
+// Whether a call of nd points may take the grid of a split transform, which
+// can be a quarter larger than the staged one: not where that grid would go
+// over the context's budget (the smaller one may still fit).
+bool split_fits(mils_context* ctx, int64_t nf, double eps, int prec, int G, bool fft2, int64_t nd,
+                size_t extra) {
+  if (!ctx->budget || prec != 0) return true;
+  PlanEntry* pe = nullptr;
+  if (get_plan(ctx, nf, eps, prec, G, &pe, false, false, 0, 0, fft2) != MILS_OK) return true;
+  if (!pe->split.split || pe->plan.fft2) return true;
+  const size_t need = layout_work(pe->split, nd, G, nullptr, nullptr) + extra;
+  const size_t tables = pe->tw ? 0 : sizeof(double) * (size_t)pe->plan.K + ((size_t)1 << 20);
+  return ctx->plan_bytes + tables + std::max(need, ctx->ws_bytes) <= ctx->budget;
 }
 
 // Size for a buffer that must hold `need` bytes and holds `have`: half
@@ -747,14 +774,17 @@ int run_single(mils_context* ctx, const double* t, const double* y, const double
   if (cap && sync)
     return fail(ctx, MILS_ERR_INVALID_ARG,
                 "a synchronous call cannot be captured into a graph: use the _async variant");
-  if (cap && !plan_ready(ctx, p->nf, p->eps, p->precision, G))
+  const bool sok = split_fits(ctx, p->nf, p->eps, p->precision, G, ctx->fft2, nd, 0);
+  if (cap && !plan_ready(ctx, p->nf, p->eps, p->precision, G, sok))
     return fail(ctx, MILS_ERR_BUSY,
                 "captured call needs a plan that does not exist yet: make one uncaptured call "
                 "with these sizes first");
   PlanEntry* pe = nullptr;
-  int rc = get_plan(ctx, p->nf, p->eps, p->precision, G, &pe, true, false, 0, 0, ctx->fft2);
+  int rc = get_plan(ctx, p->nf, p->eps, p->precision, G, &pe, true, false, 0, 0, ctx->fft2, sok);
   if (rc != MILS_OK) return rc;
-  const Plan& plan = pe->plan;
+  // (stage timing runs the staged passes of the same grid)
+  const bool split = pe->split.split && !ctx->prof;
+  const Plan& plan = split ? pe->split : pe->plan;
   const size_t need = layout_work(plan, nd, G, nullptr, nullptr);
   if (cap && need > ctx->ws_bytes)
     return fail(ctx, MILS_ERR_BUSY,
@@ -765,7 +795,7 @@ int run_single(mils_context* ctx, const double* t, const double* y, const double
   if (cap) ctx->captured = true;
   Work w{};
   layout_work(plan, nd, G, ctx->ws, &w);
-  w.tw = pe->tw;
+  w.tw = split ? pe->split_tw : pe->tw;
   w.inv_phihat = pe->inv_phihat;
   w.inv_phihat2 = pe->inv_phihat2;
 
@@ -940,6 +970,9 @@ int mils_plan_info(mils_context* ctx, int64_t nd, const mils_params* p, mils_pla
   out->tile = pl.T;
   out->bin = pl.Tb;
   out->workspace_bytes = layout_work(pl, nd, 3, nullptr, nullptr);
+  if (pe->split.split)
+    out->workspace_bytes =
+        std::max<int64_t>(out->workspace_bytes, layout_work(pe->split, nd, 3, nullptr, nullptr));
   {
     // the launch sizes of kernels.hip
     const size_t elem = pl.prec == 1 ? 8 : 16;
@@ -1062,6 +1095,7 @@ struct ScratchTables {
   double eps = 0.0;
   int prec = 0;
   bool fft2 = false;
+  int64_t n = 0;
   bool chip = false;  // tables of the sub-grids in LDS (for eps) instead
   ChipPlan plan[kChipKinds] = {};
 };
@@ -1077,24 +1111,30 @@ static int mils_periodogram_noalloc_impl(mils_context* ctx, const double* t, con
   // [1/phihat][twiddles][quadrature nodes][kernel polynomials][1/phihat in
   // two-pass order][workspace]
   Plan plan;
-  std::string err;
-  PlanRequest r{p->nf, p->eps, p->precision, 3};
-  r.fft2 = ctx->fft2;
-  if (!make_plan(r, &plan, &err)) return fail(ctx, MILS_ERR_UNSUPPORTED, err);
-  std::vector<double> tw;
-  make_twiddles(&plan, &tw);
-  std::vector<double> z, gphi, hc;
-  phihat_nodes(plan, &z, &gphi);
-  make_horner(plan, &hc);
-  const bool f32 = plan.prec == 1;
+  std::vector<double> tw, z, gphi, hc;
+  const bool f32 = p->precision == 1;
   auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
-  const size_t ph_b = up(sizeof(double) * (plan.K + 1));
-  const size_t tw_b = up(tw.size() * (f32 ? sizeof(float) : sizeof(double)));
-  const size_t nd_b = up(sizeof(double) * 2 * z.size());
-  const size_t hc_b = up(hc.size() * (f32 ? sizeof(float) : sizeof(double)));
-  const size_t p2_b = plan.fft2 ? up(sizeof(double) * plan.n) : 0;
-  const size_t tables = ph_b + tw_b + nd_b + hc_b + p2_b;
-  const size_t need = tables + layout_work(plan, nd, 3, nullptr, nullptr);
+  size_t ph_b = 0, tw_b = 0, nd_b = 0, hc_b = 0, p2_b = 0, tables = 0, need = 0;
+  // (the staged passes; where the grid of a split transform does not fit the
+  // scratch, on their own smaller grid)
+  for (bool split : {true, false}) {
+    std::string err;
+    PlanRequest r{p->nf, p->eps, p->precision, 3};
+    r.fft2 = ctx->fft2;
+    r.split = split;
+    if (!make_plan(r, &plan, &err)) return fail(ctx, MILS_ERR_UNSUPPORTED, err);
+    make_twiddles(&plan, &tw);
+    phihat_nodes(plan, &z, &gphi);
+    make_horner(plan, &hc);
+    ph_b = up(sizeof(double) * (plan.K + 1));
+    tw_b = up(tw.size() * (f32 ? sizeof(float) : sizeof(double)));
+    nd_b = up(sizeof(double) * 2 * z.size());
+    hc_b = up(hc.size() * (f32 ? sizeof(float) : sizeof(double)));
+    p2_b = plan.fft2 ? up(sizeof(double) * plan.n) : 0;
+    tables = ph_b + tw_b + nd_b + hc_b + p2_b;
+    need = tables + layout_work(plan, nd, 3, nullptr, nullptr);
+    if (need <= kNoAllocBytes || !plan.split) break;
+  }
   if (need > kNoAllocBytes)
     return fail(ctx, MILS_ERR_UNSUPPORTED,
                 "the call needs " + std::to_string(need) + " bytes of device scratch; the " +
@@ -1147,7 +1187,8 @@ static int mils_periodogram_noalloc_impl(mils_context* ctx, const double* t, con
     std::lock_guard<std::mutex> lk(g_scratch_mu);
     ScratchTables& res = g_scratch_tables[ctx->device];
     const bool same = res.valid && !res.chip && res.nf == p->nf && res.eps == p->eps &&
-                      res.prec == p->precision && res.fft2 == (bool)plan.fft2;
+                      res.prec == p->precision && res.fft2 == (bool)plan.fft2 &&
+                      res.n == plan.n;
     if (!same) {
       res.valid = false;
       std::vector<float> tw32, hc32;
@@ -1182,6 +1223,7 @@ static int mils_periodogram_noalloc_impl(mils_context* ctx, const double* t, con
       res.eps = p->eps;
       res.prec = p->precision;
       res.fft2 = plan.fft2;
+      res.n = plan.n;
     }
   }
   Work w{};
@@ -1306,21 +1348,24 @@ int mils_periodogram_shared_t(mils_context* ctx, const double* t, const double* 
     return fail(ctx, MILS_ERR_UNSUPPORTED,
                 "the shared-times call reads its sort decision back: it cannot be captured");
   PlanEntry* pe = nullptr;
-  rc = get_plan(ctx, p->nf, p->eps, p->precision, 3, &pe, true);
-  if (rc != MILS_OK) return rc;
-  const Plan& plan = pe->plan;
-  // workspace: the single-series layout, then B and B2 per output
-  // frequency and one statistics block per series plus one for the weights
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  const size_t base = up(layout_work(plan, nd, 3, nullptr, nullptr));
   const size_t bsum = up(sizeof(double) * 2 * (size_t)p->nf);
   const size_t nst = (size_t)nseries + 1;
   const size_t low = up(sizeof(double) * 6 * kLowMax * kLowParts);
+  const size_t extra = 2 * bsum + 3 * low + up(sizeof(DevStats) * nst) + 256;
+  rc = get_plan(ctx, p->nf, p->eps, p->precision, 3, &pe, true, false, 0, 0, false,
+                split_fits(ctx, p->nf, p->eps, p->precision, 3, false, nd, extra));
+  if (rc != MILS_OK) return rc;
+  const bool split = pe->split.split;
+  const Plan& plan = split ? pe->split : pe->plan;
+  // workspace: the single-series layout, then B and B2 per output
+  // frequency and one statistics block per series plus one for the weights
+  const size_t base = up(layout_work(plan, nd, 3, nullptr, nullptr));
   rc = ensure_workspace(ctx, base + 2 * bsum + 3 * low + up(sizeof(DevStats) * nst));
   if (rc != MILS_OK) return rc;
   Work w{};
   layout_work(plan, nd, 3, ctx->ws, &w);
-  w.tw = pe->tw;
+  w.tw = split ? pe->split_tw : pe->tw;
   w.inv_phihat = pe->inv_phihat;
   double* bsum_b = reinterpret_cast<double*>(ctx->ws + base);
   double* bsum_b2 = reinterpret_cast<double*>(ctx->ws + base + bsum);

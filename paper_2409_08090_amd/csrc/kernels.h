@@ -77,6 +77,18 @@ void enqueue_rows(const CallArgs& a, const Plan& p, const Work& w, int ngeo, boo
 // (spread.hip), over the tiles of rows whose flag is set.
 void enqueue_spread(const CallArgs& a, const Plan& p, const Work& w, int geo, int ng, int gbase,
                     hipStream_t s);
+// Allows a kernel more than 64 KB of dynamic LDS a workgroup.
+void big_lds(const void* kern, size_t bytes);
+
+// split.hip: the first pass of a split plan over grids g0 .. g0 + ng - 1 of w
+// (grid grid_2f of geometry 2f); then the last: into sums s0 (grid g0) and s1
+// (the next, or NULL) if given, else the power of a (three grids), or the
+// powers of the a.nser series that share their weights.
+void enqueue_split_first(const Plan& p, const Work& w, int g0, int ng, int grid_2f,
+                         hipStream_t s);
+void enqueue_split_last(const CallArgs& a, const Plan& p, const Work& w, int g0, int ng,
+                        int lowrows, double* s0, double* s1, hipStream_t s);
+
 // In one launch: lowrows rows of direct sums near f = 0 (0: none), geometry f
 // into grids 0 and 1, and geometry 2f into grid 2.
 void enqueue_spread_pg(const CallArgs& a, const Plan& p, const Work& w, int lowrows, bool f,

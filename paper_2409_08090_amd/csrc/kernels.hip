@@ -666,7 +666,7 @@ static inline unsigned grid_for(int64_t work, int64_t cap) {
 
 // Dynamic LDS above the default 64 KB of a workgroup must be allowed per
 // kernel (the big FFT passes use up to kLdsBig).
-static void big_lds(const void* kern, size_t bytes) {
+void big_lds(const void* kern, size_t bytes) {
   // once per kernel (the largest request so far), so that a call captured
   // into a graph after a first uncaptured one makes no attribute call
   static std::mutex mu;
@@ -994,6 +994,13 @@ static hipError_t launch_path_t(const CallArgs& a, const Plan& p, const Work& w,
     if (e == hipSuccess) e = hipStreamWaitEvent(s, aux->join, 0);
     return e;
   };
+  if (split_passes(p)) {
+    enqueue_split_first(p, w, 0, G, 2, s);
+    hipError_t e = join();
+    if (e != hipSuccess) return e;
+    enqueue_split_last(a, p, w, 0, G, lowrows, pg ? nullptr : a.sums, nullptr, s);
+    return hipGetLastError();
+  }
   if (p.fft2) {
     // two-pass register-tile FFT
     Fft2Bufs<Real> b;
@@ -1096,6 +1103,11 @@ static hipError_t launch_weight_sums_t(const CallArgs& aw, const Plan& p, const 
   enqueue_rows(aw, p, w, 2, true, s);
   enqueue_spread(aw, p, w, 1, 1, 1, s);
   enqueue_spread(aw, p, w, 2, 1, 2, s);
+  if (split_passes(p)) {
+    enqueue_split_first(p, w, 1, 2, 2, s);
+    enqueue_split_last(aw, p, w, 1, 2, kLowParts, bsum_b, bsum_b2, s);
+    return hipGetLastError();
+  }
   T2* in[2];
   enqueue_passes<Real>(p, w, 1, 2, 2, s, in);
   CallArgs as = aw;
@@ -1140,6 +1152,11 @@ static hipError_t launch_series_group_t(const CallArgs& a, const Plan& p, const 
     al.spow[g] = sg.power[g];
     al.sst[g] = sg.stats[g];
     al.slow[g] = sg.lowfix[g];
+  }
+  if (split_passes(p)) {
+    enqueue_split_first(p, w, 0, sg.m, -1, s);
+    enqueue_split_last(al, p, w, 0, sg.m, kLowParts, nullptr, nullptr, s);
+    return hipGetLastError();
   }
   T2* in[3];
   enqueue_passes<Real>(p, w, 0, sg.m, -1, s, in);

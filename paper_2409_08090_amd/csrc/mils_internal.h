@@ -51,6 +51,8 @@ struct Plan {
   int64_t nbins;           // ceil(n / Tb)
   int D;                   // rows per workgroup of the last pass
   int fft2;                // 1: two-pass register-tile FFT (fft2.h), n = L0 * L1
+  int split;               // R > 0: two passes split by residue (split.hip), n = R la L1
+  int la;
   int64_t tw_count;        // complex entries in the twiddle buffer
   const void* hcoef;       // device: kernel polynomial coefficients (Real), see kHornerK
 };
@@ -194,6 +196,12 @@ constexpr int kElast64 = 3072, kElast32 = 6144;
 constexpr int kLowMax = 16;
 constexpr int kLowGroup = 8;
 constexpr int kLowBlocks = 512;
+// Whether p's passes are those of its split transform (and not the staged or
+// the register-tile passes of the same grid).
+__host__ __device__ inline bool split_passes(const Plan& p) {
+  return p.split > 0 && p.npass == 2 && !p.fft2;
+}
+constexpr int kSplitMax = 16;  // most residues of a split transform
 constexpr int kLowParts = 8;  // rows of lowfix (partial sums; the last pass adds them)
 // Calls of at most kLowFusedNd points form them in workgroups of the spread's
 // launch, one row per 2048 points up to kLowRows (a quarter of the frequencies

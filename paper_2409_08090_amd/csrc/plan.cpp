@@ -208,6 +208,58 @@ void chip_kernel(double eps, bool wide, double* sigma, int* w, double* beta) {
   *beta = kernel_beta(wi, s);
 }
 
+namespace {
+
+// n = R La L1 of a split transform and its cost a cell in the units of the
+// planner's estimate, from times at n = 5e5 .. 1.6e7: a residue more costs
+// little (its reads come from L2), lines of 512 in the last pass a fifth of it
+// (their 64-byte pieces), and first-pass lines other than 512 keep 64-byte
+// pieces (256: more residues) or half as many workgroups a CU (1024).
+struct SplitShape {
+  int R = 0, La = 0, L1 = 0;
+  double cost = 1e300;
+};
+
+bool split_shape(int64_t n, SplitShape* out) {
+  SplitShape best;
+  for (int La : {256, 512, 1024})
+    for (int L1 : {512, 1024, 2048}) {
+      if (n % ((int64_t)La * L1)) continue;
+      const int64_t R = n / ((int64_t)La * L1);
+      if (R > kSplitMax) continue;
+      const double c = 1.75 + 0.008 * (double)R + (La == 512 ? 0.0 : 0.03) +
+                       (L1 == 512 ? 0.27 : L1 == 1024 ? 0.06 : 0.0);
+      if (c < best.cost) best = {(int)R, La, L1, c};
+    }
+  if (!best.R) return false;
+  *out = best;
+  return true;
+}
+
+}  // namespace
+
+bool split_plan(const Plan& p, Plan* out) {
+  if (!p.split) return false;
+  Plan q = p;
+  const int64_t L0 = (int64_t)p.split * p.la, L1 = p.n / L0;
+  q.npass = 2;
+  q.fft2 = 0;
+  q.pass[0] = FftPass{};
+  q.pass[1] = FftPass{};
+  q.pass[0].L = (int)L0;
+  q.pass[0].P = 1;
+  q.pass[0].S = L1;
+  q.pass[1].L = (int)L1;
+  q.pass[1].P = L0;
+  q.pass[1].S = 1;
+  q.nrows = L0;
+  q.S1 = L1;
+  q.T = (int)std::min<int64_t>(L1, kTileMaxCells);
+  q.D = 1;
+  *out = q;
+  return true;
+}
+
 bool make_plan(const PlanRequest& r, Plan* out, std::string* err) {
   Plan p{};
   p.prec = r.prec;
@@ -336,6 +388,7 @@ bool make_plan(const PlanRequest& r, Plan* out, std::string* err) {
   // 2048..4096 for three grids, to 8192 for one), estimated at 0.55 (first
   // pass: pruned reads, contiguous writes) + 1.0 (last pass) + 0.15 (the
   // transpose of the results) of one pass over the grid.
+  const int staged_w = kernel_width(r.eps, (double)best_n / (double)r.nf, r.prec);
   int f2_l0 = 0, f2_l1 = 0;
   if (r.fft2 && best_np >= 3 && (G == 1 || G == 3)) {
     double f2_cost = 1e300;
@@ -368,9 +421,46 @@ bool make_plan(const PlanRequest& r, Plan* out, std::string* err) {
       f2_l0 = 0;
     }
   }
+  // Split transform (split.hip) of an FP64 grid of three and more passes: n =
+  // R La L1 within the limit, where it is estimated cheaper.  The staged passes
+  // can take n too (stage timing and calls with a fixed scratch run those).
+  // Against three passes: 178 us -> 108 at n = 1.5e6, 447 -> 285 at 6.3e6; on
+  // the grids of the register-tile FFT 230 -> 200 at 4.2e6 and 412 -> 391 at
+  // 8.4e6, but at 1.7e7 a tie with the usual frequency step and 1105 -> 1227
+  // with a five times larger one (every residue reads the rows that are
+  // reached: all of them then).
+  if (r.split && r.prec == 0 && !r.batch && r.n_fixed == 0 && (G == 1 || G == 3)) {
+    SplitShape best;
+    if (f2_l0) {
+      if (best_n <= ((int64_t)1 << 23)) split_shape(best_n, &best);
+    } else if (best_np >= 3) {
+      for (int64_t n : cand) {
+        if ((double)n > nlim) break;
+        SplitShape sh;
+        if (!split_shape(n, &sh)) continue;
+        std::vector<int> lens;
+        bool big = false;
+        if (!factor(best_np, n, &lens, &big) || big) continue;
+        const int wn = kernel_width(r.eps, (double)n / (double)r.nf, r.prec);
+        const double cost = (double)n * sh.cost + 0.049 * wn * (double)r.nf;
+        if (cost < best_cost) {
+          best_cost = cost;
+          best = sh;
+          best_n = n;
+          best_len = lens;
+          best_big = false;
+        }
+      }
+    }
+    p.split = best.R;
+    p.la = best.La;
+  }
   p.n = best_n;
   p.sigma = (double)best_n / (double)r.nf;
   p.w = kernel_width(r.eps, p.sigma, r.prec);
+  // (a larger grid than the staged passes need keeps their kernel's width: the
+  // spread takes 16 cells in the time of fewer, and the sums gain accuracy)
+  if (p.split && !f2_l0) p.w = std::max(p.w, std::min(staged_w, 16));
   // a grid that fits one workgroup costs nothing extra with the widest kernel,
   // and tiny problems (a handful of frequencies, huge sigma) need the margin:
   // the floating-mean cancellation at the lowest frequencies amplifies the
@@ -474,9 +564,12 @@ void make_twiddles(Plan* p, std::vector<double>* tw) {
   for (int i = 0; i < p->npass; ++i) {
     FftPass& ps = p->pass[i];
     ps.twL_off = (int64_t)(tw->size() / 2);
-    if (ps.big || p->fft2) {
-      for (int x = 0; x < kTwLo; ++x) push_root(x, ps.L);
-      for (int h = 0; h < (ps.L + kTwLo - 1) / kTwLo; ++h) push_root((int64_t)h * kTwLo, ps.L);
+    // (a split plan's own passes: lines of la in the first)
+    const bool split = split_passes(*p);
+    if (ps.big || p->fft2 || split) {
+      const int L = split && i == 0 ? p->la : ps.L;
+      for (int x = 0; x < kTwLo; ++x) push_root(x, L);
+      for (int h = 0; h < (L + kTwLo - 1) / kTwLo; ++h) push_root((int64_t)h * kTwLo, L);
     } else {
       for (int x = 0; x < ps.L; ++x) push_root(x, ps.L);
     }
@@ -580,7 +673,7 @@ size_t layout_work(const Plan& p, int64_t nd, int G, char* base, Work* w, bool p
   }
   const size_t cbytes = p.prec == 1 ? 8 : 16;
   for (int g = 0; g < G; ++g) x.grid[g] = take(cbytes * p.n);
-  if (p.npass >= 3 || p.fft2)
+  if (p.npass >= 3 || p.fft2 || p.split)
     for (int g = 0; g < G; ++g) x.grid2[g] = take(cbytes * p.n);
   if (p.fft2) x.f2out = take((G == 3 ? sizeof(double) : 2 * sizeof(double)) * p.n);
   off = (off + 255) & ~(size_t)255;

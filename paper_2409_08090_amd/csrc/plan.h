@@ -21,6 +21,7 @@ struct PlanRequest {
   bool batch = false;   // plan for the batched kernels (no big passes)
   int64_t n_fixed = 0;  // use exactly this grid size (must factor), 0 = choose
   int tile_max = 0;     // largest spreading tile (cells), 0 = kTileMax
+  bool split = true;    // grid sizes that a split transform can take (FP64)
   bool fft2 = false;    // the two-pass register-tile FFT may replace plans of 3+ passes
 };
 
@@ -45,6 +46,10 @@ void chip_kernel(double eps, bool wide, double* sigma, int* w, double* beta);
 // Build the plan; returns false (with a message) when no supported
 // factorisation exists.
 bool make_plan(const PlanRequest& r, Plan* out, std::string* err);
+
+// The plan of the same grid as two passes split by residue (split.hip) in
+// place of three and more; false if the plan has none.
+bool split_plan(const Plan& p, Plan* out);
 
 // Twiddle tables of the plan, as interleaved (re, im) pairs in FP64; the
 // caller narrows them to FP32 for FP32 plans.  Offsets are stored in the plan.
