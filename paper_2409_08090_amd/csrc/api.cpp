@@ -219,7 +219,7 @@ struct mils_context {
   int num_cu = 256;
   // second stream (default priority) and fork/join events of a periodogram
   hipStream_t aux = nullptr;
-  hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_mid = nullptr;
+  hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   BatchState batch;
   // the single-series call captured as a HIP graph: its key (arguments,
   // workspace layout, plan) was seen on the previous call; replayed while
@@ -818,7 +818,7 @@ int run_single(mils_context* ctx, const double* t, const double* y, const double
   }
   ctx->last_words = kPathStatus;
   StageHook hook{prof_hook, ctx};
-  AuxStream aux{ctx->aux, ctx->ev_fork, ctx->ev_join, ctx->ev_mid};
+  AuxStream aux{ctx->aux, ctx->ev_fork, ctx->ev_join};
   if (!ctx->prof && ctx->aux && ctx->sg.enabled && graphs_enabled()) {
     he = launch_single_graph(ctx, a, plan, w, stream, aux);
   } else {
@@ -892,7 +892,6 @@ int mils_context_create(int device, uint64_t hbm_budget_bytes, mils_context** ou
     if (he == hipSuccess) he = hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking);
     if (he == hipSuccess) he = hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming);
     if (he == hipSuccess) he = hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming);
-    if (he == hipSuccess) he = hipEventCreateWithFlags(&c->ev_mid, hipEventDisableTiming);
     if (he == hipSuccess) he = hipMalloc(reinterpret_cast<void**>(&c->chip_done), kChipMaxSeries * sizeof(ChipDone));
     if (he == hipSuccess) he = hipMemsetAsync(c->chip_done, 0, kChipMaxSeries * sizeof(ChipDone), c->aux);
     if (he == hipSuccess) he = hipStreamSynchronize(c->aux);
@@ -933,7 +932,6 @@ int mils_context_destroy(mils_context* ctx) {
     if (ctx->sg.done) (void)hipEventDestroy(ctx->sg.done);
     if (ctx->ev_fork) (void)hipEventDestroy(ctx->ev_fork);
     if (ctx->ev_join) (void)hipEventDestroy(ctx->ev_join);
-    if (ctx->ev_mid) (void)hipEventDestroy(ctx->ev_mid);
     if (ctx->aux) (void)hipStreamDestroy(ctx->aux);
     if (ctx->host_status) (void)hipHostFree(ctx->host_status);
     for (auto& r : ctx->prof_recs) {
@@ -1234,7 +1232,7 @@ static int mils_periodogram_noalloc_impl(mils_context* ctx, const double* t, con
   w.tw = twd;
   w.inv_phihat = inv_phihat;
   w.inv_phihat2 = iphi2;
-  AuxStream aux{ctx->aux, ctx->ev_fork, ctx->ev_join, ctx->ev_mid};
+  AuxStream aux{ctx->aux, ctx->ev_fork, ctx->ev_join};
   he = launch_path(a, plan, w, stream, nullptr, ctx->aux ? &aux : nullptr);
   if (he != hipSuccess) return hip_fail(ctx, he, "kernel launch");
   ctx->last_stats = w.stats;
@@ -1444,7 +1442,7 @@ int mils_periodogram_shared_t(mils_context* ctx, const double* t, const double* 
       he = launch_series_group(a, plan, ww, sg, stream);
     }
   } else {
-    AuxStream aux{ctx->aux, ctx->ev_fork, ctx->ev_join, ctx->ev_mid};
+    AuxStream aux{ctx->aux, ctx->ev_fork, ctx->ev_join};
     for (int64_t i = 0; i < nseries && he == hipSuccess; ++i) {
       CallArgs as = a;
       as.y = y + i * nd;
@@ -1926,9 +1924,10 @@ int build_batch(mils_context* ctx, BatchState& B, const std::vector<int64_t>& id
   return MILS_OK;
 }
 
-hipError_t launch_all(const BatchState& B, hipStream_t s) {
+hipError_t launch_all(const mils_context* ctx, const BatchState& B, hipStream_t s) {
+  const AuxStream aux{ctx->aux, ctx->ev_fork, ctx->ev_join};
   for (const BatchLaunch& L : B.launches) {
-    hipError_t e = launch_batch(L, s);
+    hipError_t e = launch_batch(L, s, ctx->aux ? &aux : nullptr);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -1990,9 +1989,9 @@ int autotune_batch(mils_context* ctx, int64_t ncurves, const int64_t* nd_off, co
         continue;
       }
       if (rc != MILS_OK) break;
-      he = launch_all(T, stream);  // warm-up
+      he = launch_all(ctx, T, stream);  // warm-up
       if (he == hipSuccess) he = hipEventRecord(e0, stream);
-      if (he == hipSuccess) he = launch_all(T, stream);
+      if (he == hipSuccess) he = launch_all(ctx, T, stream);
       if (he == hipSuccess) he = hipEventRecord(e1, stream);
       if (he == hipSuccess) he = hipEventSynchronize(e1);
       float ms = 0.f;
@@ -2100,14 +2099,14 @@ int mils_batch_run(mils_context* ctx, int64_t ncurves, const int64_t* nd_off, co
     }
     he = hipStreamBeginCapture(B.cap_stream, hipStreamCaptureModeThreadLocal);
     if (he == hipSuccess) {
-      hipError_t le = launch_all(B, B.cap_stream);
+      hipError_t le = launch_all(ctx, B, B.cap_stream);
       he = hipStreamEndCapture(B.cap_stream, &B.graph);
       if (le != hipSuccess) he = le;
     }
     if (he == hipSuccess) he = hipGraphInstantiate(&B.exec, B.graph, nullptr, nullptr, 0);
     if (he != hipSuccess) return hip_fail(ctx, he, "batch graph capture");
   }
-  he = use_graph && B.exec ? hipGraphLaunch(B.exec, stream) : launch_all(B, stream);
+  he = use_graph && B.exec ? hipGraphLaunch(B.exec, stream) : launch_all(ctx, B, stream);
   if (he == hipSuccess)
     he = hipMemcpyAsync(B.status_host, B.status_dev, sizeof(int32_t) * ncurves,
                         hipMemcpyDeviceToHost, stream);

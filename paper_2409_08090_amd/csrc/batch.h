@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "chip.h"
+#include "kernels.h"
 #include "mils_internal.h"
 
 namespace mils {
@@ -100,7 +101,8 @@ struct BatchLaunch {
 // Enqueue the kernels of a batch: the series that fit LDS in one launch; for
 // the others per-series statistics, binning and direct low-frequency sums,
 // both spreads, the FFT passes, the last pass with power.
-hipError_t launch_batch(const BatchLaunch& bl, hipStream_t s);
+// Series that fit LDS run on aux (NULL: none) beside the others.
+hipError_t launch_batch(const BatchLaunch& bl, hipStream_t s, const AuxStream* aux);
 
 // Allows the on-chip kernel its dynamic LDS (before any launch or capture).
 hipError_t batch_prepare();

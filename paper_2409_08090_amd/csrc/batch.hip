@@ -26,6 +26,7 @@ namespace {
 constexpr int NT = kThreads;
 
 // Statistics of one series by one workgroup (see k_stats); writes *st.
+template <int NT>
 __device__ void stats_block(const CallArgs& a, DevStats* st, double* sh /* 5*NT */,
                             int* shi /* 2*NT */) {
   const int tid = threadIdx.x;
@@ -105,6 +106,7 @@ __device__ void stats_block(const CallArgs& a, DevStats* st, double* sh /* 5*NT 
 // Binning of one series by one workgroup: the sorted fast path, and a
 // counting sort into the slot's sorted copies when the bins are not
 // non-decreasing.  Leaves st->need_sort set when the sort ran.
+template <int NT>
 __device__ void bins_block(const CallArgs& a, const Plan& p, const Work& w, DevStats* st,
                            int* shi /* NT + 2 */) {
   const int tid = threadIdx.x;
@@ -174,6 +176,7 @@ __device__ void bins_block(const CallArgs& a, const Plan& p, const Work& w, DevS
 
 // Direct FP64 sums near f = 0 for one series (see k_lowfreq): lowfix gets
 // kLowMax x 6 values, st->k_lo / st->nlow the frequencies they belong to.
+template <int NT>
 __device__ void lowfreq_block(const CallArgs& a, DevStats* st, double* lowfix, double* red) {
   const DevStats& s = *st;
   int64_t k_lo;
@@ -183,7 +186,9 @@ __device__ void lowfreq_block(const CallArgs& a, DevStats* st, double* lowfix, d
   for (int g0 = 0; g0 < nlow; g0 += kLowGroup) {
     const int ng = nlow - g0 < kLowGroup ? nlow - g0 : kLowGroup;
     low_accumulate<kLowGroup>(a, s, k_lo + g0, ng, threadIdx.x, NT, acc);
-    block_sum<NT, 6 * kLowGroup>(acc, red, lowfix + 6 * g0);
+    const double sum = block_share_sum<NT, 6 * kLowGroup>(acc, red);
+    if ((int)threadIdx.x < 6 * kLowGroup) lowfix[6 * g0 + threadIdx.x] = sum;
+    __syncthreads();
   }
   if (threadIdx.x == 0) {
     st->k_lo = k_lo;
@@ -222,8 +227,13 @@ __device__ __forceinline__ void load_plan(const Plan* src, Plan* dst) {
 }
 
 // Per-series prologue: one workgroup per series (series that run in LDS
-// return at once).
-__global__ __launch_bounds__(NT) void k_bpro(BatchArgs ba) {
+// return at once).  Bound by the latency of one workgroup's passes over its
+// points and of the direct sums' reduction, which a batch of fewer series than
+// CUs waits for: 72 us with eight waves and shared-out sums (64 series of 100
+// to 10000 points), 113 with four and 288 exchanges a wave, 110 with sixteen.
+constexpr int kBproThreads = 512;
+__global__ __launch_bounds__(kBproThreads) void k_bpro(BatchArgs ba) {
+  constexpr int NT = kBproThreads;
   __shared__ double sh[5 * NT];
   __shared__ int shi[2 * NT + 2];
   __shared__ Plan sp;
@@ -234,13 +244,13 @@ __global__ __launch_bounds__(NT) void k_bpro(BatchArgs ba) {
   __syncthreads();
   const CallArgs a = curve_args(ba, c);
   const Work w = ba.works[ci];
-  stats_block(a, w.stats, sh, shi);
+  stats_block<NT>(a, w.stats, sh, shi);
   if (w.stats->status != 0) {
     if (threadIdx.x == 0) ba.status[c.index] = w.stats->status;
     return;
   }
-  bins_block(a, sp, w, w.stats, shi);
-  lowfreq_block(a, w.stats, w.lowfix, sh);
+  bins_block<NT>(a, sp, w, w.stats, shi);
+  lowfreq_block<NT>(a, w.stats, w.lowfix, sh);
   // row flags of both geometries, so that the spread's workgroups of empty
   // rows stop at once
   const int h = (int)ceil(sp.hw) + 1;
@@ -385,12 +395,12 @@ __global__ __launch_bounds__(NT) void k_bsmall(BatchArgs ba, const BatchItem* it
   __syncthreads();
   const CallArgs a = curve_args(ba, c);
   const Work w = ba.works[ci];
-  stats_block(a, w.stats, sh, shi);
+  stats_block<NT>(a, w.stats, sh, shi);
   if (w.stats->status != 0) {
     if (tid == 0) ba.status[c.index] = w.stats->status;
     return;
   }
-  lowfreq_block(a, w.stats, w.lowfix, sh);
+  lowfreq_block<NT>(a, w.stats, w.lowfix, sh);
   const DevStats st = *w.stats;
   const int n = (int)sp.n;
   double2* g = reinterpret_cast<double2*>(smem);  // element l of grid q at 3 l + q
@@ -474,7 +484,7 @@ __global__ __launch_bounds__(NT) void k_bsmall(BatchArgs ba, const BatchItem* it
 }
 
 template <typename Real>
-hipError_t launch_t(const BatchLaunch& bl, hipStream_t s) {
+hipError_t launch_t(const BatchLaunch& bl, hipStream_t s, const AuxStream* aux) {
   const BatchArgs& ba = bl.args;
   if (bl.nchip_series > 0) {
     hipError_t e = launch_chip_prologue(ba, bl.chip_series, bl.nchip_series, s);
@@ -484,12 +494,26 @@ hipError_t launch_t(const BatchLaunch& bl, hipStream_t s) {
         e = launch_chip_items(ba, bl.chip[i], bl.chip_items[i], bl.nchip_items[i], s);
     if (e != hipSuccess) return e;
   }
+  // the series that run in LDS, on the auxiliary stream beside the phases of
+  // the others (few of them leave most of the chip idle for their 65 us)
+  const bool fork = sizeof(Real) == 4 && bl.nsmall > 0 && bl.nstaged > 0 && aux;
   if constexpr (sizeof(Real) == 4)
-    if (bl.nsmall > 0)
-      hipLaunchKernelGGL(k_bsmall<Real>, dim3(bl.nsmall), dim3(NT), bl.small_lds, s, ba,
+    if (bl.nsmall > 0) {
+      hipStream_t s2 = fork ? aux->s : s;
+      if (fork) {
+        hipError_t e = hipEventRecord(aux->fork, s);
+        if (e == hipSuccess) e = hipStreamWaitEvent(s2, aux->fork, 0);
+        if (e != hipSuccess) return e;
+      }
+      hipLaunchKernelGGL(k_bsmall<Real>, dim3(bl.nsmall), dim3(NT), bl.small_lds, s2, ba,
                          bl.small_items);
+      if (fork) {
+        hipError_t e = hipEventRecord(aux->join, s2);
+        if (e != hipSuccess) return e;
+      }
+    }
   if (bl.nstaged == 0) return hipGetLastError();
-  hipLaunchKernelGGL(k_bpro, dim3(ba.ncurves), dim3(NT), 0, s, ba);
+  hipLaunchKernelGGL(k_bpro, dim3(ba.ncurves), dim3(kBproThreads), 0, s, ba);
   if (bl.nspread > 0)
     hipLaunchKernelGGL((bl.wmax > 16 ? k_bspread2<Real, 2> : k_bspread2<Real, 1>),
                        dim3(bl.nspread), dim3(NT), 0, s, ba, bl.spread_items);
@@ -500,14 +524,18 @@ hipError_t launch_t(const BatchLaunch& bl, hipStream_t s) {
   if (bl.nlast > 0)
     hipLaunchKernelGGL(k_blast<Real>, dim3(bl.nlast), dim3(last_threads<Real>()), bl.last_lds, s,
                        ba, bl.last_items);
+  if (fork) {
+    hipError_t e = hipStreamWaitEvent(s, aux->join, 0);
+    if (e != hipSuccess) return e;
+  }
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_batch(const BatchLaunch& bl, hipStream_t s) {
+hipError_t launch_batch(const BatchLaunch& bl, hipStream_t s, const AuxStream* aux) {
   (void)hipGetLastError();  // see launch_path: a handled earlier failure is not this launch's
-  return bl.prec == 1 ? launch_t<float>(bl, s) : launch_t<double>(bl, s);
+  return bl.prec == 1 ? launch_t<float>(bl, s, aux) : launch_t<double>(bl, s, aux);
 }
 
 hipError_t batch_prepare() {

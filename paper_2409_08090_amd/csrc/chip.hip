@@ -516,30 +516,6 @@ __global__ __launch_bounds__(ChipShape<N>::NT1) void k_chip_single(CallArgs a, C
 }
 
 // ---- batches --------------------------------------------------------------------
-constexpr int kProThreads = 256;
-
-// Sum of CNT values of every lane of a wave, the values shared out over the
-// lanes: after log2(64) exchanges of halves, lane l holds the totals of the
-// CNT / 32 values (CNT a multiple of 32) v[0 ..] that belong to bits 5 .. 1 of
-// l (93 exchanges for 96 values instead of 576).
-template <int CNT>
-__device__ __forceinline__ void wave_share_sum(double (&v)[CNT]) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int step = 0; step < 5; ++step) {
-    const int off = 32 >> step;
-    const int half = CNT >> (step + 1);
-    const bool up = lane & off;
-#pragma unroll
-    for (int i = 0; i < half; ++i) {
-      const double keep = up ? v[i + half] : v[i];
-      const double give = up ? v[i] : v[i + half];
-      v[i] = keep + __shfl_xor(give, off, 64);
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < CNT / 32; ++i) v[i] += __shfl_xor(v[i], 1, 64);
-}
 
 __device__ __forceinline__ CallArgs chip_args(const BatchArgs& ba, const BatchCurve& c) {
   CallArgs a{};
@@ -562,10 +538,11 @@ __device__ __forceinline__ CallArgs chip_args(const BatchArgs& ba, const BatchCu
 
 // Statistics, point records (w^ y~, w^: the visits then need no division) and
 // the direct sums near f = 0 of one series.
-__global__ __launch_bounds__(kProThreads) void k_chip_pro(BatchArgs ba, const BatchItem* series) {
-  constexpr int NT = kProThreads, NV = 6 * kLowMax;
+template <int NT>
+__global__ __launch_bounds__(NT) void k_chip_pro(BatchArgs ba, const BatchItem* series) {
+  constexpr int NV = 6 * kLowMax;
   __shared__ Part parts[NT / 64];
-  __shared__ double red[NT / 64][NV];
+  __shared__ double red[NT / 64 * NV];
   const int tid = threadIdx.x;
   const int ci = series[blockIdx.x].curve;
   const BatchCurve& c = ba.curves[ci];
@@ -592,22 +569,8 @@ __global__ __launch_bounds__(kProThreads) void k_chip_pro(BatchArgs ba, const Ba
   if (st.nlow > 0) {
     double acc[NV];
     low_accumulate<kLowMax>(a, st, st.k_lo, st.nlow, tid, NT, acc);
-    wave_share_sum(acc);
-    const int lane = tid & 63;
-    if (!(lane & 1)) {
-      int base = 0;  // of the values that this lane holds
-#pragma unroll
-      for (int s = 0; s < 5; ++s)
-        if (lane & (32 >> s)) base += NV >> (s + 1);
-#pragma unroll
-      for (int i = 0; i < NV / 32; ++i) red[tid >> 6][base + i] = acc[i];
-    }
-    __syncthreads();
-    if (tid < 6 * st.nlow) {
-      double s = 0.0;
-      for (int i = 0; i < NT / 64; ++i) s += red[i][tid];
-      w.lowfix[tid] = s;
-    }
+    const double sum = block_share_sum<NT, NV>(acc, red);
+    if (tid < 6 * st.nlow) w.lowfix[tid] = sum;
   }
   if (tid == 0) *w.stats = st;
 }
@@ -717,10 +680,15 @@ hipError_t launch_chip_single(const CallArgs& a, const ChipPlan& cp, int D, DevS
   return hipGetLastError();
 }
 
+constexpr int kProWide = 512;
 hipError_t launch_chip_prologue(const BatchArgs& ba, const BatchItem* series, int n,
                                 hipStream_t s) {
   (void)hipGetLastError();
-  hipLaunchKernelGGL(k_chip_pro, dim3((unsigned)n), dim3(kProThreads), 0, s, ba, series);
+  // Few series: eight waves each, as the call waits for the longest (32 us for
+  // up to 5000 points against 46 with four).  Many: four, of which a CU holds
+  // two workgroups (10 000 series: 0.8 ms against 1.0).
+  if (n < kProWide) hipLaunchKernelGGL(k_chip_pro<512>, dim3((unsigned)n), dim3(512), 0, s, ba, series);
+  else hipLaunchKernelGGL(k_chip_pro<256>, dim3((unsigned)n), dim3(256), 0, s, ba, series);
   return hipGetLastError();
 }
 

@@ -26,7 +26,6 @@ enum Stage {
 struct AuxStream {
   hipStream_t s;
   hipEvent_t fork, join;
-  hipEvent_t mid;  // two-pass plans: the second branch's spread is done
 };
 
 // Optional hook called before (begin = 1) and after (begin = 0) each stage is

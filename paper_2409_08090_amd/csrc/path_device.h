@@ -825,6 +825,51 @@ __device__ __forceinline__ void low_accumulate(const CallArgs& a, const DevStats
   }
 }
 
+// Sums of NV = 3 2^k values over the lanes of a wave, in a fixed order: the
+// lanes exchange halves k times, each then holding three values of fewer lanes,
+// and add those up.  Returns the first of the three; lanes that are multiples
+// of 64 / 2^k have the totals.  (NV + 3 log2 exchanges instead of 6 NV: they go
+// through the LDS, whose rate they were bound by.)
+template <int NV>
+__device__ __forceinline__ int wave_share_sum(double* v) {
+  const int lane = threadIdx.x & 63;
+  int base = 0, off = 32;
+#pragma unroll
+  for (int half = NV / 2; half >= 3; half /= 2, off /= 2) {
+    const bool up = lane & off;
+    if (up) base += half;
+#pragma unroll
+    for (int i = 0; i < half; ++i) {
+      const double keep = up ? v[i + half] : v[i];
+      const double give = up ? v[i] : v[i + half];
+      v[i] = keep + __shfl_xor(give, off, 64);
+    }
+  }
+#pragma unroll
+  for (; off > 0; off /= 2)
+#pragma unroll
+    for (int i = 0; i < 3; ++i) v[i] += __shfl_xor(v[i], off, 64);
+  return base;
+}
+
+// The same over a workgroup of NT threads: thread i < NV gets total i.  red:
+// NT / 64 * NV doubles of LDS.
+template <int NT, int NV>
+__device__ __forceinline__ double block_share_sum(double* v, double* red) {
+  constexpr int kStep = 64 * 3 / NV;
+  static_assert(kStep >= 1 && NV == 3 * 64 / kStep, "three values a lane");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int base = wave_share_sum<NV>(v);
+  if ((lane & (kStep - 1)) == 0)
+#pragma unroll
+    for (int i = 0; i < 3; ++i) red[(tid >> 6) * NV + base + i] = v[i];
+  __syncthreads();
+  double sum = 0.0;
+  if (tid < NV)
+    for (int i = 0; i < NT / 64; ++i) sum += red[i * NV + tid];
+  return sum;
+}
+
 // Sum `cnt` doubles of every thread of the workgroup; thread i < cnt gets the
 // total of value i.  red: LDS of (NT / 64) * cnt doubles.
 template <int NT, int CNT>

@@ -47,44 +47,19 @@ __global__ __launch_bounds__(kThreads) void k_spread_rows(CallArgs a, Plan p, Wo
 }
 
 // Direct sums A, B, B2 at four of the frequencies near f = 0 (group g: k_lo +
-// 4 g ..) over slice r of nr of the points, into row r of lowfix.  Fixed order:
-// the 24 sums are shared out over the lanes of each wave by exchanging halves,
-// then added over the waves.
+// 4 g ..) over slice r of nr of the points, into row r of lowfix, in a fixed
+// order.
 __device__ __forceinline__ void low_slice(const CallArgs& a, const DevStats& st, int g, int r,
                                           int nr, double* lowfix, double* red) {
   constexpr int NV = 24;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x;
   const int ng = st.nlow - 4 * g < 4 ? st.nlow - 4 * g : 4;
   if (ng <= 0) return;
   double v[NV];
   low_accumulate<4>(a, st, st.k_lo + 4 * g, ng, (int64_t)r * kThreads + tid,
                     (int64_t)nr * kThreads, v);
-  int base = 0;
-#pragma unroll
-  for (int s = 0; s < 3; ++s) {
-    const int off = 32 >> s, half = NV >> (s + 1);
-    const bool up = lane & off;
-    if (up) base += half;
-#pragma unroll
-    for (int i = 0; i < half; ++i) {
-      const double keep = up ? v[i + half] : v[i];
-      const double give = up ? v[i] : v[i + half];
-      v[i] = keep + __shfl_xor(give, off, 64);
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int off = 4; off > 0; off >>= 1) v[i] += __shfl_xor(v[i], off, 64);
-  if ((lane & 7) == 0)
-#pragma unroll
-    for (int i = 0; i < 3; ++i) red[(tid >> 6) * NV + base + i] = v[i];
-  __syncthreads();
-  if (tid < NV) {
-    double sum = 0.0;
-    for (int i = 0; i < kThreads / 64; ++i) sum += red[i * NV + tid];
-    lowfix[r * 6 * kLowMax + NV * g + tid] = sum;
-  }
+  const double sum = block_share_sum<kThreads, NV>(v, red);
+  if (tid < NV) lowfix[r * 6 * kLowMax + NV * g + tid] = sum;
 }
 
 // A periodogram's spreads and direct sums in one launch: the first 4 lowrows
