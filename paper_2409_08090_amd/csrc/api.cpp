@@ -1352,7 +1352,7 @@ int mils_periodogram_shared_t(mils_context* ctx, const double* t, const double* 
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const size_t bsum = up(sizeof(double) * 2 * (size_t)p->nf);
   const size_t nst = (size_t)nseries + 1;
-  const size_t low = up(sizeof(double) * 6 * kLowMax * kLowParts);
+  const size_t low = up(sizeof(double) * 6 * kLowMax * kLowRows);
   const size_t extra = 2 * bsum + 3 * low + up(sizeof(DevStats) * nst) + 256;
   rc = get_plan(ctx, p->nf, p->eps, p->precision, 3, &pe, true, false, 0, 0, false,
                 split_fits(ctx, p->nf, p->eps, p->precision, 3, false, nd, extra));

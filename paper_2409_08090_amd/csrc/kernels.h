@@ -84,7 +84,7 @@ void big_lds(const void* kern, size_t bytes);
 // (the next, or NULL) if given, else the power of a (three grids), or the
 // powers of the a.nser series that share their weights.
 void enqueue_split_first(const Plan& p, const Work& w, int g0, int ng, int grid_2f,
-                         hipStream_t s);
+                         const LowRows& lr, hipStream_t s);
 void enqueue_split_last(const CallArgs& a, const Plan& p, const Work& w, int g0, int ng,
                         int lowrows, double* s0, double* s1, hipStream_t s);
 
@@ -93,7 +93,12 @@ void enqueue_split_last(const CallArgs& a, const Plan& p, const Work& w, int g0,
 void enqueue_spread_pg(const CallArgs& a, const Plan& p, const Work& w, int lowrows, bool f,
                        bool f2, hipStream_t s);
 
-// Statistics of the call into w.stats.
+// In one launch: the A spreads of the a.nser series into grids 0 .. of w, and
+// lowrows rows of each one's direct sums.
+void enqueue_spread_series(const CallArgs& a, const Plan& p, const Work& w, int lowrows,
+                           hipStream_t s);
+
+// Statistics of the call into w.stats (a.nser > 0: of each series).
 void enqueue_stats(const CallArgs& a, const Work& w, hipStream_t s);
 
 // Direct sums at every frequency, term by term, FP64 (direct.hip; statistics

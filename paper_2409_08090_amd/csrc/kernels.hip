@@ -77,7 +77,9 @@ __device__ __forceinline__ StatsPart stats_block_combine(StatsPart x) {
 __global__ __launch_bounds__(kThreads) void k_stats(CallArgs a, Work w) {
   const int tid = threadIdx.x;
   StatsPart x = {{0.0, 0.0, 0.0}, INFINITY, -INFINITY, 0, 0};
-  const double* yv = a.periodogram ? a.y : a.h;
+  const int ser = blockIdx.y;  // series of a group
+  const double* yv = a.nser ? (ser == 0 ? a.sy[0] : ser == 1 ? a.sy[1] : a.sy[2])
+                            : a.periodogram ? a.y : a.h;
   for (int64_t j = (int64_t)blockIdx.x * kThreads + tid; j < a.nd; j += (int64_t)gridDim.x * kThreads) {
     double t = a.t[j];
     double y = yv ? yv[j] : 0.0;
@@ -95,7 +97,7 @@ __global__ __launch_bounds__(kThreads) void k_stats(CallArgs a, Work w) {
   }
   const StatsPart r = stats_block_combine(x);
   if (tid == 0) {
-    double* p = w.partials + 8 * blockIdx.x;
+    double* p = w.partials + 8 * (blockIdx.x + gridDim.x * ser);
     p[0] = r.m.W;
     p[1] = r.m.mu;
     p[2] = r.m.M2;
@@ -110,7 +112,7 @@ __global__ __launch_bounds__(kThreads) void k_stats_final(CallArgs a, Work w, in
   const int tid = threadIdx.x;
   StatsPart x = {{0.0, 0.0, 0.0}, INFINITY, -INFINITY, 0, 0};
   for (int b = tid; b < nparts; b += kThreads) {
-    const double* p = w.partials + 8 * b;
+    const double* p = w.partials + 8 * (b + nparts * (int)blockIdx.x);
     moments_merge(x.m, p[0], p[1], p[2]);
     x.lo = fmin(x.lo, p[3]);
     x.hi = fmax(x.hi, p[4]);
@@ -119,7 +121,8 @@ __global__ __launch_bounds__(kThreads) void k_stats_final(CallArgs a, Work w, in
   }
   const StatsPart r = stats_block_combine(x);
   if (tid == 0) {
-    DevStats* st = w.stats;
+    const int ser = blockIdx.x;
+    DevStats* st = !a.nser ? w.stats : ser == 0 ? a.sst[0] : ser == 1 ? a.sst[1] : a.sst[2];
     st->W = r.m.W;
     st->mu = r.m.mu;
     st->M2 = r.m.M2;
@@ -137,7 +140,7 @@ __global__ __launch_bounds__(kThreads) void k_stats_final(CallArgs a, Work w, in
     st->YY = YY;
     int status = 0;
     if (r.bad) status = -1;
-    else if (a.periodogram && a.y && !(YY > 0.0)) status = -2;
+    else if (a.periodogram && (a.y || a.nser) && !(YY > 0.0)) status = -2;
     st->status = status;
     st->nill = 0;
     st->nlow = 0;
@@ -220,10 +223,10 @@ __global__ __launch_bounds__(kThreads) void k_det_gather(CallArgs a, Plan p, Wor
 template <typename Real, int EMAX, int NT, bool TW2>
 __global__ __launch_bounds__(NT) void k_fft_pass(PassBufs<Real> b, FftPass ps,
                                                  const typename cplx<Real>::T* tw,
-                                                 const DevStats* st) {
+                                                 const DevStats* st, LowRows lr) {
   extern __shared__ __align__(16) unsigned char smem[];
-  if (st->status != 0) return;
-  const int64_t blk = xcd_remap(blockIdx.x, (int64_t)gridDim.x);
+  if (st->status != 0 || low_rows_block(lr)) return;
+  const int64_t blk = xcd_remap(blockIdx.x, (int64_t)gridDim.x - lr.n);
   const int g = blockIdx.y;
   fft_pass_block<Real, EMAX, NT, TW2>(blk, b.in[g], b.out[g], b.rowflag[g], ps, tw, smem);
 }
@@ -249,14 +252,14 @@ __global__ __launch_bounds__(NT) void k_fft_last(PassBufs<Real> b, FftPass ps, P
 template <typename Real, int G, int EMAX, int NT, bool TW2>
 __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_fft_last_ser(
     PassBufs<Real> b, FftPass ps, Plan pl, CallArgs a, const typename cplx<Real>::T* tw,
-    const double* inv_phihat, const DevStats* stp, const double* lowfix) {
+    const double* inv_phihat, const DevStats* stp, int lowrows) {
   extern __shared__ __align__(16) unsigned char smem[];
   if (stp->status != 0) return;
   const int64_t nblk = (ps.P + ps.C - 1) / ps.C;
   const int64_t blk = xcd_remap(blockIdx.x, nblk);
   const DevStats st = *stp;
   fft_last_block<Real, G, EMAX, NT, TW2, true>(blk, b, ps, pl.n, pl.nf, pl.K, a, tw, inv_phihat,
-                                               st, smem, nullptr, kLowParts);
+                                               st, smem, nullptr, lowrows);
 }
 
 // Direct FP64 sums A, B, B2 at the (at most kLowMax) frequencies nearest
@@ -385,17 +388,17 @@ __global__ __launch_bounds__(kThreads) void k_phihat2(double* iphi2, const doubl
 template <typename Real, int L0, int C, bool HALVES>
 __global__ __launch_bounds__(C * L0 / 16, 4) void k_fft2_first(Fft2Bufs<Real> b, FftPass ps,
                                                              const typename cplx<Real>::T* tw,
-                                                             const DevStats* st) {
+                                                             const DevStats* st, LowRows lr) {
   using T2 = typename cplx<Real>::T;
   using Lds = typename std::conditional<HALVES, Real, T2>::type;
   extern __shared__ __align__(16) unsigned char smem[];
-  if (st->status != 0) return;
+  if (st->status != 0 || low_rows_block(lr)) return;
   constexpr int TL = L0 / 16, NT = C * TL, LP = fft2::line_pitch_c(L0, C);
   static_assert(NT <= 1024 && (C & (C - 1)) == 0, "first-pass workgroup shape");
   const int tid = threadIdx.x;
   const int c = tid & (C - 1), t = tid / C;
   const int g = blockIdx.y;
-  const int64_t sb = xcd_remap(blockIdx.x, (int64_t)gridDim.x);
+  const int64_t sb = xcd_remap(blockIdx.x, (int64_t)gridDim.x - lr.n);
   const int64_t L1 = ps.S;
   const int64_t s = sb * C + c;
   Lds* ex = reinterpret_cast<Lds*>(smem);
@@ -698,10 +701,12 @@ hipError_t launch_phihat(double* inv_phihat, int64_t K, double w, double n, cons
   return hipGetLastError();
 }
 
-// Statistics of the call (k_stats + k_stats_final into w.stats).
+// Statistics of the call (k_stats + k_stats_final into w.stats), or of each
+// series of a group.
 void enqueue_stats(const CallArgs& a, const Work& w, hipStream_t s) {
-  hipLaunchKernelGGL(k_stats, dim3(kStatsBlocks), dim3(kThreads), 0, s, a, w);
-  hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(kThreads), 0, s, a, w, kStatsBlocks);
+  const int m = a.nser ? a.nser : 1, nb = kStatsBlocks / m;
+  hipLaunchKernelGGL(k_stats, dim3(nb, m), dim3(kThreads), 0, s, a, w);
+  hipLaunchKernelGGL(k_stats_final, dim3(m), dim3(kThreads), 0, s, a, w, nb);
 }
 
 // Reproducible binning (see k_det_keys).
@@ -727,7 +732,7 @@ static void enqueue_lowfreq(const CallArgs& a, const Work& w, hipStream_t s) {
 // One first/middle FFT pass over ng grids of b.
 template <typename Real>
 static void enqueue_pass(const FftPass& ps, const PassBufs<Real>& b, int ng, const Work& w,
-                         hipStream_t st) {
+                         const LowRows& lr, hipStream_t st) {
   using T2 = typename cplx<Real>::T;
   constexpr bool f64 = sizeof(Real) == 8;
   constexpr int EMID = f64 ? kEmid64 : kEmid32;
@@ -739,11 +744,12 @@ static void enqueue_pass(const FftPass& ps, const PassBufs<Real>& b, int ng, con
   if (ps.big) {
     auto kern = k_fft_pass<Real, EBIG, kThreadsBig, true>;
     big_lds(reinterpret_cast<const void*>(kern), lds);
-    hipLaunchKernelGGL(kern, dim3((unsigned)nblk, ng), dim3(kThreadsBig), lds, st, b, ps, tw,
-                       w.stats);
+    hipLaunchKernelGGL(kern, dim3((unsigned)nblk + lr.n, ng), dim3(kThreadsBig), lds, st, b, ps,
+                       tw, w.stats, lr);
   } else {
-    hipLaunchKernelGGL((k_fft_pass<Real, EMID, kThreads, false>), dim3((unsigned)nblk, ng),
-                       dim3(kThreads), lds, st, b, ps, tw, w.stats);
+    hipLaunchKernelGGL((k_fft_pass<Real, EMID, kThreads, false>),
+                       dim3((unsigned)nblk + lr.n, ng), dim3(kThreads), lds, st, b, ps, tw,
+                       w.stats, lr);
   }
 }
 
@@ -771,16 +777,16 @@ static void enqueue_last(const CallArgs& a, const Plan& p, const PassBufs<Real>&
       auto kern = k_fft_last_ser<Real, 1, EBIG, kThreadsBig, true>;
       big_lds(reinterpret_cast<const void*>(kern), lds);
       hipLaunchKernelGGL(kern, grid, dim3(kThreadsBig), lds, s, b, ps, p, a, tw, ip, w.stats,
-                         w.lowfix);
+                         lowrows);
     } else if (G == 3) {
       hipLaunchKernelGGL((k_fft_last_ser<Real, 3, ELAST, NTL, false>), grid, dim3(NTL), lds, s,
-                         b, ps, p, a, tw, ip, w.stats, w.lowfix);
+                         b, ps, p, a, tw, ip, w.stats, lowrows);
     } else if (G == 2) {
       hipLaunchKernelGGL((k_fft_last_ser<Real, 2, 2 * (ELAST / 3), NTL, false>), grid, dim3(NTL),
-                         lds, s, b, ps, p, a, tw, ip, w.stats, w.lowfix);
+                         lds, s, b, ps, p, a, tw, ip, w.stats, lowrows);
     } else {
       hipLaunchKernelGGL((k_fft_last_ser<Real, 1, ELAST / 3, NTL, false>), grid, dim3(NTL), lds,
-                         s, b, ps, p, a, tw, ip, w.stats, w.lowfix);
+                         s, b, ps, p, a, tw, ip, w.stats, lowrows);
     }
   } else if (ps.big) {
     auto kern = G == 3 ? k_fft_last<Real, 3, EBIG, kThreadsBig, true>
@@ -808,7 +814,7 @@ static void enqueue_last(const CallArgs& a, const Plan& p, const PassBufs<Real>&
 // set.  in[i] receives where grid g0+i ends up.
 template <typename Real>
 static void enqueue_passes(const Plan& p, const Work& w, int g0, int ng, int grid_2f,
-                           hipStream_t s, typename cplx<Real>::T** in) {
+                           const LowRows& lr, hipStream_t s, typename cplx<Real>::T** in) {
   using T2 = typename cplx<Real>::T;
   T2* cur[3];
   T2* alt[3];
@@ -824,7 +830,7 @@ static void enqueue_passes(const Plan& p, const Work& w, int g0, int ng, int gri
       b.out[i] = ip == 0 ? cur[j] : alt[j];
       b.rowflag[i] = ip == 0 ? (g0 + j == grid_2f ? w.rowflag_2f : w.rowflag_f) : nullptr;
     }
-    enqueue_pass<Real>(p.pass[ip], b, ng, w, s);
+    enqueue_pass<Real>(p.pass[ip], b, ng, w, ip == 0 ? lr : LowRows{}, s);
     if (ip > 0)
       for (int i = 0; i < ng; ++i) {
         T2* tmp = cur[i];
@@ -838,26 +844,26 @@ static void enqueue_passes(const Plan& p, const Work& w, int g0, int ng, int gri
 // First pass of the two-pass FFT over ng grids (b.grid[0 .. ng-1]).
 template <typename Real, int L0, int C>
 static void enqueue_fft2_first_l(const Plan& p, const Fft2Bufs<Real>& b, int ng, const Work& w,
-                                 hipStream_t st) {
+                                 const LowRows& lr, hipStream_t st) {
   using T2 = typename cplx<Real>::T;
   constexpr bool H = sizeof(Real) == 8;
   const FftPass& ps = p.pass[0];
   auto kern = k_fft2_first<Real, L0, C, H>;
   const size_t lds = f2_first_lds<Real>(L0, C, H);
   big_lds(reinterpret_cast<const void*>(kern), lds);
-  hipLaunchKernelGGL(kern, dim3((unsigned)(ps.S / C), ng), dim3(C * L0 / 16), lds, st, b, ps,
-                     reinterpret_cast<const T2*>(w.tw), w.stats);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(ps.S / C) + lr.n, ng), dim3(C * L0 / 16), lds, st, b,
+                     ps, reinterpret_cast<const T2*>(w.tw), w.stats, lr);
 }
 
 template <typename Real>
 static void enqueue_fft2_first(const Plan& p, const Fft2Bufs<Real>& b, int ng, const Work& w,
-                               hipStream_t st) {
+                               const LowRows& lr, hipStream_t st) {
   const int L0 = p.pass[0].L, C = p.pass[0].C;
-  if (L0 == 2048 && C == 8) enqueue_fft2_first_l<Real, 2048, 8>(p, b, ng, w, st);
-  else if (L0 == 2048) enqueue_fft2_first_l<Real, 2048, 4>(p, b, ng, w, st);
-  else if (L0 == 4096 && C == 4) enqueue_fft2_first_l<Real, 4096, 4>(p, b, ng, w, st);
-  else if (L0 == 4096) enqueue_fft2_first_l<Real, 4096, 2>(p, b, ng, w, st);
-  else enqueue_fft2_first_l<Real, 8192, 2>(p, b, ng, w, st);
+  if (L0 == 2048 && C == 8) enqueue_fft2_first_l<Real, 2048, 8>(p, b, ng, w, lr, st);
+  else if (L0 == 2048) enqueue_fft2_first_l<Real, 2048, 4>(p, b, ng, w, lr, st);
+  else if (L0 == 4096 && C == 4) enqueue_fft2_first_l<Real, 4096, 4>(p, b, ng, w, lr, st);
+  else if (L0 == 4096) enqueue_fft2_first_l<Real, 4096, 2>(p, b, ng, w, lr, st);
+  else enqueue_fft2_first_l<Real, 8192, 2>(p, b, ng, w, lr, st);
 }
 
 template <typename Real, int L1, int G>
@@ -988,6 +994,14 @@ static hipError_t launch_path_t(const CallArgs& a, const Plan& p, const Work& w,
       mark(kStageLow, 0, s2);
     }
   }
+  // rows for the first pass to add up (none: a single pass, which reads them)
+  LowRows lr{};
+  if (pg && low_fused && p.npass >= 2 && lowrows > 1) {
+    lr.low[0] = w.lowfix;
+    lr.n = 1;
+    lr.rows = lowrows;
+    lowrows = 1;
+  }
   auto join = [&]() -> hipError_t {
     if (!fork) return hipSuccess;
     hipError_t e = hipEventRecord(aux->join, s2);
@@ -995,7 +1009,7 @@ static hipError_t launch_path_t(const CallArgs& a, const Plan& p, const Work& w,
     return e;
   };
   if (split_passes(p)) {
-    enqueue_split_first(p, w, 0, G, 2, s);
+    enqueue_split_first(p, w, 0, G, 2, lr, s);
     hipError_t e = join();
     if (e != hipSuccess) return e;
     enqueue_split_last(a, p, w, 0, G, lowrows, pg ? nullptr : a.sums, nullptr, s);
@@ -1010,7 +1024,7 @@ static hipError_t launch_path_t(const CallArgs& a, const Plan& p, const Work& w,
       b.rowflag[g] = g == 2 ? w.rowflag_2f : w.rowflag_f;
     }
     mark(kStagePass0, 1, s);
-    enqueue_fft2_first<Real>(p, b, G, w, s);
+    enqueue_fft2_first<Real>(p, b, G, w, lr, s);
     mark(kStagePass0, 0, s);
     hipError_t e = join();
     if (e != hipSuccess) return e;
@@ -1029,7 +1043,7 @@ static hipError_t launch_path_t(const CallArgs& a, const Plan& p, const Work& w,
     cur[g] = reinterpret_cast<T2*>(w.grid[g]);
     alt[g] = reinterpret_cast<T2*>(w.grid2[g]);
   }
-  auto pass = [&](int ip, int g0, int ng) {
+  auto pass = [&](int ip, int g0, int ng, const LowRows& rows) {
     PassBufs<Real> b;
     for (int i = 0; i < 3; ++i) {
       const int g = g0 + i < 3 ? g0 + i : 2;
@@ -1037,23 +1051,23 @@ static hipError_t launch_path_t(const CallArgs& a, const Plan& p, const Work& w,
       b.out[i] = (ip == 0) ? cur[g] : alt[g];
       b.rowflag[i] = (ip == 0) ? (g == 2 ? w.rowflag_2f : w.rowflag_f) : nullptr;
     }
-    enqueue_pass<Real>(p.pass[ip], b, ng, w, s);
+    enqueue_pass<Real>(p.pass[ip], b, ng, w, rows, s);
   };
   if (p.npass >= 2) {
     // (timed as two launches, one per geometry)
     const int first = hook && pg ? 2 : G;
     mark(kStagePass0, 1, s);
-    pass(0, 0, first);
+    pass(0, 0, first, lr);
     mark(kStagePass0, 0, s);
     if (first < G) {
       mark(kStagePass0, 1, s);
-      pass(0, first, G - first);
+      pass(0, first, G - first, LowRows{});
       mark(kStagePass0, 0, s);
     }
   }
   for (int ip = 1; ip + 1 < p.npass; ++ip) {
     mark(kStagePass0 + ip, 1, s);
-    pass(ip, 0, G);
+    pass(ip, 0, G, LowRows{});
     mark(kStagePass0 + ip, 0, s);
     for (int g = 0; g < 3; ++g) {
       T2* tmp = cur[g];
@@ -1104,12 +1118,12 @@ static hipError_t launch_weight_sums_t(const CallArgs& aw, const Plan& p, const 
   enqueue_spread(aw, p, w, 1, 1, 1, s);
   enqueue_spread(aw, p, w, 2, 1, 2, s);
   if (split_passes(p)) {
-    enqueue_split_first(p, w, 1, 2, 2, s);
+    enqueue_split_first(p, w, 1, 2, 2, LowRows{}, s);
     enqueue_split_last(aw, p, w, 1, 2, kLowParts, bsum_b, bsum_b2, s);
     return hipGetLastError();
   }
   T2* in[2];
-  enqueue_passes<Real>(p, w, 1, 2, 2, s, in);
+  enqueue_passes<Real>(p, w, 1, 2, 2, LowRows{}, s, in);
   CallArgs as = aw;
   as.periodogram = 0;  // the last pass writes the deconvolved sums
   for (int i = 0; i < 2; ++i) {
@@ -1132,41 +1146,54 @@ static hipError_t launch_series_group_t(const CallArgs& a, const Plan& p, const 
   CallArgs al = a;
   al.nser = sg.m;
   for (int g = 0; g < sg.m; ++g) {
-    // statistics, binning (only when the points must be sorted: the sorted
-    // copy of y is the series' own; otherwise the weights-only call's bins
-    // hold), direct sums near f = 0, and the A spread into grid g
-    CallArgs ag = a;
-    ag.y = sg.y[g];
-    Work wg = w;
-    wg.stats = sg.stats[g];
-    wg.lowfix = sg.lowfix[g];
-    if (sg.need_sort) {
-      enqueue_pro_stats(ag, p, wg, s);
-      enqueue_bins(ag, p, wg, s);
-      enqueue_rows(ag, p, wg, 0, true, s);
-    } else {
-      enqueue_stats(ag, wg, s);
-    }
-    enqueue_lowfreq(ag, wg, s);
-    enqueue_spread(ag, p, wg, 1, 1, g, s);
+    al.sy[g] = sg.y[g];
     al.spow[g] = sg.power[g];
     al.sst[g] = sg.stats[g];
     al.slow[g] = sg.lowfix[g];
   }
+  int lowrows = kLowParts;
+  LowRows lr{};
+  if (!sg.need_sort) {
+    // the weights-only call's bins hold: statistics, then spreads and direct
+    // sums of the whole group
+    lowrows = low_fused_rows(a.nd);
+    enqueue_stats(al, w, s);
+    enqueue_spread_series(al, p, w, lowrows, s);
+    if (p.npass >= 2 && lowrows > 1) {
+      for (int g = 0; g < sg.m; ++g) lr.low[g] = sg.lowfix[g];
+      lr.n = sg.m;
+      lr.rows = lowrows;
+      lowrows = 1;
+    }
+  } else {
+    // the sorted copy of y is the series' own: each series by itself
+    for (int g = 0; g < sg.m; ++g) {
+      CallArgs ag = a;
+      ag.y = sg.y[g];
+      Work wg = w;
+      wg.stats = sg.stats[g];
+      wg.lowfix = sg.lowfix[g];
+      enqueue_pro_stats(ag, p, wg, s);
+      enqueue_bins(ag, p, wg, s);
+      enqueue_rows(ag, p, wg, 0, true, s);
+      enqueue_lowfreq(ag, wg, s);
+      enqueue_spread(ag, p, wg, 1, 1, g, s);
+    }
+  }
   if (split_passes(p)) {
-    enqueue_split_first(p, w, 0, sg.m, -1, s);
-    enqueue_split_last(al, p, w, 0, sg.m, kLowParts, nullptr, nullptr, s);
+    enqueue_split_first(p, w, 0, sg.m, -1, lr, s);
+    enqueue_split_last(al, p, w, 0, sg.m, lowrows, nullptr, nullptr, s);
     return hipGetLastError();
   }
   T2* in[3];
-  enqueue_passes<Real>(p, w, 0, sg.m, -1, s, in);
+  enqueue_passes<Real>(p, w, 0, sg.m, -1, lr, s, in);
   PassBufs<Real> b;
   for (int g = 0; g < 3; ++g) {
     b.in[g] = in[g < sg.m ? g : sg.m - 1];
     b.out[g] = nullptr;
     b.rowflag[g] = nullptr;
   }
-  enqueue_last<Real>(al, p, b, sg.m, w, kLowParts, s);
+  enqueue_last<Real>(al, p, b, sg.m, w, lowrows, s);
   return hipGetLastError();
 }
 

@@ -120,12 +120,13 @@ struct CallArgs {
   // call's statistics (its sort decision holds for the series, and its bin
   // starts are still in the workspace unless the points must be sorted).
   const DevStats* wstats;
-  // Last pass over nser (1..3) such series at once, grid g holding the A
-  // sums of series g: its power, statistics and direct sums near f = 0.
+  // nser (1..3) such series at once, grid g holding the A sums of series g:
+  // its values, power, statistics and direct sums near f = 0.
   int nser;
+  const double* sy[3];
   double* spow[3];
-  const DevStats* sst[3];
-  const double* slow[3];
+  DevStats* sst[3];
+  double* slow[3];
 };
 
 // Device workspace of one call, carved from one allocation.
@@ -207,10 +208,19 @@ constexpr int kLowParts = 8;  // rows of lowfix (partial sums; the last pass add
 // launch, one row per 2048 points up to kLowRows (a quarter of the frequencies
 // each: 48 registers of sums instead of 192, at twice the phase work).
 constexpr int64_t kLowFusedNd = 200000;
-constexpr int kLowRows = 32;
+// (Series that share their times always do: their spreads are one launch.)
+// The first FFT pass adds the rows up in a workgroup of its own (a last pass
+// that reads 32 rows one after another at its few such outputs ends 20 us
+// later than the others).
+struct LowRows {
+  double* low[3];  // each: rows to add up into the first
+  int n;           // of them
+  int rows;
+};
+constexpr int kLowRows = 64;
 inline int low_fused_rows(int64_t nd) {
-  const int64_t r = (nd + 2047) / 2048;
-  return (int)(r < kLowRows ? r : kLowRows);
+  const int64_t r = (nd + 2047) / 2048, most = nd <= kLowFusedNd ? 32 : kLowRows;
+  return (int)(r < most ? r : most);
 }
 
 // LDS pitch of the last FFT pass: its rows are interleaved element by element

@@ -303,10 +303,15 @@ __device__ __forceinline__ void add_wave_points(double* acc, int tcap, int T, in
 // geometries of the 1e6-point curve: 47 us of it).  Against records in LDS, a
 // barrier per 256 points and arguments in scratch: both spreads of that curve,
 // side by side, 115 -> 73 us (FP32 100 -> 55), 1e5 points 27 -> 17 us.
-template <typename Real, int GEO, int NG, int NT, int SETS>
+//
+// SER: the A grids of NG series that share their times and weights (a.sy,
+// a.sst; st the weights-only call's statistics): one evaluation of the kernel
+// and the phase of a point for all of them.
+template <typename Real, int GEO, int NG, int NT, int SETS, bool SER = false>
 __device__ __forceinline__ void spread_tile(int tile, int Tt, int tcap, const CallArgs& a,
                                             const Plan& p, const Work& w, const DevStats& st,
-                                            void* out0, void* out1, double* acc) {
+                                            void* out0, void* out1, double* acc,
+                                            void* out2 = nullptr) {
   using T2 = typename cplx<Real>::T;
   const int tid = threadIdx.x;
   const int n = (int)p.n, nd = (int)a.nd;
@@ -337,6 +342,12 @@ __device__ __forceinline__ void spread_tile(int tile, int Tt, int tcap, const Ca
   __syncthreads();
   const PointSource src = point_source(a, w, st);
   const double invW = 1.0 / st.W;
+  double ysub[NG] = {};
+  if constexpr (SER) {
+    ysub[0] = ((ConstPtr<double>)&a.sst[0]->ysub)[0];
+    if constexpr (NG > 1) ysub[1] = ((ConstPtr<double>)&a.sst[1]->ysub)[0];
+    if constexpr (NG > 2) ysub[2] = ((ConstPtr<double>)&a.sst[2]->ysub)[0];
+  }
   // a kernel support can meet the tile at most once unless the tile spans
   // nearly the whole periodic grid
   const bool wrap_free = T <= n - p.w;
@@ -352,11 +363,30 @@ __device__ __forceinline__ void spread_tile(int tile, int Tt, int tcap, const Ca
       if (j < jend) {
         // (all three loads at once: few points of the ranges miss the tile)
         const double t = src.t[j];
-        double y, dv;
-        point_values<GEO>(src, a, j, y, dv);
+        double y[SER ? NG : 1], dv;
+        if constexpr (SER) {
+          dv = src.dy ? src.dy[j] : 1.0;
+          y[0] = a.sy[0][j];
+          if constexpr (NG > 1) y[1] = a.sy[1][j];
+          if constexpr (NG > 2) y[2] = a.sy[2][j];
+        } else {
+          point_values<GEO>(src, a, j, y[0], dv);
+        }
         point_cell<Real, GEO>(t, st, a, p, a0, lb, u);
         if (wrap_free && (lb >= T || lb + p.w <= 0)) lb = kSpreadNone;
-        point_strengths<Real, GEO, NG>(t, y, dv, st, a, invW, hs);
+        if constexpr (SER) {
+          double pc, ps;
+          prephase(t, st.tau, a.fch, a.fcl, pc, ps);
+          const double wh = 1.0 / (dv * dv) * invW;
+#pragma unroll
+          for (int g = 0; g < NG; ++g) {
+            const double yt = y[g] - ysub[g];
+            hs[2 * g] = (Real)(wh * yt * pc);
+            hs[2 * g + 1] = (Real)(wh * yt * ps);
+          }
+        } else {
+          point_strengths<Real, GEO, NG>(t, y[0], dv, st, a, invW, hs);
+        }
       }
       add_wave_points<Real, NG, SETS, 0>(acc, tcap, T, n, p.w, lk, jend - j0, lb, u, hs);
     }
@@ -364,7 +394,7 @@ __device__ __forceinline__ void spread_tile(int tile, int Tt, int tcap, const Ca
   __syncthreads();
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
-    T2* out = reinterpret_cast<T2*>(g == 0 ? out0 : out1) + a0;
+    T2* out = reinterpret_cast<T2*>(g == 0 ? out0 : g == 1 ? out1 : out2) + a0;
     for (int x = tid; x < T; x += NT) {
       T2 v;
       v.x = (Real)acc[(2 * g) * tcap + x];
@@ -776,6 +806,22 @@ __device__ __forceinline__ void low_band(const DevStats& st, double f0, double d
   }
   k_lo = (int64_t)lo;
   nlow = (int)fmin(kb - lo + 1.0, (double)kLowMax);
+}
+
+// Extra workgroups of a first pass (the last lr.n of x, y = 0): the rows of
+// direct sums into the first.  True for them.
+__device__ __forceinline__ bool low_rows_block(const LowRows& lr) {
+  const int i = (int)blockIdx.x - ((int)gridDim.x - lr.n);
+  if (i < 0) return false;
+  const int x = threadIdx.x;
+  if (blockIdx.y == 0 && x < 6 * kLowMax) {
+    double* low = i == 0 ? lr.low[0] : i == 1 ? lr.low[1] : lr.low[2];
+    double sum = 0.0;
+#pragma unroll 8
+    for (int r = 0; r < lr.rows; ++r) sum += low[r * 6 * kLowMax + x];
+    low[x] = sum;
+  }
+  return true;
 }
 
 // This thread's contributions to A, B, B2 at frequencies k_lo + g0 + q,

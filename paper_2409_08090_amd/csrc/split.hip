@@ -44,9 +44,10 @@ struct Roots {
 // blockIdx.y: LA / 16 threads a column, the columns fastest.
 template <int LA, int NT>
 __global__ __launch_bounds__(NT, 4) void k_split_first(Fft2Bufs<double> b, FftPass ps, int R,
-                                                       const double2* tw, const DevStats* st) {
+                                                       const double2* tw, const DevStats* st,
+                                                       LowRows lr) {
   extern __shared__ __align__(16) unsigned char smem[];
-  if (((ConstPtr<int>)&st->status)[0] != 0) return;
+  if (((ConstPtr<int>)&st->status)[0] != 0 || low_rows_block(lr)) return;
   constexpr int TL = LA / 16, C = NT / TL, LP = fft2::line_pitch_c(LA, C);
   constexpr int WR = 64 / C;  // rows that one load of a wave covers
   static_assert(C >= 4 && C <= 16 && WR >= 4, "rows of a wave in whole words of flags");
@@ -54,7 +55,7 @@ __global__ __launch_bounds__(NT, 4) void k_split_first(Fft2Bufs<double> b, FftPa
   const int c = tid & (C - 1), t = tid / C;
   const int tw0 = __builtin_amdgcn_readfirstlane(t);  // a multiple of WR
   const int g = blockIdx.y;
-  const int blk = (int)xcd_remap(blockIdx.x, (int64_t)gridDim.x);
+  const int blk = (int)xcd_remap(blockIdx.x, (int64_t)gridDim.x - lr.n);
   const int rho = blk % R, s = (blk / R) * C + c;
   const int L1 = (int)ps.S;
   double* ex = reinterpret_cast<double*>(smem);
@@ -303,14 +304,15 @@ Fft2Bufs<double> bufs(const Work& w, int g0, int ng, int grid_2f) {
 
 // (a workgroup's LDS above 64 KB must be allowed for its kernel)
 template <int LA, int NT>
-void first(const Plan& p, const Fft2Bufs<double>& b, int ng, const Work& w, hipStream_t s) {
+void first(const Plan& p, const Fft2Bufs<double>& b, int ng, const Work& w, const LowRows& lr,
+           hipStream_t s) {
   constexpr int C = NT / (LA / 16);
   constexpr size_t lds = split_lds<LA, NT>();
   const FftPass& ps = p.pass[0];
   auto kern = k_split_first<LA, NT>;
   big_lds(reinterpret_cast<const void*>(kern), lds);
-  hipLaunchKernelGGL(kern, dim3((unsigned)(ps.S / C * p.split), ng), dim3(NT), lds, s, b, ps,
-                     p.split, reinterpret_cast<const double2*>(w.tw), w.stats);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(ps.S / C * p.split) + lr.n, ng), dim3(NT), lds, s, b,
+                     ps, p.split, reinterpret_cast<const double2*>(w.tw), w.stats, lr);
 }
 
 template <int L1, int NT, int NG, int MODE>
@@ -337,14 +339,14 @@ void last_l(const CallArgs& a, const Plan& p, const Fft2Bufs<double>& b, int ng,
 }  // namespace
 
 void enqueue_split_first(const Plan& p, const Work& w, int g0, int ng, int grid_2f,
-                         hipStream_t s) {
+                         const LowRows& lr, hipStream_t s) {
   const Fft2Bufs<double> b = bufs(w, g0, ng, grid_2f);
   // 8 columns (128-byte pieces) a workgroup: with 4, lines of 1024 took 320 us
   // instead of 297 in all at n = 6.3e6
   switch (p.la) {
-    case 256: first<256, 256>(p, b, ng, w, s); break;
-    case 512: first<512, 256>(p, b, ng, w, s); break;
-    default: first<1024, 512>(p, b, ng, w, s); break;
+    case 256: first<256, 256>(p, b, ng, w, lr, s); break;
+    case 512: first<512, 256>(p, b, ng, w, lr, s); break;
+    default: first<1024, 512>(p, b, ng, w, lr, s); break;
   }
 }
 

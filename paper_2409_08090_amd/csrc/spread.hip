@@ -86,6 +86,38 @@ __global__ __launch_bounds__(kThreads) void k_spread_pg(CallArgs a, Plan p, Work
 }
 
 // The same with fixed summation orders.
+// The A spreads of NG series that share their times and weights, with their
+// direct sums (the first 4 lowrows NG workgroups; their statistics are there).
+// One launch instead of a spread and two kernels of direct sums a series: 160
+// us -> 82 for three series of 4e5 points, statistics included.
+template <typename Real, int NG, int SETS>
+__global__ __launch_bounds__(kThreads) void k_spread_series(CallArgs a, Plan p, Work w,
+                                                            int lowrows) {
+  __shared__ double acc[2 * NG * kTileMax];
+  const DevStats st = load_stats(a.wstats);
+  if (st.status != 0) return;
+  int b = (int)blockIdx.x;
+  if (b < 4 * lowrows * NG) {
+    const int g = b / (4 * lowrows);
+    b -= g * 4 * lowrows;
+    CallArgs ag = a;
+    ag.y = g == 0 ? a.sy[0] : g == 1 ? a.sy[1] : a.sy[2];
+    const DevStats* sp = g == 0 ? a.sst[0] : g == 1 ? a.sst[1] : a.sst[2];
+    double* low = g == 0 ? a.slow[0] : g == 1 ? a.slow[1] : a.slow[2];
+    const DevStats sg = load_stats(sp);
+    if (sg.status == 0) low_slice(ag, sg, b & 3, b >> 2, lowrows, low, acc);
+    return;
+  }
+  b -= 4 * lowrows * NG;
+  const int nb = (int)gridDim.x - 4 * lowrows * NG;
+  const int tpr = (int)p.S1 / p.T;
+  const int ntile = (int)p.nrows * tpr;
+  for (int t = b; t < ntile; t += nb)
+    if (row_set(w.rowflag_f, t / tpr))
+      spread_tile<Real, 1, NG, kThreads, SETS, true>(t, p.T, kTileMax, a, p, w, st, w.grid[0],
+                                                     w.grid[1], acc, w.grid[2]);
+}
+
 template <typename Real, int GEO, int NG>
 __global__ __launch_bounds__(kThreads) void k_spread_det(CallArgs a, Plan p, Work w, void* out0,
                                                          void* out1) {
@@ -120,6 +152,18 @@ void enqueue(const CallArgs& a, const Plan& p, const Work& w, int gbase, hipStre
   else
     hipLaunchKernelGGL((k_spread_rows<Real, GEO, NG, 2>), grid, dim3(kThreads), 0, s, a, p, w,
                        out0, out1);
+}
+
+template <typename Real, int NG>
+void enqueue_series(const CallArgs& a, const Plan& p, const Work& w, int lowrows, hipStream_t s) {
+  const int64_t n = (p.S1 / p.T) * p.nrows;
+  const dim3 grid((unsigned)(4 * lowrows * NG + (n < kSpreadGrid ? n : kSpreadGrid)));
+  if (p.w <= 16)
+    hipLaunchKernelGGL((k_spread_series<Real, NG, 1>), grid, dim3(kThreads), 0, s, a, p, w,
+                       lowrows);
+  else
+    hipLaunchKernelGGL((k_spread_series<Real, NG, 2>), grid, dim3(kThreads), 0, s, a, p, w,
+                       lowrows);
 }
 
 template <typename Real>
@@ -160,6 +204,19 @@ void enqueue_spread_pg(const CallArgs& a, const Plan& p, const Work& w, int lowr
                        bool f2, hipStream_t s) {
   if (p.prec == 1) enqueue_pg<float>(a, p, w, lowrows, f, f2, s);
   else enqueue_pg<double>(a, p, w, lowrows, f, f2, s);
+}
+
+void enqueue_spread_series(const CallArgs& a, const Plan& p, const Work& w, int lowrows,
+                           hipStream_t s) {
+  if (p.prec == 1) {
+    if (a.nser == 1) enqueue_series<float, 1>(a, p, w, lowrows, s);
+    else if (a.nser == 2) enqueue_series<float, 2>(a, p, w, lowrows, s);
+    else enqueue_series<float, 3>(a, p, w, lowrows, s);
+  } else {
+    if (a.nser == 1) enqueue_series<double, 1>(a, p, w, lowrows, s);
+    else if (a.nser == 2) enqueue_series<double, 2>(a, p, w, lowrows, s);
+    else enqueue_series<double, 3>(a, p, w, lowrows, s);
+  }
 }
 
 }  // namespace mils
