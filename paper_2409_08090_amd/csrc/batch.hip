@@ -97,8 +97,11 @@ __device__ void stats_block(const CallArgs& a, DevStats* st, double* sh /* 5*NT 
     else if (!(YY > 0.0)) status = -2;
     st->status = status;
     st->nill = 0;
-    st->nlow = 0;
-    st->k_lo = 0;
+    int64_t k_lo = 0;
+    int nlow = 0;
+    if (status == 0) low_band(*st, a.f0, a.df, a.nf, k_lo, nlow);
+    st->nlow = nlow;
+    st->k_lo = k_lo;
   }
   __syncthreads();
 }
@@ -174,27 +177,19 @@ __device__ void bins_block(const CallArgs& a, const Plan& p, const Work& w, DevS
   __syncthreads();
 }
 
-// Direct FP64 sums near f = 0 for one series (see k_lowfreq): lowfix gets
-// kLowMax x 6 values, st->k_lo / st->nlow the frequencies they belong to.
+// Direct FP64 sums near f = 0 for one series (see k_lowfreq) at the
+// frequencies st->k_lo .. into lowfix (kLowMax x 6 values).
 template <int NT>
-__device__ void lowfreq_block(const CallArgs& a, DevStats* st, double* lowfix, double* red) {
-  const DevStats& s = *st;
-  int64_t k_lo;
-  int nlow;
-  low_band(s, a.f0, a.df, a.nf, k_lo, nlow);
+__device__ void lowfreq_block(const CallArgs& a, const DevStats* st, double* lowfix, double* red) {
+  const DevStats s = *st;
   double acc[6 * kLowGroup];
-  for (int g0 = 0; g0 < nlow; g0 += kLowGroup) {
-    const int ng = nlow - g0 < kLowGroup ? nlow - g0 : kLowGroup;
-    low_accumulate<kLowGroup>(a, s, k_lo + g0, ng, threadIdx.x, NT, acc);
+  for (int g0 = 0; g0 < s.nlow; g0 += kLowGroup) {
+    const int ng = s.nlow - g0 < kLowGroup ? s.nlow - g0 : kLowGroup;
+    low_accumulate<kLowGroup>(a, s, s.k_lo + g0, ng, threadIdx.x, NT, acc);
     const double sum = block_share_sum<NT, 6 * kLowGroup>(acc, red);
     if ((int)threadIdx.x < 6 * kLowGroup) lowfix[6 * g0 + threadIdx.x] = sum;
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    st->k_lo = k_lo;
-    st->nlow = nlow;
-  }
-  __syncthreads();
 }
 
 __device__ __forceinline__ CallArgs curve_args(const BatchArgs& ba, const BatchCurve& c) {
@@ -228,9 +223,10 @@ __device__ __forceinline__ void load_plan(const Plan* src, Plan* dst) {
 
 // Per-series prologue: one workgroup per series (series that run in LDS
 // return at once).  Bound by the latency of one workgroup's passes over its
-// points and of the direct sums' reduction, which a batch of fewer series than
-// CUs waits for: 72 us with eight waves and shared-out sums (64 series of 100
-// to 10000 points), 113 with four and 288 exchanges a wave, 110 with sixteen.
+// points, which a batch of fewer series than CUs waits for; the direct sums
+// near f = 0 (k_blow) run beside the spread and the FFT.  64 series of 100 to
+// 10000 points: 29 us, 72 with the direct sums in it (and 113 with four waves
+// a series and 288 exchanges a wave in their reduction).
 constexpr int kBproThreads = 512;
 __global__ __launch_bounds__(kBproThreads) void k_bpro(BatchArgs ba) {
   constexpr int NT = kBproThreads;
@@ -250,7 +246,6 @@ __global__ __launch_bounds__(kBproThreads) void k_bpro(BatchArgs ba) {
     return;
   }
   bins_block<NT>(a, sp, w, w.stats, shi);
-  lowfreq_block<NT>(a, w.stats, w.lowfix, sh);
   // row flags of both geometries, so that the spread's workgroups of empty
   // rows stop at once
   const int h = (int)ceil(sp.hw) + 1;
@@ -259,6 +254,16 @@ __global__ __launch_bounds__(kBproThreads) void k_bpro(BatchArgs ba) {
     w.rowflag_2f[r] = (unsigned char)row_active<2>(r, h, sp, w.bin_start, (int)a.nd);
   }
   if (threadIdx.x == 0) ba.status[c.index] = 0;
+}
+
+// Direct sums near f = 0 of the staged series.
+__global__ __launch_bounds__(kBproThreads) void k_blow(BatchArgs ba) {
+  __shared__ double red[kBproThreads / 64 * 6 * kLowGroup];
+  const int ci = blockIdx.x;
+  if (ba.curves[ci].small) return;
+  const Work& w = ba.works[ci];
+  if (w.stats->status != 0) return;
+  lowfreq_block<kBproThreads>(curve_args(ba, ba.curves[ci]), w.stats, w.lowfix, red);
 }
 
 // Spreading: one workgroup per tile of one series (every tile of every
@@ -494,26 +499,32 @@ hipError_t launch_t(const BatchLaunch& bl, hipStream_t s, const AuxStream* aux) 
         e = launch_chip_items(ba, bl.chip[i], bl.chip_items[i], bl.nchip_items[i], s);
     if (e != hipSuccess) return e;
   }
-  // the series that run in LDS, on the auxiliary stream beside the phases of
-  // the others (few of them leave most of the chip idle for their 65 us)
-  const bool fork = sizeof(Real) == 4 && bl.nsmall > 0 && bl.nstaged > 0 && aux;
+  // On the auxiliary stream, beside the phases of the staged series: the series
+  // that run in LDS (few of them leave most of the chip idle for their 47 us),
+  // then the staged ones' direct sums, which only the last pass needs.
+  const bool fork = bl.nstaged > 0 && aux;
+  hipStream_t s2 = fork ? aux->s : s;
+  auto follow = [&]() -> hipError_t {  // s2 waits for what s has queued
+    if (!fork) return hipSuccess;
+    hipError_t e = hipEventRecord(aux->fork, s);
+    return e == hipSuccess ? hipStreamWaitEvent(s2, aux->fork, 0) : e;
+  };
   if constexpr (sizeof(Real) == 4)
     if (bl.nsmall > 0) {
-      hipStream_t s2 = fork ? aux->s : s;
-      if (fork) {
-        hipError_t e = hipEventRecord(aux->fork, s);
-        if (e == hipSuccess) e = hipStreamWaitEvent(s2, aux->fork, 0);
-        if (e != hipSuccess) return e;
-      }
+      hipError_t e = follow();
+      if (e != hipSuccess) return e;
       hipLaunchKernelGGL(k_bsmall<Real>, dim3(bl.nsmall), dim3(NT), bl.small_lds, s2, ba,
                          bl.small_items);
-      if (fork) {
-        hipError_t e = hipEventRecord(aux->join, s2);
-        if (e != hipSuccess) return e;
-      }
     }
   if (bl.nstaged == 0) return hipGetLastError();
   hipLaunchKernelGGL(k_bpro, dim3(ba.ncurves), dim3(kBproThreads), 0, s, ba);
+  {
+    hipError_t e = follow();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_blow, dim3(ba.ncurves), dim3(kBproThreads), 0, s2, ba);
+    if (fork) e = hipEventRecord(aux->join, s2);
+    if (e != hipSuccess) return e;
+  }
   if (bl.nspread > 0)
     hipLaunchKernelGGL((bl.wmax > 16 ? k_bspread2<Real, 2> : k_bspread2<Real, 1>),
                        dim3(bl.nspread), dim3(NT), 0, s, ba, bl.spread_items);
@@ -521,13 +532,13 @@ hipError_t launch_t(const BatchLaunch& bl, hipStream_t s, const AuxStream* aux) 
     if (bl.npass_items[ip] > 0)
       hipLaunchKernelGGL(k_bpass<Real>, dim3(bl.npass_items[ip]), dim3(NT), bl.pass_lds[ip], s,
                          ba, bl.pass_items[ip], ip);
-  if (bl.nlast > 0)
-    hipLaunchKernelGGL(k_blast<Real>, dim3(bl.nlast), dim3(last_threads<Real>()), bl.last_lds, s,
-                       ba, bl.last_items);
   if (fork) {
     hipError_t e = hipStreamWaitEvent(s, aux->join, 0);
     if (e != hipSuccess) return e;
   }
+  if (bl.nlast > 0)
+    hipLaunchKernelGGL(k_blast<Real>, dim3(bl.nlast), dim3(last_threads<Real>()), bl.last_lds, s,
+                       ba, bl.last_items);
   return hipGetLastError();
 }
 
