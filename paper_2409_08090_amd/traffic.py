@@ -35,6 +35,8 @@ STAGE_OF = [
     ("k_row_compact", "row_class"),
     ("k_fft_last", "fft_last_power"), ("k_fft2_first", "fft_pass_0"),
     ("k_fft2_last", "fft_last_power"), ("k_fft2_out", "fft_out"),
+    ("k_pro_stats", "stats"), ("k_pro_bins", "bin_sort"), ("k_pro_rows", "row_class"),
+    ("k_split_first", "fft_pass_0"), ("k_split_last", "fft_last_power"),
 ]
 
 
@@ -69,7 +71,8 @@ def _is_2f(name):
 
 def stage_bytes(disp, scale):
     """Average scaled bytes per periodogram of each stage, over the complete
-    periodograms in the trace (each starts with k_stats).  A multi-pass plan
+    periodograms in the trace (each starts with k_pro_stats or k_stats; spreads
+    of both geometries in one launch make stage spread).  A multi-pass plan
     launches the first FFT pass twice (the 2f grid, then the two f grids,
     after the 2f spread): those two make stage fft_pass_0, and the i-th
     later pass launch is fft_pass_i.  A two-pass register-tile plan has one
@@ -80,7 +83,7 @@ def stage_bytes(disp, scale):
     npass = 0
     fork = False
     for _, name, kib in disp:
-        if "k_stats" in name and "k_stats_final" not in name:
+        if "k_pro_stats" in name or ("k_stats" in name and "k_stats_final" not in name):
             cur = defaultdict(float)
             steps.append(cur)
             npass = 0
@@ -88,7 +91,9 @@ def stage_bytes(disp, scale):
         if cur is None:
             continue
         stage = None
-        if "k_spread" in name:
+        if "k_spread_pg" in name:
+            stage = "spread"
+        elif "k_spread" in name:
             fork = fork or _is_2f(name)
             stage = "spread_2f" if _is_2f(name) else "spread_f"
         elif "k_fft_pass" in name:
@@ -120,7 +125,8 @@ def copy_scale(disp):
 # that fixes their launch shapes: a change to any of them makes stored
 # counter readings stale.
 SINGLE_PATH_SOURCES = ("device_math.h", "fft2.h", "fft2_index.h", "fft_core.h", "kernels.h",
-                       "kernels.hip", "mils_internal.h", "path_device.h", "plan.cpp", "plan.h")
+                       "kernels.hip", "mils_internal.h", "path_device.h", "plan.cpp", "plan.h",
+                       "prologue.hip", "split.hip", "spread.hip")
 
 
 def kernel_source_hash(root):
