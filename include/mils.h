@@ -154,14 +154,17 @@ int mils_context_set_graphs(mils_context *ctx, int enable);
  * environment has MILS_FFT2=0 at context creation; the plans of both
  * choices are cached side by side. */
 int mils_context_set_fft2(mils_context *ctx, int enable);
-/* Batched periodograms (mils_periodogram_batch and the serving loop): a
- * series whose three grids fit one workgroup's LDS (FP64 complex, at most
- * 3072 cells) runs its whole pipeline -- statistics, direct sums near f = 0,
- * spread, transforms, deconvolution and power -- in that workgroup, with no
- * grid in device memory.  Its grids are FP64 in either precision.  On by
- * default; 0 sends every series through the staged kernels. */
+/* Batched periodograms (mils_periodogram_batch and the serving loop) without
+ * grids in device memory.  FP64: a series of at most 16384 points (or few
+ * frequencies) has its frequencies split by residue, k = rho + D kappa, and
+ * one workgroup spreads, transforms and evaluates each residue on grids in
+ * LDS.  FP32: a series whose three grids fit one workgroup's LDS (FP64
+ * complex, at most 3072 cells) runs its whole pipeline in that workgroup.
+ * The grids are FP64 in either precision.  On by default; 0 sends every
+ * series through the staged kernels. */
 int mils_context_set_batch_onchip(mils_context *ctx, int enable);
-/* Series of the last batch built on this context that ran on chip. */
+/* Series of the last batch built on this context whose three grids fit one
+ * workgroup's LDS whole and ran on chip. */
 int64_t mils_context_batch_onchip(const mils_context *ctx);
 
 /* Fill *out with the plan for a periodogram of nd points with parameters p.
@@ -333,14 +336,16 @@ int mils_periodogram_shared_t(mils_context *ctx, const double *t, const double *
  * are device arrays (dy may be NULL).  common supplies eps, precision,
  * normalization and flags (its f0, df, nf are ignored).  status_per_curve
  * (host, nullable, ncurves int32) receives each curve's device-side status.
- * Synchronous.  The series run together, phase by phase (per-series
+ * Synchronous.  Series on chip (mils_context_set_batch_onchip) take one
+ * launch per grid size; the others run together, phase by phase (per-series
  * statistics, binning and low-frequency sums; both spreads; each FFT pass;
  * the last pass with power), each phase one launch over the tiles of every
- * series; the launches of a batch layout are captured once in a HIP graph
- * and replayed by later calls with the same layout and pointers.  Every
- * series has its own device workspace (its three grids, 48 bytes per grid
- * cell in FP64 and 24 in FP32, plus binning buffers); a batch that needs more
- * than the context's budget allows (or 24 GiB) runs in chunks.
+ * series.  A layout's first call launches its kernels; a repeat (the same
+ * layout and pointers) captures them in a HIP graph, which later repeats
+ * replay.  Every staged series has its own device workspace (its three grids,
+ * 48 bytes per grid cell in FP64 and 24 in FP32, plus binning buffers), a
+ * series on sub-grids 16 bytes a point; a batch that needs more than the
+ * context's budget allows (or 24 GiB) runs in chunks.
  */
 int mils_periodogram_batch(mils_context *ctx, int64_t ncurves, const int64_t *nd_off,
                            const double *t, const double *y, const double *dy,
@@ -465,11 +470,15 @@ int mils_server_destroy(mils_server *srv);
  * power, 8 direct sums near f = 0, 9 row classes of both geometries and
  * 10 the transpose into frequency order (9 and 10: two-pass register-tile
  * plans, whose first pass, stage 4, transforms all three grids in one
- * launch).  A periodogram runs stage 3, stage 8 and (multi-pass plans) the
- * first pass of the 2f grid on a second stream of the context, beside the f
- * geometry (stage 4 then counts two launches per call, and stages that
- * overlap share the GPU).  mils_profile_enable(ctx, 1) clears the
- * accumulators.
+ * launch).  Where stages share a launch in an unprofiled call (both spreads,
+ * the direct sums of up to 2e5 points, the first pass of all grids of a
+ * multi-pass plan), profiling launches them apart (stage 4 of a multi-pass
+ * plan then counts two launches per call).  Profiled calls run the passes that
+ * mils_plan_info reports: FP64 series that an unprofiled call takes through
+ * sub-grids in LDS, or through two passes instead of three on the same grid,
+ * run staged.  Direct sums of more points run on a second stream beside the
+ * first pass (stages that overlap share the GPU).  mils_profile_enable(ctx, 1)
+ * clears the accumulators.
  * mils_profile_read waits for the recorded events and adds, per stage, the
  * total elapsed milliseconds and the number of timed launches to ms_total[s]
  * and launches[s] (host arrays of MILS_NUM_STAGES entries), then clears them.
