@@ -545,6 +545,10 @@ bool plan_ready(mils_context* ctx, int64_t nf, double eps, int prec, int G, bool
   return it != ctx->plans.end() && it->second.tw;
 }
 
+// Whether the plan without a split transform has a grid of its own (those of
+// the register-tile FFT keep theirs).
+bool staged_smaller(const PlanEntry& e) { return e.split.split && !e.plan.fft2; }
+
 // Whether a call of nd points may take the grid of a split transform, which
 // can be a quarter larger than the staged one: not where that grid would go
 // over the context's budget (the smaller one may still fit).
@@ -553,7 +557,7 @@ bool split_fits(mils_context* ctx, int64_t nf, double eps, int prec, int G, bool
   if (!ctx->budget || prec != 0) return true;
   PlanEntry* pe = nullptr;
   if (get_plan(ctx, nf, eps, prec, G, &pe, false, false, 0, 0, fft2) != MILS_OK) return true;
-  if (!pe->split.split || pe->plan.fft2) return true;
+  if (!staged_smaller(*pe)) return true;
   const size_t need = layout_work(pe->split, nd, G, nullptr, nullptr) + extra;
   const size_t tables = pe->tw ? 0 : sizeof(double) * (size_t)pe->plan.K + ((size_t)1 << 20);
   return ctx->plan_bytes + tables + std::max(need, ctx->ws_bytes) <= ctx->budget;
@@ -777,24 +781,32 @@ int run_single(mils_context* ctx, const double* t, const double* y, const double
   if (cap && sync)
     return fail(ctx, MILS_ERR_INVALID_ARG,
                 "a synchronous call cannot be captured into a graph: use the _async variant");
-  const bool sok = split_fits(ctx, p->nf, p->eps, p->precision, G, ctx->fft2, nd, 0);
+  bool sok = split_fits(ctx, p->nf, p->eps, p->precision, G, ctx->fft2, nd, 0);
   if (cap && !plan_ready(ctx, p->nf, p->eps, p->precision, G, sok))
     return fail(ctx, MILS_ERR_BUSY,
                 "captured call needs a plan that does not exist yet: make one uncaptured call "
                 "with these sizes first");
   PlanEntry* pe = nullptr;
-  int rc = get_plan(ctx, p->nf, p->eps, p->precision, G, &pe, true, false, 0, 0, ctx->fft2, sok);
+  bool split = false;
+  int rc = MILS_OK;
+  for (;;) {
+    rc = get_plan(ctx, p->nf, p->eps, p->precision, G, &pe, true, false, 0, 0, ctx->fft2, sok);
+    if (rc != MILS_OK) return rc;
+    // (stage timing runs the staged passes of the same grid)
+    split = pe->split.split && !ctx->prof;
+    const size_t need = layout_work(split ? pe->split : pe->plan, nd, G, nullptr, nullptr);
+    if (cap && need > ctx->ws_bytes)
+      return fail(ctx, MILS_ERR_BUSY,
+                  "captured call needs a larger workspace: make one uncaptured call with these "
+                  "sizes first");
+    rc = ensure_workspace(ctx, need);
+    // device memory that the split transform's larger grid does not fit may
+    // fit the staged one
+    if (!(rc == MILS_ERR_OOM && sok && staged_smaller(*pe))) break;
+    sok = false;
+  }
   if (rc != MILS_OK) return rc;
-  // (stage timing runs the staged passes of the same grid)
-  const bool split = pe->split.split && !ctx->prof;
   const Plan& plan = split ? pe->split : pe->plan;
-  const size_t need = layout_work(plan, nd, G, nullptr, nullptr);
-  if (cap && need > ctx->ws_bytes)
-    return fail(ctx, MILS_ERR_BUSY,
-                "captured call needs a larger workspace: make one uncaptured call with these "
-                "sizes first");
-  rc = ensure_workspace(ctx, need);
-  if (rc != MILS_OK) return rc;
   if (cap) ctx->captured = true;
   Work w{};
   layout_work(plan, nd, G, ctx->ws, &w);
@@ -1354,16 +1366,21 @@ int mils_periodogram_shared_t(mils_context* ctx, const double* t, const double* 
   const size_t nst = (size_t)nseries + 1;
   const size_t low = up(sizeof(double) * 6 * kLowMax * kLowRows);
   const size_t extra = 2 * bsum + 3 * low + up(sizeof(DevStats) * nst) + 256;
-  rc = get_plan(ctx, p->nf, p->eps, p->precision, 3, &pe, true, false, 0, 0, false,
-                split_fits(ctx, p->nf, p->eps, p->precision, 3, false, nd, extra));
+  bool sok = split_fits(ctx, p->nf, p->eps, p->precision, 3, false, nd, extra), split = false;
+  size_t base = 0;
+  for (;;) {
+    rc = get_plan(ctx, p->nf, p->eps, p->precision, 3, &pe, true, false, 0, 0, false, sok);
+    if (rc != MILS_OK) return rc;
+    split = pe->split.split;
+    // workspace: the single-series layout, then B and B2 per output
+    // frequency and one statistics block per series plus one for the weights
+    base = up(layout_work(split ? pe->split : pe->plan, nd, 3, nullptr, nullptr));
+    rc = ensure_workspace(ctx, base + 2 * bsum + 3 * low + up(sizeof(DevStats) * nst));
+    if (!(rc == MILS_ERR_OOM && sok && staged_smaller(*pe))) break;  // (as in run_single)
+    sok = false;
+  }
   if (rc != MILS_OK) return rc;
-  const bool split = pe->split.split;
   const Plan& plan = split ? pe->split : pe->plan;
-  // workspace: the single-series layout, then B and B2 per output
-  // frequency and one statistics block per series plus one for the weights
-  const size_t base = up(layout_work(plan, nd, 3, nullptr, nullptr));
-  rc = ensure_workspace(ctx, base + 2 * bsum + 3 * low + up(sizeof(DevStats) * nst));
-  if (rc != MILS_OK) return rc;
   Work w{};
   layout_work(plan, nd, 3, ctx->ws, &w);
   w.tw = split ? pe->split_tw : pe->tw;
