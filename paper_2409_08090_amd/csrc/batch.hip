@@ -1,14 +1,16 @@
 // batch.hip -- periodograms of many independent series (gfx950).
 //
-// A batch runs as a short sequence of launches (captured once in a HIP graph
-// by the host): one workgroup per series computes its statistics, binning
-// and direct low-frequency sums; then each later phase -- both spreads, every
-// FFT pass, the last pass with deconvolution and power -- is one launch whose
-// workgroups are the tiles of all series of the batch (a host-built work
+// A batch runs as a short sequence of launches (a repeated layout's captured
+// in a HIP graph by the host).  FP64 series of at most 16384 points run on
+// sub-grids in LDS (chip.hip), FP32 series whose grids fit LDS in one workgroup
+// each (k_bsmall).  For the others one workgroup per series computes its
+// statistics, binning and row flags; then each later phase -- both spreads,
+// every FFT pass, the last pass with deconvolution and power -- is one launch
+// whose workgroups are the tiles of all series of the batch (a host-built work
 // list of (series, tile) items), so that every phase has the whole GPU's
-// memory parallelism whatever the size mix.  Series are grouped into
-// grid-size classes that share a plan (twiddles, kernel transform); each
-// series has its own workspace.
+// memory parallelism whatever the size mix; the direct low-frequency sums run
+// beside them.  Series are grouped into grid-size classes that share a plan
+// (twiddles, kernel transform); each series has its own workspace.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
