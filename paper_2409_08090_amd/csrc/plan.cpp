@@ -218,9 +218,9 @@ namespace {
 
 // n = R La L1 of a split transform and its cost a cell in the units of the
 // planner's estimate, from times at n = 5e5 .. 1.6e7: a residue more costs
-// little (its reads come from L2), lines of 512 in the last pass a fifth of it
-// (their 64-byte pieces), and first-pass lines other than 512 keep 64-byte
-// pieces (256: more residues) or half as many workgroups a CU (1024).
+// little (its reads come from L2), last-pass lines of 512 a seventh more and of
+// 1024 3 % more than 2048 (shorter runs of loads), first-pass lines of 256
+// (twice the residues) or 1024 (half the workgroups a CU) 2 % more than 512.
 struct SplitShape {
   int R = 0, La = 0, L1 = 0;
   double cost = 1e300;

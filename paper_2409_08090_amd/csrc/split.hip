@@ -19,7 +19,10 @@
 //
 // The three-pass plans that this replaces move the grids through memory once
 // more each way and hold lines of about 120 cells, with LDS traffic for every
-// radix stage.
+// radix stage: 38 + 34 + 35 us for the three grids of 1.57e6 cells, here 21 +
+// 37 (75 MB written and read: 15 us each at the rate of a fill).  Both passes
+// are bound by their workgroups' latency, which load, exchange and store in
+// turn, four (first) and two (last) waves a SIMD.
 #include <hip/hip_runtime.h>
 
 #include "fft2.h"
