@@ -3,7 +3,7 @@
 // The frequencies of a series are split by residue: k = rho + D kappa, rho <
 // D.  The sums over kappa for one rho are the same transform again (first
 // frequency f0 + rho df, step D df, about nf / D frequencies), on a grid of
-// N ~ 1.28 nf / D cells.  With D chosen so that N is one of a few powers of
+// N >= 1.36 nf / D cells.  With D chosen so that N is one of a few powers of
 // two, one workgroup takes one rho: it spreads all points of the series onto
 // its grids in LDS, transforms them there and writes its share of the power.
 // Nothing but the points and the power crosses HBM, no grid size needs a plan

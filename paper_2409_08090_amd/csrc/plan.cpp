@@ -202,12 +202,18 @@ double planner_sigma(double eps, int prec, bool batch) { return choose_sigma(eps
 
 double kernel_beta(int w, double sigma) { return 0.97 * M_PI * w * (1.0 - 1.0 / (2.0 * sigma)); }
 
+// sigma 1.36 and the width that then has the staged kernel's error estimate
+// (16 cells at eps = 1e-9, which the spread takes in the time of fewer).  A
+// residue's band fills its grid to N / sigma, while the grid of a staged series
+// rounds up to a smooth size, so at the staged kernel's own sigma the sub-grids
+// would be the less accurate: aliasing at the band edge 1.05e-9 at 1.28 and
+// 1.6e-10 here, 2.7e-10 to 1.2e-9 on the staged plans' grids of 1.25 to 1.33.
+// It costs 6 % more residues.
 void chip_kernel(double eps, bool wide, double* sigma, int* w, double* beta) {
-  // 1.28, the factor that the smooth grid sizes of ordinary plans come to;
-  // 2 when that would need a kernel wider than kMaxWidth cells
-  double s = 1.28;
-  if (std::log(width_margin(0) / eps) / (M_PI * std::sqrt(1.0 - 1.0 / s)) > kMaxWidth) s = 2.0;
-  int wi = wide ? kMaxWidth : kernel_width(eps, s, 0);
+  const double s0 = planner_sigma(eps, 0, true);
+  const double s = std::max(s0, 1.36);
+  const double same = std::sqrt((1.0 - 1.0 / s0) / (1.0 - 1.0 / s));
+  int wi = wide ? kMaxWidth : (int)std::ceil(kernel_width(eps, s0, 0) * same + 1.0);
   wi += wi & 1;
   *sigma = s;
   *w = wi;
