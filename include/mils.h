@@ -155,8 +155,10 @@ int mils_context_set_graphs(mils_context *ctx, int enable);
  * choices are cached side by side. */
 int mils_context_set_fft2(mils_context *ctx, int enable);
 /* Batched periodograms (mils_periodogram_batch and the serving loop) without
- * grids in device memory.  FP64: a series of at most 16384 points (or few
- * frequencies) has its frequencies split by residue, k = rho + D kappa, and
+ * grids in device memory.  FP64: where it is estimated shorter (up to 16384
+ * points, from the series' points and frequencies and the size of the batch;
+ * always for few frequencies, or where the staged kernels' workspace cannot be
+ * had) a series has its frequencies split by residue, k = rho + D kappa, and
  * one workgroup spreads, transforms and evaluates each residue on grids in
  * LDS.  FP32: a series whose three grids fit one workgroup's LDS (FP64
  * complex, at most 3072 cells) runs its whole pipeline in that workgroup.

@@ -1529,50 +1529,35 @@ size_t layout_chip(int64_t nd, char* base, Work* w) {
   return o_rec + up(sizeof(double) * 2 * nd);
 }
 
+// Which FP64 series of a batch run on sub-grids in LDS (chip_rule.h): none,
+// those for which it is estimated shorter, or all that can.
+enum class ChipUse { kNone, kBatch, kAll };
+
 // The series of a batch that run on sub-grids in LDS: kind[c] (see ChipSet;
-// -1: not) and residues D[c].  A series takes the largest grid of the batch,
-// or the smallest that holds it whole.  The batch's grid is the one whose
-// estimated time is shortest: larger grids visit every point from fewer
-// workgroups, smaller ones spread few series over the chip.
-void choose_chip(const mils_context* ctx, const ChipSet& cs, const std::vector<int64_t>& idx,
-                 const int64_t* nd_off, const int64_t* nf_off, std::vector<int>* kind,
-                 std::vector<int>* D) {
-  const int64_t m = (int64_t)idx.size();
-  auto size_of = [&](int64_t nf, int top) {  // smallest grid up to top that holds nf whole
-    int i = 0;
-    while (i < top && nf > cs.plan[i].nfmax) ++i;
-    return i;
-  };
-  auto takes = [&](int64_t nd, int64_t nf) { return nd <= kChipBatchNd || nf <= kChipOneNf; };
-  int best = 0;
-  double best_cost = 1e300;
-  for (int top = 0; top < kChipBatchSizes; ++top) {
-    double total = 0.0, longest = 0.0;
-    for (int64_t c = 0; c < m; ++c) {
-      const int64_t nd = nd_off[idx[c] + 1] - nd_off[idx[c]];
-      const int64_t nf = nf_off[idx[c] + 1] - nf_off[idx[c]];
-      if (!takes(nd, nf)) continue;
-      const int i = size_of(nf, top);
-      // cycles of one residue (measured: 18 a point with the three grids at
-      // once, 33 one after another, and about 10 a cell)
-      const double one = (double)nd * (kChipBatchN[i] > 2048 ? 33.0 : 18.0) +
-                         10.0 * kChipBatchN[i] + 10000.0;
-      total += one * (double)chip_residues(nf, cs.plan[i].nfmax);
-      longest = std::max(longest, one);
-    }
-    const double cost = std::max(total / ctx->num_cu, longest);
-    if (cost < 0.97 * best_cost) {
-      best_cost = cost;
-      best = top;
-    }
+// -1: not) and residues D[c].
+void choose_chip(const mils_context* ctx, const ChipSet& cs, ChipUse use,
+                 const std::vector<int64_t>& idx, const int64_t* nd_off, const int64_t* nf_off,
+                 std::vector<int>* kind, std::vector<int>* D) {
+  const size_t m = idx.size();
+  int nfmax[kChipBatchSizes];
+  for (int i = 0; i < kChipBatchSizes; ++i) nfmax[i] = cs.plan[i].nfmax;
+  const chiprule::Rule rule{nfmax, ctx->num_cu, cs.plan[0].w > 16};
+  std::vector<int64_t> nd(m), nf(m);
+  for (size_t c = 0; c < m; ++c) {
+    nd[c] = nd_off[idx[c] + 1] - nd_off[idx[c]];
+    nf[c] = nf_off[idx[c] + 1] - nf_off[idx[c]];
   }
-  for (int64_t c = 0; c < m; ++c) {
-    const int64_t nd = nd_off[idx[c] + 1] - nd_off[idx[c]];
-    const int64_t nf = nf_off[idx[c] + 1] - nf_off[idx[c]];
-    if (!takes(nd, nf)) continue;
-    const int k = size_of(nf, best) + (nf <= kChipWideNf ? kChipBatchSizes : 0);
-    (*kind)[c] = k;
-    (*D)[c] = (int)chip_residues(nf, cs.plan[k].nfmax);
+  std::vector<int> size;
+  chiprule::choose_batch(rule, nd, nf, use == ChipUse::kAll, &size);
+  int64_t count[kChipBatchSizes + 1] = {};  // [0]: staged
+  for (int i : size) ++count[i + 1];
+  mils_log(2, "batch of %lld: %lld staged, on sub-grids of 256 %lld, 1024 %lld, 2048 %lld, 4096 %lld, "
+           "8192 %lld", (long long)m, (long long)count[0], (long long)count[1], (long long)count[2],
+           (long long)count[3], (long long)count[4], (long long)count[5]);
+  for (size_t c = 0; c < m; ++c) {
+    if (size[c] < 0) continue;
+    (*kind)[c] = size[c] + (nf[c] <= kChipWideNf ? kChipBatchSizes : 0);
+    (*D)[c] = (int)chip_residues(nf[c], nfmax[size[c]]);
   }
 }
 
@@ -1588,7 +1573,7 @@ int build_batch(mils_context* ctx, BatchState& B, const std::vector<int64_t>& id
                 const int64_t* nd_off, const double* t, const double* y, const double* dy,
                 const int64_t* nf_off, const double* f0, const double* df,
                 const mils_params* common, double* power, int64_t nstatus, hipStream_t stream,
-                bool use_chip) {
+                ChipUse use) {
   const int64_t m = (int64_t)idx.size();
   const int prec = common->precision;
   hipError_t he = hipSuccess;
@@ -1596,8 +1581,9 @@ int build_batch(mils_context* ctx, BatchState& B, const std::vector<int64_t>& id
   // and kernel) and its number of residues; -1: a staged series (or, FP32
   // forms, one whose grids fit LDS)
   std::vector<int> chip_of(m, -1), chip_D(m, 0);
-  const ChipSet* chips = use_chip && prec == 0 ? get_chip(ctx, common->eps, true) : nullptr;
-  if (chips) choose_chip(ctx, *chips, idx, nd_off, nf_off, &chip_of, &chip_D);
+  const ChipSet* chips =
+      use != ChipUse::kNone && prec == 0 ? get_chip(ctx, common->eps, true) : nullptr;
+  if (chips) choose_chip(ctx, *chips, use, idx, nd_off, nf_off, &chip_of, &chip_D);
   // grid size of each series, then grid-size classes (ratio <= 1.06) that share a plan
   // A batch of one series makes its class's plan also when the series runs in
   // LDS: the serving loop's warm-up runs one short series per class, and longer
@@ -2000,7 +1986,7 @@ int autotune_batch(mils_context* ctx, int64_t ncurves, const int64_t* nd_off, co
       std::vector<double> sig(sample.size(), cv.first);
       std::vector<int> tm(sample.size(), cv.second);
       rc = build_batch(ctx, T, sample, sig, tm, nd_off, t, y, dy, nf_off, f0, df, common, power,
-                       ncurves, stream, false);
+                       ncurves, stream, ChipUse::kNone);
       if (rc == MILS_ERR_UNSUPPORTED) {  // this sigma does not plan for the band
         rc = MILS_OK;
         continue;
@@ -2103,8 +2089,13 @@ int mils_batch_run(mils_context* ctx, int64_t ncurves, const int64_t* nd_off, co
   const bool repeated = B.valid && B.key == key;
   if (!repeated) {
     B.valid = false;
-    int rc = build_batch(ctx, B, idx, sig, tmax, nd_off, t, y, dy, nf_off, f0, df, common, power,
-                         ncurves, stream, ctx->batch_onchip);
+    auto build = [&](ChipUse use) {
+      return build_batch(ctx, B, idx, sig, tmax, nd_off, t, y, dy, nf_off, f0, df, common, power,
+                         ncurves, stream, use);
+    };
+    int rc = build(ctx->batch_onchip ? ChipUse::kBatch : ChipUse::kNone);
+    // staged series need 48 bytes and more a grid cell, sub-grids 16 a point
+    if (rc == MILS_ERR_OOM && ctx->batch_onchip && prec == 0) rc = build(ChipUse::kAll);
     if (rc != MILS_OK) return rc;
     B.key = key;
     B.valid = true;

@@ -1,8 +1,8 @@
 // batch.hip -- periodograms of many independent series (gfx950).
 //
 // A batch runs as a short sequence of launches (a repeated layout's captured
-// in a HIP graph by the host).  FP64 series of at most 16384 points run on
-// sub-grids in LDS (chip.hip), FP32 series whose grids fit LDS in one workgroup
+// in a HIP graph by the host).  FP64 series run on sub-grids in LDS (chip.hip)
+// where that is estimated shorter (chip_rule.h), FP32 series whose grids fit LDS in one workgroup
 // each (k_bsmall).  For the others one workgroup per series computes its
 // statistics, binning and row flags; then each later phase -- both spreads,
 // every FFT pass, the last pass with deconvolution and power -- is one launch

@@ -14,6 +14,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "chip_rule.h"
 #include "mils_internal.h"
 
 namespace mils {
@@ -47,25 +48,6 @@ constexpr int kChipMaxSeries = 64;
 hipError_t launch_chip_single(const CallArgs& a, const ChipPlan& cp, int D, DevStats* st,
                               ChipDone* done, int* host_status, int nseries, int64_t dy_stride,
                               hipStream_t s);
-
-// Sub-grid sizes; single calls take one of the first two.
-constexpr int kChipBatchN[] = {256, 1024, 2048, 4096, 8192};
-constexpr int kChipBatchSizes = 5;
-// kinds of a batch's items: a grid size with the tolerance's kernel, or with
-// the widest one
-constexpr int kChipKinds = 2 * kChipBatchSizes;
-// most frequencies of a series that takes the widest kernel (its whole grid
-// fits one pass of the staged path, which does the same), and of a series
-// whose three grids would fit one workgroup's LDS whole
-constexpr int64_t kChipWideNf = 800, kChipOneNf = 2400;
-// Most points of a batched series.  Here a series costs about D (33 nd + 10 N)
-// cycles of one CU (N = 8192, D = nf / 6400), in the staged phases about
-// 700 nd and the launches of every phase: 419 series of 8192 to 10000 points
-// took 5.8 ms there and 4.1 ms here.
-constexpr int64_t kChipBatchNd = 16384;
-
-// Residues (workgroups) of a series on sub-grids of at most nfmax frequencies.
-inline int64_t chip_residues(int64_t nf, int nfmax) { return (nf + nfmax - 1) / nfmax; }
 
 // Batch: the statistics of the on-chip series and their point records
 // (prologue, one workgroup per series), then one workgroup per item (series,

@@ -1,4 +1,4 @@
-// Host checks of the sub-grids in LDS (plan.cpp, chip.h), built and run by
+// Host checks of the sub-grids in LDS (plan.cpp, chip_rule.h), built and run by
 // tests/test_subgrid_host.py.  Prints "ok" at the end.
 #include <algorithm>
 #include <cmath>
@@ -7,7 +7,7 @@
 #include <string>
 #include <vector>
 
-#include "../paper_2409_08090_amd/csrc/chip.h"
+#include "../paper_2409_08090_amd/csrc/chip_rule.h"
 #include "../paper_2409_08090_amd/csrc/plan.h"
 
 using namespace mils;
@@ -75,9 +75,97 @@ static int accuracy() {
   return bad;
 }
 
+// The sizes that choose_batch gives, eps = 1e-9 on 256 CUs.
+struct Sizes {
+  int nfmax[kChipBatchSizes];
+  chiprule::Rule rule(bool two_sets = false) const { return {nfmax, 256, two_sets}; }
+  Sizes() {
+    double sigma, beta;
+    int w;
+    chip_kernel(1e-9, false, &sigma, &w, &beta);
+    for (int i = 0; i < kChipBatchSizes; ++i) nfmax[i] = (int)((double)kChipBatchN[i] / sigma);
+  }
+};
+
+// Layouts of `count` series of nd points at nd ratio frequencies, timed both
+// ways (us, replayed; the sub-grids at their best size): the rule takes the
+// shorter.
+static int choice() {
+  const struct {
+    int count, nd;
+    double ratio;
+    int staged_us, on_us;
+  } timed[] = {
+      {1, 100, 12, 106, 63},       {1, 4000, 12, 118, 99},      {1, 13000, 12, 167, 195},
+      {1, 10000, 3, 129, 169},     {4, 13000, 1, 149, 200},     {4, 13000, 30, 247, 484},
+      {4, 8000, 100, 362, 498},    {15, 2000, 12, 139, 88},     {15, 4000, 100, 604, 433},
+      {15, 13000, 12, 359, 490},   {60, 1000, 12, 165, 92},     {60, 8000, 12, 477, 647},
+      {60, 2000, 100, 1216, 599},  {60, 13000, 12, 1060, 1489}, {250, 4000, 30, 3277, 1909},
+      {250, 4000, 3, 392, 270},    {250, 8000, 12, 1671, 2356}, {250, 13000, 12, 4074, 5322},
+      {1000, 300, 30, 1005, 420},  {1000, 1000, 3, 514, 252},   {1000, 2000, 12, 1629, 1210},
+      {1000, 8000, 12, 6382, 9251}, {1000, 13000, 3, 3274, 6070}};
+  const Sizes s;
+  int bad = 0;
+  for (const auto& x : timed) {
+    std::vector<int64_t> nd(x.count, x.nd), nf(x.count, (int64_t)(x.nd * x.ratio));
+    std::vector<int> size;
+    chiprule::choose_batch(s.rule(), nd, nf, false, &size);
+    for (int z : size)
+      if ((z < 0) != (x.staged_us < x.on_us)) {
+        std::printf("%d x %d, ratio %g: size %d, staged %d us, sub-grids %d us\n", x.count, x.nd,
+                    x.ratio, z, x.staged_us, x.on_us);
+        ++bad;
+        break;
+      }
+  }
+  return bad;
+}
+
+// Every choice is one that the kernels can take: a size whose residues hold the
+// series, staged beyond the range of the rule unless the series is short enough
+// for one workgroup, and with `all` whatever can be is on sub-grids.
+static int forms() {
+  const Sizes s;
+  int bad = 0;
+  unsigned x = 12345;
+  auto rnd = [&]() { return (double)((x = x * 1664525u + 1013904223u) >> 8) / 16777216.0; };
+  for (int trial = 0; trial < 300; ++trial) {
+    const int m = 1 + (int)(rnd() * rnd() * 200);
+    std::vector<int64_t> nd, nf;
+    for (int i = 0; i < m; ++i) {
+      nd.push_back((int64_t)std::exp(rnd() * std::log(1e6)));
+      nf.push_back((int64_t)std::exp(rnd() * std::log((double)(1 << 28))));
+      if (trial % 4 == 0) nf.back() = 1 + (int64_t)(rnd() * 3000);
+    }
+    for (bool all : {false, true})
+      for (bool two : {false, true}) {
+        std::vector<int> size;
+        chiprule::choose_batch(s.rule(two), nd, nf, all, &size);
+        for (int i = 0; i < m; ++i) {
+          const bool can = nd[i] <= kChipBatchNd || nf[i] <= kChipOneNf;
+          bool ok = size[i] >= -1 && size[i] < kChipBatchSizes;
+          if (size[i] < 0) ok = ok && !(all && can) && nf[i] > kChipOneNf;
+          else {
+            const int64_t D = chip_residues(nf[i], s.nfmax[size[i]]);
+            ok = ok && can && D * s.nfmax[size[i]] >= nf[i] && D <= 0x7fffffff &&
+                 (nf[i] + D - 1) / D <= s.nfmax[size[i]];
+          }
+          if (!ok) {
+            std::printf("nd %lld nf %lld: size %d\n", (long long)nd[i], (long long)nf[i], size[i]);
+            ++bad;
+          }
+        }
+      }
+  }
+  return bad;
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
-  const int bad = what == "accuracy" ? accuracy() : 1;
+  const int bad = what == "accuracy" ? accuracy()
+                  : what == "choice" ? choice()
+                  : what == "forms"  ? forms()
+                                     : 1;
   if (bad) return 1;
   std::printf("ok\n");
   return 0;

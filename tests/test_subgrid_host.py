@@ -1,5 +1,6 @@
 """Host checks of the sub-grids in LDS: their kernel against the staged
-plans' (tests/subgrid_check.cpp, no GPU)."""
+plans', and the rule that takes a batch's series there
+(tests/subgrid_check.cpp, no GPU)."""
 import os
 import shutil
 import subprocess
@@ -29,3 +30,11 @@ def check(tmp_path_factory):
 
 def test_as_accurate_as_the_staged_plan_of_the_series(check):
     check("accuracy")
+
+
+def test_batches_take_the_path_that_was_timed_shorter(check):
+    check("choice")
+
+
+def test_every_choice_fits_the_kernels(check):
+    check("forms")
