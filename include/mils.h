@@ -382,7 +382,9 @@ int mils_batch_tuning(mils_context *ctx, int64_t nf, double eps, int32_t precisi
  * streams (a lane that frees up takes everything that has arrived: continuous
  * batching), and read back to host memory.  Requests whose frequency count
  * exceeds the batch limit run through the single-series path on a lane.
- * Thread-safe: any host thread may submit, poll, wait and take.
+ * Thread-safe: any host thread may submit, poll, wait and take.  The grid of a
+ * request depends on that request alone, so its result is the same, to
+ * rounding, whatever it is batched with.
  *
  * Plan classes: a request is computed on its frequency grid f0 + k df
  * extended to the next class size (nf rounded up to ceil(64 * 2^(j/16)),

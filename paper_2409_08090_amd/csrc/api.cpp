@@ -1530,8 +1530,9 @@ size_t layout_chip(int64_t nd, char* base, Work* w) {
 }
 
 // Which FP64 series of a batch run on sub-grids in LDS (chip_rule.h): none,
-// those for which it is estimated shorter, or all that can.
-enum class ChipUse { kNone, kBatch, kAll };
+// those for which it is estimated shorter in this batch, all that can, or by
+// each series alone (the serving loop, whose batches are whatever has arrived).
+enum class ChipUse { kNone, kBatch, kAll, kAlone };
 
 // The series of a batch that run on sub-grids in LDS: kind[c] (see ChipSet;
 // -1: not) and residues D[c].
@@ -1547,8 +1548,11 @@ void choose_chip(const mils_context* ctx, const ChipSet& cs, ChipUse use,
     nd[c] = nd_off[idx[c] + 1] - nd_off[idx[c]];
     nf[c] = nf_off[idx[c] + 1] - nf_off[idx[c]];
   }
-  std::vector<int> size;
-  chiprule::choose_batch(rule, nd, nf, use == ChipUse::kAll, &size);
+  std::vector<int> size(m);
+  if (use == ChipUse::kAlone)
+    for (size_t c = 0; c < m; ++c) size[c] = chiprule::choose_alone(rule, nd[c], nf[c]);
+  else
+    chiprule::choose_batch(rule, nd, nf, use == ChipUse::kAll, &size);
   int64_t count[kChipBatchSizes + 1] = {};  // [0]: staged
   for (int i : size) ++count[i + 1];
   mils_log(2, "batch of %lld: %lld staged, on sub-grids of 256 %lld, 1024 %lld, 2048 %lld, 4096 %lld, "
@@ -1584,14 +1588,12 @@ int build_batch(mils_context* ctx, BatchState& B, const std::vector<int64_t>& id
   const ChipSet* chips =
       use != ChipUse::kNone && prec == 0 ? get_chip(ctx, common->eps, true) : nullptr;
   if (chips) choose_chip(ctx, *chips, use, idx, nd_off, nf_off, &chip_of, &chip_D);
-  // grid size of each series, then grid-size classes (ratio <= 1.06) that share a plan
-  // A batch of one series makes its class's plan also when the series runs in
-  // LDS: the serving loop's warm-up runs one short series per class, and longer
-  // series of the class need the plan.
+  // grid size of each series, then grid-size classes that share a plan (ratio
+  // <= 1.06; served series keep their own grid, whatever shares the batch)
+  const double class_ratio = use == ChipUse::kAlone ? 1.0 : 1.06;
   std::vector<int64_t> ngrid(m, 0);
-  const bool all_plans = m == 1;
   for (int64_t c = 0; c < m; ++c) {
-    if (chip_of[c] >= 0 && !all_plans) continue;
+    if (chip_of[c] >= 0) continue;
     const int64_t nf = nf_off[idx[c] + 1] - nf_off[idx[c]];
     auto k = std::make_tuple(nf, prec, common->eps, sig[c]);
     auto it = B.grid_of_nf.find(k);
@@ -1608,7 +1610,7 @@ int build_batch(mils_context* ctx, BatchState& B, const std::vector<int64_t>& id
   }
   std::vector<std::pair<int64_t, int>> ns;
   for (int64_t c = 0; c < m; ++c)
-    if (chip_of[c] < 0 || all_plans) ns.push_back({ngrid[c], tmax[c]});
+    if (chip_of[c] < 0) ns.push_back({ngrid[c], tmax[c]});
   std::sort(ns.begin(), ns.end(), [](const std::pair<int64_t, int>& x, const std::pair<int64_t, int>& y) {
     return x.second != y.second ? x.second < y.second : x.first < y.first;
   });
@@ -1620,7 +1622,7 @@ int build_batch(mils_context* ctx, BatchState& B, const std::vector<int64_t>& id
   for (size_t i = 0; i < ns.size();) {
     size_t j = i;
     while (j + 1 < ns.size() && ns[j + 1].second == ns[i].second &&
-           (double)ns[j + 1].first <= 1.06 * (double)ns[i].first)
+           (double)ns[j + 1].first <= class_ratio * (double)ns[i].first)
       ++j;
     const int cid = (int)cls_n.size();
     cls_n.push_back(ns[j].first);
@@ -1633,7 +1635,7 @@ int build_batch(mils_context* ctx, BatchState& B, const std::vector<int64_t>& id
   std::vector<int> cls_of(m, 0);
   std::vector<char> cls_tuned(ncls, 0);
   for (int64_t c = 0; c < m; ++c) {
-    if (chip_of[c] >= 0 && !all_plans) continue;
+    if (chip_of[c] >= 0) continue;
     cls_of[c] = cls_of_n[{ngrid[c], tmax[c]}];
     cls_nf[cls_of[c]] = std::max<int64_t>(cls_nf[cls_of[c]], nf_off[idx[c] + 1] - nf_off[idx[c]]);
     if (sig[c] > 1.0) cls_tuned[cls_of[c]] = 1;
@@ -2093,7 +2095,9 @@ int mils_batch_run(mils_context* ctx, int64_t ncurves, const int64_t* nd_off, co
       return build_batch(ctx, B, idx, sig, tmax, nd_off, t, y, dy, nf_off, f0, df, common, power,
                          ncurves, stream, use);
     };
-    int rc = build(ctx->batch_onchip ? ChipUse::kBatch : ChipUse::kNone);
+    int rc = build(!use_graph          ? ChipUse::kAlone
+                   : ctx->batch_onchip ? ChipUse::kBatch
+                                       : ChipUse::kNone);
     // staged series need 48 bytes and more a grid cell, sub-grids 16 a point
     if (rc == MILS_ERR_OOM && ctx->batch_onchip && prec == 0) rc = build(ChipUse::kAll);
     if (rc != MILS_OK) return rc;

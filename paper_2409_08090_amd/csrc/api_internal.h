@@ -8,7 +8,9 @@
 
 #include "../../include/mils.h"
 
-// Batched periodograms; use_graph = false launches directly (no capture).
+// Batched periodograms.  use_graph = false (the serving loop): no tuning, direct
+// launches (no capture), and the path and grid of a series depend on that
+// series alone, so that its result does not depend on what it is batched with.
 int mils_batch_run(mils_context* ctx, int64_t ncurves, const int64_t* nd_off, const double* t,
                    const double* y, const double* dy, const int64_t* nf_off, const double* f0,
                    const double* df, const mils_params* common, double* power,

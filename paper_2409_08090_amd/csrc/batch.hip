@@ -2,8 +2,8 @@
 //
 // A batch runs as a short sequence of launches (a repeated layout's captured
 // in a HIP graph by the host).  FP64 series run on sub-grids in LDS (chip.hip)
-// where that is estimated shorter (chip_rule.h), FP32 series whose grids fit LDS in one workgroup
-// each (k_bsmall).  For the others one workgroup per series computes its
+// where that is estimated shorter (chip_rule.h), FP32 series whose grids fit
+// LDS in one workgroup each (k_bsmall).  For the others one workgroup per series computes its
 // statistics, binning and row flags; then each later phase -- both spreads,
 // every FFT pass, the last pass with deconvolution and power -- is one launch
 // whose workgroups are the tiles of all series of the batch (a host-built work

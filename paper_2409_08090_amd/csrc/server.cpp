@@ -34,6 +34,7 @@
 
 #include "../../include/mils.h"
 #include "api_internal.h"
+#include "chip_rule.h"
 
 namespace {
 
@@ -278,46 +279,58 @@ void mils_server::count_plans(Lane* L) {
   L->plan_s_seen = sec;
 }
 
-// Runs every plan class up to nf_max once on this lane (parameters p apart
-// from the grid): a one-series batch for the batched classes and a
-// single-series call for the larger ones, on a short synthetic series (the
-// single-series classes with nf / 12 points, so that the workspace also
-// grows ahead of traffic).  Returns the first error.
+// Runs every plan class up to nf_max on this lane (parameters p apart from the
+// grid): a one-series batch for the batched classes and a single-series call
+// for the larger ones, on a synthetic series.  The batched classes take a short
+// one and, in FP64, one too long for sub-grids in LDS, which builds the class's
+// staged plan (classes of few frequencies never need it); the single-series
+// classes nf / 12 points, so that the workspace also grows ahead of traffic.
+// Returns the first error.
 int mils_server::run_warm(Lane* L, const mils_params& p, int64_t nf_max) {
-  const int64_t top = nf_class(nf_max);
-  std::vector<double> h;
-  for (int64_t v = nf_class(1);; v = nf_class(v + 1)) {
-    const bool single = v > kBatchMaxNf;
-    const int64_t nd = single ? std::max<int64_t>(64, v / 12) : 64;
-    // sorted times on [0, 20) with irregular spacing, a sinusoid, unit errors
-    h.resize(3 * (size_t)nd);
+  // sorted times on [0, 20) with irregular spacing, a sinusoid, unit errors
+  auto synthetic = [](int64_t nd) {
+    std::vector<double> h(3 * (size_t)nd);
     for (int64_t j = 0; j < nd; ++j) {
       const double u = ((double)j + 0.5 + 0.4 * std::sin(7.1 * (double)j)) / (double)nd;
       h[j] = 20.0 * u;
       h[nd + j] = std::sin(2.3 * h[j]) + 0.1 * std::cos(17.0 * (double)j);
       h[2 * nd + j] = 1.0;
     }
-    if (!grow_device(&L->d_in, &L->d_in_cap, 3 * (size_t)nd) ||
-        !grow_device(&L->d_out, &L->d_out_cap, (size_t)v))
+    return h;
+  };
+  auto run = [&](const std::vector<double>& h, int64_t nf, bool single) -> int {
+    const int64_t nd = (int64_t)h.size() / 3;
+    if (!grow_device(&L->d_in, &L->d_in_cap, h.size()) ||
+        !grow_device(&L->d_out, &L->d_out_cap, (size_t)nf))
       return MILS_ERR_OOM;
-    if (hipMemcpyAsync(L->d_in, h.data(), 3 * (size_t)nd * sizeof(double), hipMemcpyHostToDevice,
+    if (hipMemcpyAsync(L->d_in, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice,
                        L->stream) != hipSuccess)
       return MILS_ERR_DEVICE;
     mils_params q = p;
-    q.nf = v;
+    q.nf = nf;
     q.f0 = q.df = 0.01;
     int rc;
     if (single) {
       rc = mils_periodogram(L->ctx, L->d_in, L->d_in + nd, L->d_in + 2 * nd, nd, &q, L->d_out,
                             L->stream);
     } else {
-      const int64_t nd_off[2] = {0, nd}, nf_off[2] = {0, v};
+      const int64_t nd_off[2] = {0, nd}, nf_off[2] = {0, nf};
       int32_t st = MILS_OK;
       rc = mils_batch_run(L->ctx, 1, nd_off, L->d_in, L->d_in + nd, L->d_in + 2 * nd, nf_off,
                           &q.f0, &q.df, &q, L->d_out, &st, L->stream, false);
     }
     if (rc != MILS_OK && rc != MILS_ERR_DEGENERATE) return rc;
-    if (hipStreamSynchronize(L->stream) != hipSuccess) return MILS_ERR_DEVICE;
+    return hipStreamSynchronize(L->stream) == hipSuccess ? MILS_OK : MILS_ERR_DEVICE;
+  };
+  const bool f64 = p.precision == MILS_FP64;
+  const std::vector<double> brief = synthetic(64);
+  const std::vector<double> lengthy = synthetic(f64 ? mils::kChipBatchNd + 1 : 0);
+  const int64_t top = nf_class(nf_max);
+  for (int64_t v = nf_class(1);; v = nf_class(v + 1)) {
+    const bool single = v > kBatchMaxNf;
+    int rc = run(single ? synthetic(std::max<int64_t>(64, v / 12)) : brief, v, single);
+    if (rc == MILS_OK && !single && f64 && v > mils::kChipOneNf) rc = run(lengthy, v, false);
+    if (rc != MILS_OK) return rc;
     if (v >= top) break;
   }
   return MILS_OK;

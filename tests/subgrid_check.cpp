@@ -156,6 +156,15 @@ static int forms() {
           }
         }
       }
+    // (a served series, from itself alone)
+    for (int i = 0; i < m; ++i) {
+      const int z = chiprule::choose_alone(s.rule(), nd[i], nf[i]);
+      if (z < -1 || z >= kChipBatchSizes || (z < 0 && nf[i] <= kChipOneNf) ||
+          (z >= 0 && nd[i] > kChipBatchNd && nf[i] > kChipOneNf)) {
+        std::printf("served nd %lld nf %lld: size %d\n", (long long)nd[i], (long long)nf[i], z);
+        ++bad;
+      }
+    }
   }
   return bad;
 }
