@@ -707,17 +707,22 @@ void make_horner(const Plan& p, std::vector<double>* coef) {
   const long double beta = (long double)p.beta;
   coef->assign((size_t)N * kHornerK, 0.0);
   std::vector<long double> fv(N), ch(N), mono(N), tm1(N), t0(N), t1(N);
+  // cos(pi m (2 i + 1) / (2 N)), the same for every cell (worked out for each,
+  // they were nine tenths of a table's 0.6 ms)
+  std::vector<long double> cs((size_t)N * N);
+  for (int m = 0; m < N; ++m)
+    for (int i = 0; i < N; ++i) cs[(size_t)m * N + i] = cosl(pi * m * (2 * i + 1) / (2.0L * N));
   for (int k = 0; k < p.w && k < kHornerK; ++k) {
     // samples at the Chebyshev points u_i of [-1, 1] (t = (u + 1) / 2)
     for (int i = 0; i < N; ++i) {
-      const long double u = cosl(pi * (2 * i + 1) / (2.0L * N));
+      const long double u = cs[(size_t)N + i];
       const long double z = ((long double)k + 0.5L * (u + 1.0L)) / hw - 1.0L;
       const long double a = 1.0L - z * z;
       fv[i] = a >= 0 ? expl(beta * (sqrtl(a) - 1.0L)) : 0.0L;
     }
     for (int m = 0; m < N; ++m) {
       long double acc = 0;
-      for (int i = 0; i < N; ++i) acc += fv[i] * cosl(pi * m * (2 * i + 1) / (2.0L * N));
+      for (int i = 0; i < N; ++i) acc += fv[i] * cs[(size_t)m * N + i];
       ch[m] = (m == 0 ? 1.0L : 2.0L) * acc / N;
     }
     // sum_m ch[m] T_m(u) as a polynomial in u (T_1 = u, T_{m+1} = 2u T_m - T_{m-1})

@@ -38,3 +38,7 @@ def test_batches_take_the_path_that_was_timed_shorter(check):
 
 def test_every_choice_fits_the_kernels(check):
     check("forms")
+
+
+def test_first_call_at_a_tolerance_is_not_held_up_by_its_tables(check):
+    check("time")
