@@ -22,6 +22,7 @@
 #include "api_internal.h"
 #include "batch.h"
 #include "chip.h"
+#include "chip_tables.h"
 #include "fft2.h"
 #include "index_math.h"
 #include "kernels.h"
@@ -440,67 +441,27 @@ int get_plan(mils_context* ctx, int64_t nf, double eps, int prec, int G, PlanEnt
   return MILS_OK;
 }
 
-// Tables of the sub-grids in LDS for tolerance eps: the host's part (the first
-// doubles of the tables), their size, and what finishes them at d.
-struct ChipTables {
-  std::vector<double> host;
-  size_t bytes = 0;
-  size_t o_hc[2], o_z[2], nz[2], o_tw[kChipBatchSizes], o_ph[kChipKinds];
-  ChipPlan plan[kChipKinds] = {};
-};
-
-void make_chip_tables(double eps, ChipTables* t) {
-  auto add = [&](const std::vector<double>& v) {
-    const size_t at = t->host.size();
-    t->host.insert(t->host.end(), v.begin(), v.end());
-    t->host.resize((t->host.size() + 31) & ~(size_t)31);
-    return at;
-  };
-  Plan kern[2] = {};
-  for (int wide = 0; wide < 2; ++wide) {
-    Plan& p = kern[wide];
-    chip_kernel(eps, wide != 0, &p.sigma, &p.w, &p.beta);
-    std::vector<double> z, gphi, hc;
-    phihat_nodes(p, &z, &gphi);
-    make_horner(p, &hc);
-    t->o_hc[wide] = add(hc);
-    t->nz[wide] = z.size();
-    z.insert(z.end(), gphi.begin(), gphi.end());
-    t->o_z[wide] = add(z);
-  }
-  std::vector<double> tw;
-  for (int i = 0; i < kChipBatchSizes; ++i) {
-    make_twiddle2(kChipBatchN[i], &tw);
-    t->o_tw[i] = add(tw);
-  }
-  size_t off = t->host.size();
-  for (int k = 0; k < kChipKinds; ++k) {
-    ChipPlan& c = t->plan[k];
-    const int wide = k / kChipBatchSizes;
-    c.N = kChipBatchN[k % kChipBatchSizes];
-    c.nfmax = (int)std::floor((double)c.N / kern[wide].sigma);
-    c.w = kern[wide].w;
-    c.hw = 0.5 * c.w;
-    t->o_ph[k] = off;
-    off += ((size_t)(c.nfmax / 2 + 1) + 31) & ~(size_t)31;
-  }
-  t->bytes = sizeof(double) * off;
-}
-
-// Uploads t to buf (t->bytes) and waits on stream s; plan[] then points there.
+// Makes the tables t at buf (t.bytes) on stream s and waits; plan[] then points
+// there.
 hipError_t upload_chip_tables(const ChipTables& t, char* buf, ChipPlan* plan, hipStream_t s) {
   double* d = reinterpret_cast<double*>(buf);
-  hipError_t he = hipMemcpyAsync(d, t.host.data(), sizeof(double) * t.host.size(),
-                                 hipMemcpyHostToDevice, s);
+  const std::vector<double> host = make_chip_tables(t);
+  hipError_t he =
+      hipMemcpyAsync(d, host.data(), sizeof(double) * host.size(), hipMemcpyHostToDevice, s);
   for (int k = 0; k < kChipKinds && he == hipSuccess; ++k) {
     const int wide = k / kChipBatchSizes;
-    plan[k] = t.plan[k];
+    const ChipTables::Kind& src = t.kind[k];
     ChipPlan& c = plan[k];
-    c.hcoef = d + t.o_hc[wide];
-    c.tw = d + t.o_tw[k % kChipBatchSizes];
-    c.iph = d + t.o_ph[k];
-    he = launch_phihat(d + t.o_ph[k], c.nfmax / 2, (double)c.w, (double)c.N, d + t.o_z[wide],
-                       d + t.o_z[wide] + t.nz[wide], (int)t.nz[wide], s);
+    c.N = src.N;
+    c.nfmax = src.nfmax;
+    c.w = src.w;
+    c.hw = 0.5 * src.w;
+    c.hcoef = d + t.hcoef[wide];
+    c.tw = d + t.tw[k % kChipBatchSizes];
+    c.iph = d + src.iph;
+    const double* z = d + t.nodes[wide];
+    he = launch_phihat(d + src.iph, c.nfmax / 2, (double)c.w, (double)c.N, z, z + t.nnodes[wide],
+                       t.nnodes[wide], s);
   }
   if (he == hipSuccess) he = hipStreamSynchronize(s);
   if (he == hipSuccess) he = chip_prepare();
@@ -515,10 +476,10 @@ const ChipSet* get_chip(mils_context* ctx, double eps, bool make) {
   if (it != ctx->chips.end()) return &it->second;
   if (!make) return nullptr;
   const auto t_build = std::chrono::steady_clock::now();
-  ChipTables t;
-  make_chip_tables(eps, &t);
+  const ChipTables t = layout_chip_tables(eps);
   ChipSet cs;
   cs.bytes = t.bytes;
+  // (before they are made: without room for them, every call comes by here)
   if (ctx->budget && ctx->plan_bytes + ctx->ws_bytes + cs.bytes > ctx->budget) return nullptr;
   if (hipMalloc(reinterpret_cast<void**>(&cs.buf), cs.bytes) != hipSuccess) {
     (void)hipGetLastError();
@@ -1168,8 +1129,7 @@ static int mils_periodogram_noalloc_impl(mils_context* ctx, const double* t, con
   if (kind >= 0) {
     // a short series on sub-grids in LDS, as in mils_periodogram: its tables
     // and statistics in the scratch
-    ChipTables ct;
-    make_chip_tables(p->eps, &ct);
+    const ChipTables ct = layout_chip_tables(p->eps);
     std::lock_guard<std::mutex> lk(g_scratch_mu);
     ScratchTables& res = g_scratch_tables[ctx->device];
     if (!(res.valid && res.chip && res.eps == p->eps)) {

@@ -621,9 +621,10 @@ void make_twiddle2(int L, std::vector<double>* tw) {
   }
 }
 
+int phihat_node_count(int w) { return w + 8; }
+
 void phihat_nodes(const Plan& p, std::vector<double>* z, std::vector<double>* gphi) {
-  int q = 2 * p.w + 16;
-  if (q % 2) ++q;
+  const int q = 2 * phihat_node_count(p.w);
   z->clear();
   gphi->clear();
   const long double pi = 3.14159265358979323846264338327950288L;

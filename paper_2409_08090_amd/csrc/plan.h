@@ -62,6 +62,9 @@ void make_twiddle2(int L, std::vector<double>* tw);
 // the phihat kernel (even rule of q points on [-1, 1], positive half).
 void phihat_nodes(const Plan& p, std::vector<double>* z, std::vector<double>* gphi);
 
+// Number of those nodes for a kernel of w cells.
+int phihat_node_count(int w);
+
 // Monomial coefficients of the kernel polynomials (Chebyshev interpolation of
 // phi((k + t)/hw - 1), t in [0, 1], in long double): coef[j * kHornerK + k],
 // j = 0 the highest degree, horner_n(p.prec) coefficients, k < kHornerK.

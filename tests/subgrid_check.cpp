@@ -1,4 +1,4 @@
-// Host checks of the sub-grids in LDS (plan.cpp, chip_rule.h), built and run by
+// Host checks of the sub-grids in LDS (plan.cpp, chip_rule.h, chip_tables.cpp), built and run by
 // tests/test_subgrid_host.py.  Prints "ok" at the end.
 #include <algorithm>
 #include <chrono>
@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "../paper_2409_08090_amd/csrc/chip_rule.h"
+#include "../paper_2409_08090_amd/csrc/chip_tables.h"
 #include "../paper_2409_08090_amd/csrc/plan.h"
 
 using namespace mils;
@@ -189,12 +190,65 @@ static int host_time() {
   return best > 0.5;
 }
 
+// The tables of a tolerance: the layout, which every call without tables of its
+// own asks for, costs next to nothing; what is made lies where it says, in
+// pieces that do not overlap, and is what the kernels and sizes need.
+static int tables() {
+  int bad = 0;
+  for (double eps : {1e-14, 1e-12, 1e-9, 1e-5, 1e-2}) {
+    double best = 1e9;
+    ChipTables t;
+    for (int rep = 0; rep < 50; ++rep) {
+      const auto t0 = std::chrono::steady_clock::now();
+      t = layout_chip_tables(eps);
+      best = std::min(best, std::chrono::duration<double>(std::chrono::steady_clock::now() - t0)
+                                .count());
+    }
+    if (best > 50e-6) bad += std::printf("layout takes %.0f us\n", 1e6 * best) > 0;
+    const std::vector<double> made = make_chip_tables(t);
+    std::vector<std::pair<size_t, size_t>> used;  // [from, to)
+    auto same = [&](const std::vector<double>& v, size_t at, const char* what) {
+      used.push_back({at, at + v.size()});
+      if (at + v.size() > t.host || std::memcmp(&made[at], v.data(), 8 * v.size()) != 0)
+        bad += std::printf("eps %g: %s\n", eps, what) > 0;
+    };
+    std::vector<double> v, g;
+    for (bool wide : {false, true}) {
+      Plan p{};
+      chip_kernel(eps, wide, &p.sigma, &p.w, &p.beta);
+      make_horner(p, &v);
+      same(v, t.hcoef[wide], "kernel polynomials");
+      phihat_nodes(p, &v, &g);
+      if ((int)v.size() != t.nnodes[wide]) bad += std::printf("nodes\n") > 0;
+      v.insert(v.end(), g.begin(), g.end());
+      same(v, t.nodes[wide], "quadrature nodes");
+      for (int i = 0; i < kChipBatchSizes; ++i) {
+        const ChipTables::Kind& k = t.kind[i + (wide ? kChipBatchSizes : 0)];
+        if (k.w != p.w || k.N != kChipBatchN[i] || (double)k.nfmax * p.sigma > k.N || k.w % 2)
+          bad += std::printf("eps %g: kind of %d cells\n", eps, k.N) > 0;
+        used.push_back({k.iph, k.iph + (size_t)k.nfmax / 2 + 1});
+      }
+    }
+    for (int i = 0; i < kChipBatchSizes; ++i) {
+      make_twiddle2(kChipBatchN[i], &v);
+      same(v, t.tw[i], "roots");
+    }
+    std::sort(used.begin(), used.end());
+    for (size_t i = 0; i + 1 < used.size(); ++i)
+      if (used[i].second > used[i + 1].first) bad += std::printf("pieces overlap\n") > 0;
+    if (made.size() != t.host || 8 * used.back().second > t.bytes)
+      bad += std::printf("sizes\n") > 0;
+  }
+  return bad;
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   const int bad = what == "accuracy" ? accuracy()
                   : what == "choice" ? choice()
                   : what == "forms"  ? forms()
                   : what == "time"   ? host_time()
+                  : what == "tables" ? tables()
                                      : 1;
   if (bad) return 1;
   std::printf("ok\n");

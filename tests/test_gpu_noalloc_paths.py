@@ -1,0 +1,49 @@
+"""The allocation-free call with one path's tables after the other's in its
+scratch: sub-grids in LDS, the split transform, LDS passes and the
+register-tile FFT in turn, at two tolerances, each call made twice and against
+mils_periodogram (same grid and kernel: rounding only)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+from paper_2409_08090_amd import mils, workloads  # noqa: E402
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x, dtype=np.float64)).cuda()
+
+
+def test_tables_of_every_path_in_turn():
+    small, sub = workloads.single_small(seed=1, nd=60, nf=700), workloads.single_small(seed=2, nd=900, nf=9000)
+    mid, big = workloads.single_large(seed=3, nd=9000, span_years=1), workloads.single_large(seed=4, nd=30_000, span_years=2)
+    calls = [(sub, "fp64", 1e-9), (sub, "fp64", 1e-6), (mid, "fp64", 1e-9), (sub, "fp64", 1e-9),
+             (big, "fp64", 1e-9), (small, "fp64", 1e-9), (mid, "fp32", 1e-5), (sub, "fp64", 1e-6),
+             (big, "fp64", 1e-6), (sub, "fp64", 1e-6), (sub, "fp32", 1e-5), (big, "fp64", 1e-9)]
+    a, b = mils.Context(0), mils.Context(0)
+    for i, (c, prec, eps) in enumerate(calls):
+        args = (dev(c.t), dev(c.y), dev(c.dy), c.f0, c.df, c.nf)
+        ref = mils.periodogram(*args, eps=eps, precision=prec, ctx=a).cpu().numpy()
+        for ctx in (a, b):  # the scratch is the GPU's, not the context's
+            p = mils.periodogram_noalloc(*args, eps=eps, precision=prec, ctx=ctx).cpu().numpy()
+            tol = 1e-12 if prec == "fp64" else 1e-6
+            assert np.max(np.abs(p - ref)) <= tol * np.max(np.abs(ref)), (i, c.nd, prec, eps)
+    a.close()
+    b.close()
+
+
+def test_budget_without_room_for_the_sub_grid_tables():
+    """A short series in a context whose budget holds its staged workspace but
+    not the tables of the sub-grids runs staged, call after call."""
+    c = workloads.single_small(seed=5, nd=900, nf=9000)
+    args = (dev(c.t), dev(c.y), dev(c.dy), c.f0, c.df, c.nf)
+    ref = mils.periodogram(*args).cpu().numpy()
+    need = mils.plan_info(c.nd, c.nf, 1e-9)["workspace_bytes"]
+    ctx = mils.Context(0, hbm_budget_bytes=need + (96 << 10))
+    for _ in range(3):
+        p = mils.periodogram(*args, ctx=ctx).cpu().numpy()
+        assert np.max(np.abs(p - ref)) <= 1e-8 * np.max(np.abs(ref))
+    ctx.close()

@@ -17,8 +17,8 @@ pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 def check(tmp_path_factory):
     exe = tmp_path_factory.mktemp("subgrid") / "subgrid_check"
     subprocess.run(["g++", "-O2", "-std=c++17", "-I/opt/rocm/include", "-D__HIP_PLATFORM_AMD__",
-                    os.path.join(HERE, "subgrid_check.cpp"), os.path.join(CSRC, "plan.cpp"), "-o",
-                    str(exe)], check=True)
+                    os.path.join(HERE, "subgrid_check.cpp"), os.path.join(CSRC, "plan.cpp"),
+                    os.path.join(CSRC, "chip_tables.cpp"), "-o", str(exe)], check=True)
 
     def run(what):
         r = subprocess.run([str(exe), what], capture_output=True, text=True, timeout=300)
@@ -42,3 +42,7 @@ def test_every_choice_fits_the_kernels(check):
 
 def test_first_call_at_a_tolerance_is_not_held_up_by_its_tables(check):
     check("time")
+
+
+def test_tables_lie_where_their_layout_says(check):
+    check("tables")
