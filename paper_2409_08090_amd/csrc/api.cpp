@@ -1069,6 +1069,7 @@ struct ScratchTables {
   double eps = 0.0;
   int prec = 0;
   bool fft2 = false;
+  int split = 0;
   int64_t n = 0;
   bool chip = false;  // tables of the sub-grids in LDS (for eps) instead
   ChipPlan plan[kChipKinds] = {};
@@ -1089,14 +1090,16 @@ static int mils_periodogram_noalloc_impl(mils_context* ctx, const double* t, con
   const bool f32 = p->precision == 1;
   auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
   size_t ph_b = 0, tw_b = 0, nd_b = 0, hc_b = 0, p2_b = 0, tables = 0, need = 0;
-  // (the staged passes; where the grid of a split transform does not fit the
-  // scratch, on their own smaller grid)
+  // (where the grid of a split transform does not fit the scratch, the staged
+  // passes on their own smaller grid)
   for (bool split : {true, false}) {
     std::string err;
     PlanRequest r{p->nf, p->eps, p->precision, 3};
     r.fft2 = ctx->fft2;
     r.split = split;
     if (!make_plan(r, &plan, &err)) return fail(ctx, MILS_ERR_UNSUPPORTED, err);
+    Plan two;
+    if (split_plan(plan, &two)) plan = two;
     make_twiddles(&plan, &tw);
     phihat_nodes(plan, &z, &gphi);
     make_horner(plan, &hc);
@@ -1161,7 +1164,7 @@ static int mils_periodogram_noalloc_impl(mils_context* ctx, const double* t, con
     ScratchTables& res = g_scratch_tables[ctx->device];
     const bool same = res.valid && !res.chip && res.nf == p->nf && res.eps == p->eps &&
                       res.prec == p->precision && res.fft2 == (bool)plan.fft2 &&
-                      res.n == plan.n;
+                      res.split == plan.split && res.n == plan.n;
     if (!same) {
       res.valid = false;
       std::vector<float> tw32, hc32;
@@ -1196,7 +1199,11 @@ static int mils_periodogram_noalloc_impl(mils_context* ctx, const double* t, con
       res.eps = p->eps;
       res.prec = p->precision;
       res.fft2 = plan.fft2;
+      res.split = plan.split;
       res.n = plan.n;
+      mils_log(2, "scratch tables nf=%lld eps=%g %s: n=%lld passes=%d%s%s", (long long)p->nf, p->eps,
+               f32 ? "fp32" : "fp64", (long long)plan.n, plan.npass, plan.fft2 ? " fft2" : "",
+               plan.split ? " split" : "");
     }
   }
   Work w{};

@@ -2,6 +2,11 @@
 scratch: sub-grids in LDS, the split transform, LDS passes and the
 register-tile FFT in turn, at two tolerances, each call made twice and against
 mils_periodogram (same grid and kernel: rounding only)."""
+import os
+import re
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
@@ -11,6 +16,8 @@ pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
 
 from paper_2409_08090_amd import mils, workloads  # noqa: E402
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def dev(x):
@@ -47,3 +54,34 @@ def test_budget_without_room_for_the_sub_grid_tables():
         p = mils.periodogram(*args, ctx=ctx).cpu().numpy()
         assert np.max(np.abs(p - ref)) <= 1e-8 * np.max(np.abs(ref))
     ctx.close()
+
+
+# (the grids of the last two fit the scratch only as staged ones, or not split)
+PROBE = """
+import sys
+sys.path.insert(0, {root!r})
+import torch
+from paper_2409_08090_amd import mils
+for nf in (170_003, 480_011, 700_001, 770_001):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    t = torch.sort(torch.rand(9000, generator=g, device="cuda", dtype=torch.float64) * 500.0).values
+    y = torch.randn(9000, generator=g, device="cuda", dtype=torch.float64)
+    p = mils.periodogram_noalloc(t, y, None, 0.001, 0.0004, nf)
+    q = mils.periodogram(t, y, None, 0.001, 0.0004, nf)
+    print("rel", nf, float((p - q).abs().max() / q.abs().max()))
+"""
+
+
+def test_grids_of_a_split_transform_take_it():
+    """A grid that the planner chose for the split transform runs its two
+    passes (the staged ones gain nothing from its size)."""
+    env = dict(os.environ, MILS_LOG_LEVEL="2")
+    r = subprocess.run([sys.executable, "-c", PROBE.format(root=ROOT)], capture_output=True,
+                       text=True, timeout=110, env=env)
+    assert r.returncode == 0, r.stderr[-2000:]
+    tables = re.findall(r"scratch tables nf=(\d+) .*? n=(\d+) passes=(\d+)(.*)", r.stderr)
+    assert [int(x[0]) for x in tables] == [170_003, 480_011, 700_001, 770_001], r.stderr[-2000:]
+    assert all(x[2] == "2" and "split" in x[3] for x in tables[:2]), tables
+    rel = [float(x) for x in re.findall(r"rel \d+ (\S+)", r.stdout)]
+    assert max(rel[:2]) <= 1e-12 and max(rel) <= 1e-8, rel
