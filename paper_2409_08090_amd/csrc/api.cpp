@@ -1956,7 +1956,9 @@ int autotune_batch(mils_context* ctx, int64_t ncurves, const int64_t* nd_off, co
       std::vector<int> tm(sample.size(), cv.second);
       rc = build_batch(ctx, T, sample, sig, tm, nd_off, t, y, dy, nf_off, f0, df, common, power,
                        ncurves, stream, ChipUse::kNone);
-      if (rc == MILS_ERR_UNSUPPORTED) {  // this sigma does not plan for the band
+      // this sigma does not plan for the band, or the sample's grids cannot be
+      // had (the batch itself may do without them: sub-grids in LDS)
+      if (rc == MILS_ERR_UNSUPPORTED || rc == MILS_ERR_OOM) {
         rc = MILS_OK;
         continue;
       }
@@ -1978,6 +1980,7 @@ int autotune_batch(mils_context* ctx, int64_t ncurves, const int64_t* nd_off, co
       }
     }
     if (rc != MILS_OK) break;
+    if (best_ms == 1e300) continue;  // no candidate ran: no decision
     ctx->tuned[key] = best;
     mils_log(2, "tuning: band %d eps %g %s -> sigma %g, tile cap %d (%.3f ms)", kv.first,
              common->eps, prec == 1 ? "fp32" : "fp64", best.first, best.second, best_ms);
