@@ -182,6 +182,11 @@ struct mils_context {
   size_t plan_bytes = 0;
   char* ws = nullptr;
   size_t ws_bytes = 0;
+  size_t ws_refused = 0;  // smallest workspace that the device had no memory for, 0: none
+  // Fault injection for tests of that: with MILS_WORKSPACE_LIMIT=N in the
+  // environment when the context is created, larger workspaces are refused
+  // (on the host; the device is not asked).  0: off.
+  size_t ws_limit = 0;
   // Set once a call has been captured into a caller's graph: that graph
   // holds pointers into the workspace, so a later growth keeps the old
   // buffer (freed with the context) instead of freeing it.
@@ -512,14 +517,17 @@ bool staged_smaller(const PlanEntry& e) { return e.split.split && !e.plan.fft2; 
 
 // Whether a call of nd points may take the grid of a split transform, which
 // can be a quarter larger than the staged one: not where that grid would go
-// over the context's budget (the smaller one may still fit).
+// over the context's budget, nor where the device had no memory for as much
+// before (the smaller one may still fit).
 bool split_fits(mils_context* ctx, int64_t nf, double eps, int prec, int G, bool fft2, int64_t nd,
                 size_t extra) {
-  if (!ctx->budget || prec != 0) return true;
+  if ((!ctx->budget && !ctx->ws_refused) || prec != 0) return true;
   PlanEntry* pe = nullptr;
   if (get_plan(ctx, nf, eps, prec, G, &pe, false, false, 0, 0, fft2) != MILS_OK) return true;
   if (!staged_smaller(*pe)) return true;
   const size_t need = layout_work(pe->split, nd, G, nullptr, nullptr) + extra;
+  if (ctx->ws_refused && need >= ctx->ws_refused && need > ctx->ws_bytes) return false;
+  if (!ctx->budget) return true;
   const size_t tables = pe->tw ? 0 : sizeof(double) * (size_t)pe->plan.K + ((size_t)1 << 20);
   return ctx->plan_bytes + tables + std::max(need, ctx->ws_bytes) <= ctx->budget;
 }
@@ -562,10 +570,13 @@ int ensure_workspace(mils_context* ctx, size_t bytes) {
   }
   char* p = nullptr;
   size_t got = 0;
-  if (malloc_grown(&p, want, bytes, &got) != hipSuccess) {
+  const bool refuse = ctx->ws_limit && bytes > ctx->ws_limit;
+  if (refuse || malloc_grown(&p, ctx->ws_limit ? bytes : want, bytes, &got) != hipSuccess) {
     (void)hipGetLastError();
+    if (!ctx->ws_refused || bytes < ctx->ws_refused) ctx->ws_refused = bytes;
     return fail(ctx, MILS_ERR_OOM, "hipMalloc of the workspace failed");
   }
+  if (got >= ctx->ws_refused) ctx->ws_refused = 0;
   ctx->ws = p;
   ctx->ws_bytes = got;
   mils_log(2, "workspace grown to %.1f MB", (double)got / 1e6);
@@ -877,6 +888,8 @@ int mils_context_create(int device, uint64_t hbm_budget_bytes, mils_context** ou
       delete c;
       return MILS_ERR_DEVICE;
     }
+    if (const char* lim = std::getenv("MILS_WORKSPACE_LIMIT"))
+      c->ws_limit = (size_t)std::strtoull(lim, nullptr, 10);
     if (const char* tf = std::getenv("MILS_TUNE_CACHE")) {
       c->tune_file = tf;
       c->tune_key = tune_device_key(device);
