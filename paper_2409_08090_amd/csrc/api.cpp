@@ -203,6 +203,7 @@ struct mils_context {
   // of their finished workgroups, and where the last one leaves the status
   // (host_status + kChipStatus, as the device addresses it)
   std::map<double, ChipSet> chips;
+  bool no_chips = false;  // given back to a budget without room for them (see without_chips)
   ChipDone* chip_done = nullptr;
   int* chip_status = nullptr;
   // where the last call left its status: DevStats on the device, kChipStatus
@@ -479,7 +480,7 @@ hipError_t upload_chip_tables(const ChipTables& t, char* buf, ChipPlan* plan, hi
 const ChipSet* get_chip(mils_context* ctx, double eps, bool make) {
   auto it = ctx->chips.find(eps);
   if (it != ctx->chips.end()) return &it->second;
-  if (!make) return nullptr;
+  if (!make || ctx->no_chips) return nullptr;
   const auto t_build = std::chrono::steady_clock::now();
   const ChipTables t = layout_chip_tables(eps);
   ChipSet cs;
@@ -501,6 +502,26 @@ const ChipSet* get_chip(mils_context* ctx, double eps, bool make) {
   mils_log(2, "on-chip tables eps=%g: w=%d, %.2f ms", eps, cs.plan[0].w,
            1e3 * std::chrono::duration<double>(std::chrono::steady_clock::now() - t_build).count());
   return &ctx->chips.emplace(eps, cs).first->second;
+}
+
+// run(), and once more without the tables of the sub-grids if the budget has no
+// room for it beside them: what fits without them is not refused because an
+// earlier call made them.  (A captured call's graph holds their address; and the
+// context goes on without, so that calls of both kinds do not make and free
+// them in turn.)
+template <typename F>
+int without_chips(mils_context* ctx, const F& run) {
+  const int rc = run();
+  if (rc != MILS_ERR_OOM || !ctx->budget || ctx->chips.empty() || ctx->captured) return rc;
+  if (hipDeviceSynchronize() != hipSuccess) return rc;
+  for (auto& kv : ctx->chips) {
+    (void)hipFree(kv.second.buf);
+    ctx->plan_bytes -= kv.second.bytes;
+  }
+  ctx->chips.clear();
+  ctx->no_chips = true;
+  ctx->batch.valid = false;  // its launches hold their addresses
+  return run();
 }
 
 // Whether the single-series plan of (nf, eps, prec, G) exists with its device
@@ -1040,8 +1061,10 @@ int mils_trig_sums(mils_context* ctx, const double* t, const double* h, int64_t 
   mils_params p{f0, df, nf, eps, precision, 0, 0};
   rc = check_params(&p);
   if (rc != MILS_OK) return fail(ctx, rc, "invalid parameters");
-  return run_single(ctx, t, nullptr, nullptr, h, nd, &p, nullptr, out,
-                    reinterpret_cast<hipStream_t>(hip_stream), true);
+  return without_chips(ctx, [&] {
+    return run_single(ctx, t, nullptr, nullptr, h, nd, &p, nullptr, out,
+                      reinterpret_cast<hipStream_t>(hip_stream), true);
+  });
 }
 
 int mils_periodogram_async(mils_context* ctx, const double* t, const double* y, const double* dy,
@@ -1049,8 +1072,10 @@ int mils_periodogram_async(mils_context* ctx, const double* t, const double* y, 
   if (!ctx) return MILS_ERR_INVALID_ARG;
   int rc = mils_check_periodogram_args(t, y, nd, p, power);
   if (rc != MILS_OK) return fail(ctx, rc, "invalid periodogram arguments");
-  return run_single(ctx, t, y, dy, nullptr, nd, p, power, nullptr,
-                    reinterpret_cast<hipStream_t>(hip_stream), false);
+  return without_chips(ctx, [&] {
+    return run_single(ctx, t, y, dy, nullptr, nd, p, power, nullptr,
+                      reinterpret_cast<hipStream_t>(hip_stream), false);
+  });
 }
 
 int mils_periodogram(mils_context* ctx, const double* t, const double* y, const double* dy,
@@ -1058,8 +1083,10 @@ int mils_periodogram(mils_context* ctx, const double* t, const double* y, const 
   if (!ctx) return MILS_ERR_INVALID_ARG;
   int rc = mils_check_periodogram_args(t, y, nd, p, power);
   if (rc != MILS_OK) return fail(ctx, rc, "invalid periodogram arguments");
-  return run_single(ctx, t, y, dy, nullptr, nd, p, power, nullptr,
-                    reinterpret_cast<hipStream_t>(hip_stream), true);
+  return without_chips(ctx, [&] {
+    return run_single(ctx, t, y, dy, nullptr, nd, p, power, nullptr,
+                      reinterpret_cast<hipStream_t>(hip_stream), true);
+  });
 }
 
 static int mils_periodogram_noalloc_impl(mils_context* ctx, const double* t, const double* y,
@@ -1297,8 +1324,10 @@ int mils_direct_periodogram(mils_context* ctx, const double* t, const double* y,
   if (!ctx) return MILS_ERR_INVALID_ARG;
   int rc = mils_check_periodogram_args(t, y, nd, p, power);
   if (rc != MILS_OK) return fail(ctx, rc, "invalid periodogram arguments");
-  return run_direct(ctx, t, y, dy, nullptr, nd, p, power, nullptr,
-                    reinterpret_cast<hipStream_t>(hip_stream));
+  return without_chips(ctx, [&] {
+    return run_direct(ctx, t, y, dy, nullptr, nd, p, power, nullptr,
+                      reinterpret_cast<hipStream_t>(hip_stream));
+  });
 }
 
 int mils_direct_trig_sums(mils_context* ctx, const double* t, const double* h, int64_t nd,
@@ -1315,14 +1344,15 @@ int mils_direct_trig_sums(mils_context* ctx, const double* t, const double* h, i
   int rc = check_nd(nd);
   if (rc == MILS_OK) rc = check_params(&p);
   if (rc != MILS_OK) return fail(ctx, rc, "invalid trig-sum arguments");
-  return run_direct(ctx, t, nullptr, nullptr, h, nd, &p, nullptr, out_re_im,
-                    reinterpret_cast<hipStream_t>(hip_stream));
+  return without_chips(ctx, [&] {
+    return run_direct(ctx, t, nullptr, nullptr, h, nd, &p, nullptr, out_re_im,
+                      reinterpret_cast<hipStream_t>(hip_stream));
+  });
 }
 
-int mils_periodogram_shared_t(mils_context* ctx, const double* t, const double* y,
-                              const double* dy, int64_t dy_stride, int64_t nd, int64_t nseries,
-                              const mils_params* p, double* power, int32_t* status_per_series,
-                              void* hip_stream) {
+static int run_shared(mils_context* ctx, const double* t, const double* y, const double* dy,
+                      int64_t dy_stride, int64_t nd, int64_t nseries, const mils_params* p,
+                      double* power, int32_t* status_per_series, void* hip_stream) {
   if (!ctx) return MILS_ERR_INVALID_ARG;
   int rc = mils_check_periodogram_args(t, y, nd, p, power);
   if (rc != MILS_OK) return fail(ctx, rc, "invalid periodogram arguments");
@@ -1466,6 +1496,16 @@ int mils_periodogram_shared_t(mils_context* ctx, const double* t, const double* 
   if (first == MILS_ERR_INVALID_ARG) return fail(ctx, first, "non-finite input or dy <= 0");
   if (first == MILS_ERR_DEGENERATE) return fail(ctx, first, "constant data: zero reference chi^2");
   return MILS_OK;
+}
+
+int mils_periodogram_shared_t(mils_context* ctx, const double* t, const double* y,
+                              const double* dy, int64_t dy_stride, int64_t nd, int64_t nseries,
+                              const mils_params* p, double* power, int32_t* status_per_series,
+                              void* hip_stream) {
+  return without_chips(ctx, [&] {
+    return run_shared(ctx, t, y, dy, dy_stride, nd, nseries, p, power, status_per_series,
+                      hip_stream);
+  });
 }
 
 }  // extern "C"
@@ -2006,10 +2046,10 @@ int autotune_batch(mils_context* ctx, int64_t ncurves, const int64_t* nd_off, co
   return rc;
 }
 
-int mils_batch_run(mils_context* ctx, int64_t ncurves, const int64_t* nd_off, const double* t,
-                   const double* y, const double* dy, const int64_t* nf_off, const double* f0,
-                   const double* df, const mils_params* common, double* power,
-                   int32_t* status_per_curve, void* hip_stream, bool use_graph) {
+static int run_batch(mils_context* ctx, int64_t ncurves, const int64_t* nd_off, const double* t,
+                     const double* y, const double* dy, const int64_t* nf_off, const double* f0,
+                     const double* df, const mils_params* common, double* power,
+                     int32_t* status_per_curve, void* hip_stream, bool use_graph) {
   if (!ctx) return MILS_ERR_INVALID_ARG;
   if (ncurves < 1 || ncurves > (int64_t)0x7fffffff || !nd_off || !nf_off || !f0 || !df ||
       !common || !t || !y || !power)
@@ -2082,7 +2122,8 @@ int mils_batch_run(mils_context* ctx, int64_t ncurves, const int64_t* nd_off, co
                    : ctx->batch_onchip ? ChipUse::kBatch
                                        : ChipUse::kNone);
     // staged series need 48 bytes and more a grid cell, sub-grids 16 a point
-    if (rc == MILS_ERR_OOM && ctx->batch_onchip && prec == 0) rc = build(ChipUse::kAll);
+    if (rc == MILS_ERR_OOM && ctx->batch_onchip && prec == 0 && !ctx->no_chips)
+      rc = build(ChipUse::kAll);
     if (rc != MILS_OK) return rc;
     B.key = key;
     B.valid = true;
@@ -2116,6 +2157,16 @@ int mils_batch_run(mils_context* ctx, int64_t ncurves, const int64_t* nd_off, co
   }
   if (worst != MILS_OK) ctx->err = "some series of the batch have invalid or constant data";
   return worst;
+}
+
+int mils_batch_run(mils_context* ctx, int64_t ncurves, const int64_t* nd_off, const double* t,
+                   const double* y, const double* dy, const int64_t* nf_off, const double* f0,
+                   const double* df, const mils_params* common, double* power,
+                   int32_t* status_per_curve, void* hip_stream, bool use_graph) {
+  return without_chips(ctx, [&] {
+    return run_batch(ctx, ncurves, nd_off, t, y, dy, nf_off, f0, df, common, power,
+                     status_per_curve, hip_stream, use_graph);
+  });
 }
 
 extern "C" {

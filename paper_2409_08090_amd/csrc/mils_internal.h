@@ -152,7 +152,7 @@ struct Work {
   void* f2out;               // two-pass plans: last-pass results, n doubles (power) or double2 (sums)
   double* lowpart;        // per-block partial direct sums near f = 0
   double* lowfix;         // direct sums A, B, B2 near f = 0: rows of kLowMax x 6 that the
-                          // last pass adds (kLowParts, or up to kLowRows of a fused call)
+                          // last pass adds (kLowParts, or low_fused_rows of a fused call)
   uint64_t* keys;         // det_keys(nd) sort keys of the reproducible binning
   double* rec;            // on-chip series of a batch: nd pairs (w^ y~, w^)
 };

@@ -684,7 +684,9 @@ size_t layout_work(const Plan& p, int64_t nd, int G, char* base, Work* w, bool p
   }
   if (!per_series) x.lowpart = reinterpret_cast<double*>(take(sizeof(double) * 6 * kLowMax * kLowBlocks));
   if (!per_series) x.keys = reinterpret_cast<uint64_t*>(take(sizeof(uint64_t) * det_keys(nd)));
-  x.lowfix = reinterpret_cast<double*>(take(sizeof(double) * 6 * kLowMax * (per_series ? 1 : kLowRows)));
+  const int lowrows =
+      per_series ? 1 : nd <= kLowFusedNd ? std::max(kLowParts, low_fused_rows(nd)) : kLowParts;
+  x.lowfix = reinterpret_cast<double*>(take(sizeof(double) * 6 * kLowMax * lowrows));
   // (whole words: the spread reads four flags at a time)
   x.rowflag_f = reinterpret_cast<unsigned char*>(take((p.nrows + 3) & ~(int64_t)3));
   x.rowflag_2f = reinterpret_cast<unsigned char*>(take((p.nrows + 3) & ~(int64_t)3));

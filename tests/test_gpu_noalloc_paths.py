@@ -85,3 +85,53 @@ def test_grids_of_a_split_transform_take_it():
     assert all(x[2] == "2" and "split" in x[3] for x in tables[:2]), tables
     rel = [float(x) for x in re.findall(r"rel \d+ (\S+)", r.stdout)]
     assert max(rel[:2]) <= 1e-12 and max(rel) <= 1e-8, rel
+
+
+def test_sub_grid_tables_make_room_for_a_larger_call():
+    """A budget that holds a short and then a longer call on their staged grids
+    holds them too when the short one ran on sub-grids and left their tables:
+    every way through an entry point that allocates."""
+    c = workloads.single_small(seed=6, nd=400, nf=4000)
+    short = (dev(c.t), dev(c.y), dev(c.dy), c.f0, c.df, c.nf)
+    rng = np.random.default_rng(1)
+    nd, nf = 20_000, 60_000
+    t, y = dev(np.sort(rng.uniform(0.0, 100.0, nd))), dev(rng.normal(0.0, 1.0, nd))
+    y2 = torch.stack([y, y * y])
+
+    def long_call(kind, ctx):
+        if kind == "periodogram":
+            return mils.periodogram(t, y, None, 0.002, 0.002, nf, ctx=ctx)
+        if kind == "sums":
+            return mils.trig_sums(t, y, 0.002, 0.002, nf, ctx=ctx).abs()
+        if kind == "shared":
+            return mils.periodogram_shared_t(t, y2, None, 0.002, 0.002, nf, ctx=ctx)[0]
+        off, foff = np.array([0, nd], dtype=np.int64), np.array([0, nf], dtype=np.int64)
+        one = np.array([0.002])
+        return mils.periodogram_batch(t, y, None, off, foff, one, one, ctx=ctx)
+
+    def fits(kind, budget, staged):
+        ctx = mils.Context(0, hbm_budget_bytes=budget)
+        try:
+            mils.periodogram(*short, deterministic=staged, ctx=ctx)
+            p = long_call(kind, ctx)
+            mils.periodogram(*short, ctx=ctx)
+            return p
+        except mils.MilsError as e:
+            assert e.status == mils.MILS_ERR_OOM
+            return None
+        finally:
+            ctx.close()
+
+    for kind in ("periodogram", "sums", "shared", "batch"):
+        ref = long_call(kind, mils.default_context(0))
+        lo, hi = 1 << 20, 1 << 26  # refused, held
+        assert fits(kind, lo, True) is None and fits(kind, hi, True) is not None
+        while hi - lo > 4096:
+            mid = (lo + hi) // 2
+            if fits(kind, mid, True) is None:
+                lo = mid
+            else:
+                hi = mid
+        p = fits(kind, hi, False)
+        assert p is not None, (kind, hi)
+        assert float((p - ref).abs().max() / ref.abs().max()) <= 1e-8
