@@ -202,7 +202,12 @@ constexpr int kLowBlocks = 512;
 __host__ __device__ inline bool split_passes(const Plan& p) {
   return p.split > 0 && p.npass == 2 && !p.fft2;
 }
-constexpr int kSplitMax = 16;  // most residues of a split transform
+// Most residues of a split transform.  Every residue reads the rows that are
+// reached, all of them with a frequency step of the inverse time span or more:
+// at that step 12 and 15 residues are slower than the three passes they replace
+// (N_f = 2.0e7: 2.22 -> 2.73 ms, raw sums of 1.8e7 0.84 -> 0.93), 10 are not
+// (1.6e7: 1.84 -> 1.61).
+constexpr int kSplitMax = 10;
 constexpr int kLowParts = 8;  // rows of lowfix (partial sums; the last pass adds them)
 // Calls of at most kLowFusedNd points form them in workgroups of the spread's
 // launch, one row per 2048 points up to kLowRows (a quarter of the frequencies

@@ -6,7 +6,7 @@
 //   Y(s, rho + R kappa) = sum_a e(a kappa / La) [ e(a rho / (R La))
 //                                 sum_r e(r rho / R) x(a + La r, s) ],
 // a fold of the column to La cells and one transform of that length per
-// residue, so that R may be any number while the lines stay powers of two in
+// residue, so that R may be any number (up to kSplitMax) while the lines stay powers of two in
 // registers (fft2.h: 16 cells a thread).  The fold only reads the rows that a
 // kernel support reaches: with the usual frequency step of 1/5 of the inverse
 // time span those are a fifth (geometry f) and two fifths (2f) of the rows, so
@@ -69,9 +69,10 @@ __global__ __launch_bounds__(NT, 4) void k_split_first(Fft2Bufs<double> b, FftPa
   const int lane = tid & 63;
   // Row flags, one load for four r: lane 16 i + q holds those of the wave's
   // rows of element q, a bit a row.
-  unsigned fl[kSplitMax / 4];
+  constexpr int kFlags = (kSplitMax + 3) / 4;
+  unsigned fl[kFlags];
 #pragma unroll
-  for (int i = 0; i < kSplitMax / 4; ++i) {
+  for (int i = 0; i < kFlags; ++i) {
     fl[i] = 0;
     const int r = 4 * i + (lane >> 4);
     if (r < R) {
@@ -106,7 +107,7 @@ __global__ __launch_bounds__(NT, 4) void k_split_first(Fft2Bufs<double> b, FftPa
   for (int r = 1; r < R; ++r) {
     unsigned f = fl[0];
 #pragma unroll
-    for (int i = 1; i < kSplitMax / 4; ++i)
+    for (int i = 1; i < kFlags; ++i)
       if (r >= 4 * i) f = fl[i];
     const int r4 = 16 * (r & 3);
     const unsigned qm = (unsigned)(__ballot(f != 0) >> r4) & 0xffffu;
