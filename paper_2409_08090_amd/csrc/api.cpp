@@ -441,9 +441,13 @@ int get_plan(mils_context* ctx, int64_t nf, double eps, int prec, int G, PlanEnt
   const double build_s =
       std::chrono::duration<double>(std::chrono::steady_clock::now() - t_build).count();
   ctx->plan_build_s += build_s;
-  mils_log(2, "plan nf=%lld eps=%g %s%s: n=%lld w=%d passes=%d%s, %.2f ms", (long long)nf, eps,
+  char shape[64] = "";
+  if (e.split.split)
+    std::snprintf(shape, sizeof(shape), " split %d x %d x %d", e.split.split, e.split.la,
+                  e.split.pass[1].L);
+  mils_log(2, "plan nf=%lld eps=%g %s%s: n=%lld w=%d passes=%d%s%s, %.2f ms", (long long)nf, eps,
            prec == 1 ? "fp32" : "fp64", batch ? " batch" : "", (long long)e.plan.n, e.plan.w,
-           e.plan.npass, e.plan.fft2 ? " two-pass" : "", build_s * 1e3);
+           e.plan.npass, e.plan.fft2 ? " two-pass" : "", shape, build_s * 1e3);
   return MILS_OK;
 }
 
