@@ -6,9 +6,11 @@
 // N >= 1.36 nf / D cells.  With D chosen so that N is one of a few powers of
 // two, one workgroup takes one rho: it spreads all points of the series onto
 // its grids in LDS, transforms them there and writes its share of the power.
-// Nothing but the points and the power crosses HBM, no grid size needs a plan
-// of its own, and a series is spread over D workgroups.  Every point is
-// visited by D workgroups, so this is the cheaper way up to a limit on nd.
+// Nothing but the points and the power crosses HBM, the tables serve every
+// number of frequencies, and a series is spread over D workgroups.  (A single
+// call and one of shared times still make the staged plan of their size, which
+// profiled, reproducible and refused calls fall back on.)  Every point is
+// visited by D workgroups: the cheaper way for short series (chip_rule.h).
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -1,13 +1,14 @@
 // chip.hip -- periodograms on grids in LDS, one workgroup per residue of the
 // frequency index (gfx950); see chip.h.
 //
-// What bounds it: a visit of a point to one grid is ~300 FP64 instructions
-// (coordinate, phase, w polynomials, 2 w products) and 2 w LDS atomic adds,
-// and every point is visited by all D workgroups of its series.  HBM sees
-// only the points and the power, so the time is arithmetic and LDS.  Cells k
-// and w - 1 - k of a point share the even and odd parts of one polynomial
-// (the kernel is even), which halves the evaluation; one point per thread
-// leaves each wave's adds on 64 different runs of cells.
+// What bounds it: every point is visited by all D workgroups of its series, and
+// HBM sees only the points and the power, so the time is FP64 arithmetic and LDS
+// adds.  A lane works out the coordinate and phase of one point; then 16 lanes
+// take one point's cells, each lane with the polynomial of its own cell in
+// registers (a second set for kernels of 17 to 20 cells), so that four points
+// of the wave cost one evaluation by Horner's rule, two products and two LDS
+// adds a grid.  A row's adds are one run of cells; with a point per lane the
+// 64 runs of a wave's add collide in the banks (9 LDS cycles against 26).
 #include <hip/hip_runtime.h>
 
 #include <mutex>

@@ -85,7 +85,6 @@ __global__ __launch_bounds__(kThreads) void k_spread_pg(CallArgs a, Plan p, Work
                                    p, w, st, w.grid[2], w.grid[2], acc);
 }
 
-// The same with fixed summation orders.
 // The A spreads of NG series that share their times and weights, with their
 // direct sums (the first 4 lowrows NG workgroups; their statistics are there).
 // One launch instead of a spread and two kernels of direct sums a series: 160
@@ -118,6 +117,7 @@ __global__ __launch_bounds__(kThreads) void k_spread_series(CallArgs a, Plan p, 
                                                      w.grid[1], acc, w.grid[2]);
 }
 
+// k_spread_rows with fixed summation orders.
 template <typename Real, int GEO, int NG>
 __global__ __launch_bounds__(kThreads) void k_spread_det(CallArgs a, Plan p, Work w, void* out0,
                                                          void* out1) {
