@@ -735,28 +735,19 @@ CallArgs single_args(const double* t, const double* y, const double* dy, const d
   return a;
 }
 
-// Kind (see ChipSet) of a single-series call that runs in LDS, -1: staged.
-// One workgroup takes about 8 us and 0.011 us a point (measured at 100 to 8000
-// points) and the chip holds one per CU; the staged kernels of a short series
-// take about 60 us (launches) and 70 us per 1e6 frequencies.
+// Kind (see ChipSet) of a single-series call, or one of series that share their
+// times, that runs in LDS, -1: staged.
 int chip_single_kind(mils_context* ctx, const Plan& plan, const CallArgs& a) {
   if (plan.prec != 0 || a.deterministic) return -1;
+  // (a grid of one staged pass takes the widest kernel here as there)
+  const bool wide = plan.npass == 1;
   double sigma, beta;
-  int w, best = -1;
-  chip_kernel(a.dmin, false, &sigma, &w, &beta);
-  double best_us = 60.0 + 70e-6 * (double)a.nf;
-  for (int i = 0; i < 2; ++i) {  // 256 and 1024 cells
-    const int N = kChipBatchN[i];
-    const int64_t D = chip_residues(a.nf, (int)std::floor((double)N / sigma));
-    const double rounds = std::ceil((double)(D + kLowMax) / ctx->num_cu);
-    const double us = rounds * ((N > 256 ? 10.0 : 8.0) + 0.011 * (double)a.nd);
-    if (us < best_us) {
-      best_us = us;
-      best = i;
-    }
-  }
-  // (a grid of one staged pass takes the widest kernel there too)
-  return best >= 0 && plan.npass == 1 ? best + kChipBatchSizes : best;
+  int w, nfmax[2];
+  chip_kernel(a.dmin, wide, &sigma, &w, &beta);
+  for (int i = 0; i < 2; ++i) nfmax[i] = (int)std::floor((double)kChipBatchN[i] / sigma);
+  const int i = chiprule::choose_single(chiprule::Rule{nfmax, ctx->num_cu, w > 16},
+                                        a.periodogram != 0, a.nd, a.nf);
+  return i >= 0 && wide ? i + kChipBatchSizes : i;
 }
 
 // Common body of the single-series calls.

@@ -1,8 +1,7 @@
-// chip_rule.h -- which FP64 series of a batch run on sub-grids in LDS (chip.h)
-// and on which size, by estimated time (host only, no HIP: a host build checks
-// it).
+// chip_rule.h -- which FP64 series run on sub-grids in LDS (chip.h) and on which
+// size, by estimated time (host only, no HIP: a host build checks it).
 //
-// The estimates are fits to batches of 1 to 1000 equal series of 100 to 25000
+// The estimates for batches are fits to batches of 1 to 1000 equal series of 100 to 25000
 // points at 1 to 100 frequencies a point, every size of sub-grid and the staged
 // phases timed at each (270 layouts; eps = 1e-9): a workgroup takes a + b nd us
 // (of a full chip's time, or alone, when the call waits for it), and a call of
@@ -15,6 +14,7 @@
 #pragma once
 
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <vector>
 
@@ -179,6 +179,50 @@ inline int choose_alone(const Rule& r, int64_t nd, int64_t nf) {
   one.add(nd, nf);
   for (int k = 0; k < 16; ++k) many.add(nd, nf);
   return best <= 1.05 * (call_us(r, {}, one) + call_us(r, {}, many)) ? size : -1;
+}
+
+// ---- single calls ---------------------------------------------------------------
+// A single call (pg false: of raw sums), on the first two sizes; series that
+// share their times take the same, so that their results are the single calls'.
+// Fits to 2 to 8000 points at 100 to 6e6 frequencies, within 8 %: a call takes
+// 27 us and a round of workgroups, one a CU, `first` alone or `each` with more
+// behind it, and `b` a point.  The staged kernels take 60 us of launches, a
+// share a frequency (two passes; the split transform beyond 1.6e5) and, where
+// few frequencies leave the spread few tiles, a share a point.  At 3e6
+// frequencies and 100 points: 16 rounds 286 us, staged 195; at 1.2e4 and 1000
+// 41 and 59.
+struct Round {
+  double first, each, b;
+};
+constexpr Round kRound[2] = {{7.5, 13.0, 7.5e-3}, {10.0, 15.5, 6.8e-3}};
+constexpr Round kRoundSums[2] = {{7.0, 9.8, 3.8e-3}, {7.8, 11.0, 3.8e-3}};
+
+inline double single_us(const Rule& r, int i, bool pg, int64_t nd, int64_t nf) {
+  const Round& q = pg ? kRound[i] : kRoundSums[i];
+  // (a periodogram has one more workgroup for each frequency near f = 0)
+  const double blocks = (double)(chip_residues(nf, r.nfmax[i]) + (pg ? 16 : 0));
+  const double rounds = std::ceil(blocks / r.num_cu);
+  const double b = q.b * (r.two_sets ? (pg ? 1.75 : 1.55) : 1.0);
+  return 27.0 + rounds * ((rounds > 1.0 ? q.each : q.first) + b * (double)nd);
+}
+inline double single_staged_us(bool pg, int64_t nd, int64_t nf) {
+  const double share = pg ? 4.5e-5 : 2.2e-5;
+  const double tiles = (double)nd * (pg ? std::min(16.5e-3, 10.0 / (double)nf)
+                                        : std::min(14e-3, 25.0 / (double)nf));
+  return (pg && nf > 160000 ? 68.0 : 60.0) + share * (double)nf + tiles;
+}
+// Size (0 or 1) of the sub-grids of such a call, -1: staged.
+inline int choose_single(const Rule& r, bool pg, int64_t nd, int64_t nf) {
+  double best = single_staged_us(pg, nd, nf);
+  int size = -1;
+  for (int i = 0; i < 2; ++i) {
+    const double us = single_us(r, i, pg, nd, nf);
+    if (us < best) {
+      best = us;
+      size = i;
+    }
+  }
+  return size;
 }
 
 }  // namespace chiprule

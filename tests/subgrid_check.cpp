@@ -123,6 +123,38 @@ static int choice() {
   return bad;
 }
 
+// Single calls and raw sums, timed staged and on either size (us): the rule
+// takes one within 12 % of the shortest.
+static int single() {
+  const struct {
+    bool pg;
+    int nd, nf;
+    double us[3];  // staged, 256 cells, 1024 cells
+  } timed[] = {
+      {true, 100, 1200, {57.4, 34.5, 36.4}},       {true, 1000, 12000, {58.6, 39.7, 41.5}},
+      {true, 3000, 48000, {60.8, 71.6, 56.6}},     {true, 5000, 30000, {61.0, 75.3, 71.6}},
+      {true, 6000, 72000, {62.7, 140.3, 79.3}},    {true, 8000, 12000, {62.4, 100.3, 100.3}},
+      {true, 8000, 100, {189.7, 157.1, 158.4}},    {true, 2, 200000, {89.6, 95.8, 56.0}},
+      {true, 100, 500000, {99.4, 180.7, 73.9}},    {true, 100, 2000000, {154.0, 604.8, 204.0}},
+      {true, 100, 3000000, {194.9, 893.4, 286.0}}, {true, 2, 6000000, {358.4, 1792.0, 560.8}},
+      {true, 3000, 200000, {76.8, 203.1, 96.0}},   {false, 100, 12000, {60.2, 34.5, 35.4}},
+      {false, 8000, 3000, {128.8, 63.6, 63.5}},    {false, 3000, 100000, {63.4, 87.6, 46.3}},
+      {false, 100, 2000000, {104.3, 462.3, 153.5}}, {false, 100, 3000000, {125.7, 680.2, 211.6}},
+      {false, 1000, 500000, {69.9, 170.8, 70.2}}};
+  const Sizes s;
+  int bad = 0;
+  for (const auto& x : timed) {
+    const int i = chiprule::choose_single(s.rule(), x.pg, x.nd, x.nf);
+    const double best = std::min(x.us[0], std::min(x.us[1], x.us[2]));
+    if (x.us[i + 1] > 1.12 * best) {
+      std::printf("%s %d points, %d frequencies: size %d takes %.1f us, best %.1f\n",
+                  x.pg ? "power" : "sums", x.nd, x.nf, i, x.us[i + 1], best);
+      ++bad;
+    }
+  }
+  return bad;
+}
+
 // Every choice is one that the kernels can take: a size whose residues hold the
 // series, staged beyond the range of the rule unless the series is short enough
 // for one workgroup, and with `all` whatever can be is on sub-grids.
@@ -246,6 +278,7 @@ int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   const int bad = what == "accuracy" ? accuracy()
                   : what == "choice" ? choice()
+                  : what == "single" ? single()
                   : what == "forms"  ? forms()
                   : what == "time"   ? host_time()
                   : what == "tables" ? tables()

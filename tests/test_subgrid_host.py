@@ -36,6 +36,10 @@ def test_batches_take_the_path_that_was_timed_shorter(check):
     check("choice")
 
 
+def test_single_calls_take_the_path_that_was_timed_shorter(check):
+    check("single")
+
+
 def test_every_choice_fits_the_kernels(check):
     check("forms")
 
