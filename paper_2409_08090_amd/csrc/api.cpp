@@ -1168,17 +1168,21 @@ static int mils_periodogram_noalloc_impl(mils_context* ctx, const double* t, con
     // a short series on sub-grids in LDS, as in mils_periodogram: its tables
     // and statistics in the scratch
     const ChipTables ct = layout_chip_tables(p->eps);
-    std::lock_guard<std::mutex> lk(g_scratch_mu);
-    ScratchTables& res = g_scratch_tables[ctx->device];
-    if (!(res.valid && res.chip && res.eps == p->eps)) {
-      res.valid = false;
-      he = upload_chip_tables(ct, base, res.plan, stream);
-      if (he != hipSuccess) return hip_fail(ctx, he, "scratch plan upload");
-      res.valid = true;
-      res.chip = true;
-      res.eps = p->eps;
+    ChipPlan cp;
+    {
+      // (not while the call runs: calls on other GPUs go on meanwhile)
+      std::lock_guard<std::mutex> lk(g_scratch_mu);
+      ScratchTables& res = g_scratch_tables[ctx->device];
+      if (!(res.valid && res.chip && res.eps == p->eps)) {
+        res.valid = false;
+        he = upload_chip_tables(ct, base, res.plan, stream);
+        if (he != hipSuccess) return hip_fail(ctx, he, "scratch plan upload");
+        res.valid = true;
+        res.chip = true;
+        res.eps = p->eps;
+      }
+      cp = res.plan[kind];
     }
-    const ChipPlan cp = res.plan[kind];
     DevStats* st = reinterpret_cast<DevStats*>(base + up(ct.bytes));
     he = launch_chip_single(a, cp, (int)chip_residues(p->nf, cp.nfmax), st, ctx->chip_done,
                             ctx->chip_status, 1, 0, stream);
