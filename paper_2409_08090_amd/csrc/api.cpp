@@ -510,9 +510,10 @@ const ChipSet* get_chip(mils_context* ctx, double eps, bool make) {
 
 // run(), and once more without the tables of the sub-grids if the budget has no
 // room for it beside them: what fits without them is not refused because an
-// earlier call made them.  (A captured call's graph holds their address; and the
-// context goes on without, so that calls of both kinds do not make and free
-// them in turn.)
+// earlier call made them.  (A captured call's graph holds their address.)  The
+// context then goes on without, so that calls of both kinds do not make and free
+// them in turn; a call that does not fit without them either changes nothing for
+// the ones after it.
 template <typename F>
 int without_chips(mils_context* ctx, const F& run) {
   const int rc = run();
@@ -525,7 +526,9 @@ int without_chips(mils_context* ctx, const F& run) {
   ctx->chips.clear();
   ctx->no_chips = true;
   ctx->batch.valid = false;  // its launches hold their addresses
-  return run();
+  const int again = run();
+  if (again == MILS_ERR_OOM) ctx->no_chips = false;
+  return again;
 }
 
 // Whether the single-series plan of (nf, eps, prec, G) exists with its device

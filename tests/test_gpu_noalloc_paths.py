@@ -135,3 +135,40 @@ def test_sub_grid_tables_make_room_for_a_larger_call():
         p = fits(kind, hi, False)
         assert p is not None, (kind, hi)
         assert float((p - ref).abs().max() / ref.abs().max()) <= 1e-8
+
+
+REFUSED = """
+import sys
+sys.path.insert(0, {root!r})
+import torch
+from paper_2409_08090_amd import mils
+g = torch.Generator(device="cuda")
+g.manual_seed(1)
+t = torch.sort(torch.rand(400, generator=g, device="cuda", dtype=torch.float64) * 50.0).values
+y = torch.randn(400, generator=g, device="cuda", dtype=torch.float64)
+ctx = mils.Context(0, hbm_budget_bytes=32 << 20)
+ref = mils.periodogram(t, y, None, 0.002, 0.002, 4000, ctx=ctx)
+for i in range(2):
+    print("refused", i, file=sys.stderr, flush=True)
+    try:
+        mils.periodogram(t, y, None, 0.002, 0.002, 4_000_000, ctx=ctx)
+        print("not refused")
+    except mils.MilsError as e:
+        assert e.status == mils.MILS_ERR_OOM
+    for k in range(2):
+        p = mils.periodogram(t, y, None, 0.002, 0.002, 4000, ctx=ctx)
+        assert float((p - ref).abs().max() / ref.abs().max()) <= 1e-12
+ctx.close()
+print("ok")
+"""
+
+
+def test_a_call_larger_than_the_budget_leaves_sub_grids_on():
+    """One that the budget has no room for at all is refused; short calls after
+    it take the sub-grids as before it."""
+    env = dict(os.environ, MILS_LOG_LEVEL="2")
+    r = subprocess.run([sys.executable, "-c", REFUSED.format(root=ROOT)], capture_output=True,
+                       text=True, timeout=110, env=env)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", (r.stdout, r.stderr[-2000:])
+    parts = r.stderr.split("refused ")
+    assert [len(re.findall("on-chip tables", x)) for x in parts] == [1, 1, 1], r.stderr[-3000:]
