@@ -14,6 +14,7 @@
 #include <cstdarg>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -242,6 +243,8 @@ struct mils_context {
   } sg;
   // batch autotuner: (N_f band, eps, precision) -> (sigma, largest spreading tile)
   std::map<std::tuple<int, double, int>, std::pair<double, int>> tuned;
+  // ... the bands that there was no memory to time a candidate for
+  std::set<std::tuple<int, double, int>> untunable;
   std::string tune_file;  // MILS_TUNE_CACHE at creation ("" = none)
   std::string tune_key;   // this device's key in that file
 };
@@ -1999,7 +2002,7 @@ int autotune_batch(mils_context* ctx, int64_t ncurves, const int64_t* nd_off, co
   BatchState T;
   for (auto& kv : bands) {
     const auto key = std::make_tuple(kv.first, common->eps, prec);
-    if (ctx->tuned.count(key) || (int)kv.second.size() < kTuneMin) continue;
+    if (ctx->tuned.count(key) || ctx->untunable.count(key) || (int)kv.second.size() < kTuneMin) continue;
     std::vector<int64_t> sample;
     const int64_t nb = (int64_t)kv.second.size();
     const int64_t ns = std::min<int64_t>(nb, kTuneSample);
@@ -2035,7 +2038,10 @@ int autotune_batch(mils_context* ctx, int64_t ncurves, const int64_t* nd_off, co
       }
     }
     if (rc != MILS_OK) break;
-    if (best_ms == 1e300) continue;  // no candidate ran: no decision
+    if (best_ms == 1e300) {  // no candidate ran: no decision, nor another try on every call
+      ctx->untunable.insert(key);
+      continue;
+    }
     ctx->tuned[key] = best;
     mils_log(2, "tuning: band %d eps %g %s -> sigma %g, tile cap %d (%.3f ms)", kv.first,
              common->eps, prec == 1 ? "fp32" : "fp64", best.first, best.second, best_ms);

@@ -1,5 +1,9 @@
 """Batches whose staged grids the context's budget has no room for, while the
 16 bytes a point that sub-grids in LDS need fit."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
@@ -33,3 +37,33 @@ def test_batch_on_sub_grids_where_staged_grids_do_not_fit(count):
                 assert np.max(np.abs(q[nf_off[c] + k] - ref)) <= 1e-8 * np.max(np.abs(ref))
     finally:
         ctx.close()
+
+
+REPEAT = """
+import sys
+sys.path.insert(0, {root!r})
+import numpy as np
+from paper_2409_08090_amd import mils, workloads
+rng = np.random.default_rng(20)
+t, y, dy, nd_off, nf_off, f0, df = mils.pack_curves([workloads.batch_curve(rng, 6000) for _ in range(20)])
+ctx = mils.Context(0, hbm_budget_bytes=6 << 20)
+for i in range(3):
+    print("call", i, file=sys.stderr, flush=True)
+    mils.periodogram_batch(t, y, dy, nd_off, nf_off, f0, df, ctx=ctx)
+ctx.close()
+print("ok")
+"""
+
+
+def test_refused_candidates_are_tried_once():
+    """The tuner tries a band's candidates on the first call only, also when
+    there was memory for none."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    env = dict(os.environ, MILS_LOG_LEVEL="2")
+    env.pop("MILS_TUNE_CACHE", None)
+    r = subprocess.run([sys.executable, "-c", REPEAT.format(root=root)], capture_output=True,
+                       text=True, timeout=110, env=env)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stderr[-2000:]
+    first, second, third = r.stderr.split("call ")[1:]
+    assert "HBM budget" in first, first
+    assert "HBM budget" not in second + third, second + third
